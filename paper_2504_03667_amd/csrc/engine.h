@@ -115,17 +115,37 @@ __host__ __device__ constexpr uint64_t tag_word(uint32_t tag, uint32_t value) {
 }
 __host__ __device__ constexpr uint32_t word_tag(uint64_t w) { return (uint32_t)(w >> 32); }
 
-// A gang's tagged records of the Dijkstra rounds, as a structure of arrays:
-// for each slot (exchange parity) and field, nwg consecutive words (member g at
-// index g), so that a wave reading the words of 64 consecutive members touches
-// four cache lines instead of one per member.  Fields: the dist of the
-// member's key (0xffffffff: no key), the key's vertex, and (count << 1) | the
-// zero-weight hazard flag; each word tagged.  The fourth field is unused
-// (32 bytes per member and slot).
-enum { kRecDist = 0, kRecVert = 1, kRecCnt = 2, kRecFields = 4 };
+// A gang's tagged records of the Dijkstra rounds: 64 bytes per member, its
+// record of exchange parity 0 in the first half and of parity 1 in the second,
+// so that no two members ever store into the same 64-byte line.  (Packed side by
+// side, 16 members' stores share a line whose ownership moves between the XCDs:
+// an exchange of 256 members with three packed words each took 2.7 us in a
+// loop of bare exchanges, two words in a line of their own 1.7 us; 64 members
+// 1.9 and 1.2 us.)  A record is two words: kRecDist holds the dist of the
+// member's key (0xffffffff: no key) under a 32-bit tag, kRecRest the rest of the
+// record (rec_rest) under a 21-bit tag.  The last two words are unused.
+enum { kRecDist = 0, kRecRest = 1, kRecFields = 4 };
 __host__ __device__ inline uint64_t* rec_word(uint64_t* recs, int nwg, uint32_t slot, int field, int g) {
-    return recs + ((size_t)slot * kRecFields + (size_t)field) * (size_t)nwg + (size_t)g;
+    (void)nwg;
+    return recs + ((size_t)g * 2 + slot) * kRecFields + (size_t)field;
 }
+
+// The second word of a record: the lowest vertex of the member's key (24 bits:
+// at most 1024 members of at most 16384 columns), the number of its columns at
+// that dist (15 bits), the zero-weight hazard flag, and the low 21 bits of the
+// tag, which tell exchange b from b - 2, the only other one whose word the slot
+// can hold (or from the cleared word, before the tag first wraps).  Bit 63 stays
+// clear (see exchange_stamp).
+constexpr int kRestCountShift = 24, kRestZeroShift = 39, kRestTagShift = 42;
+constexpr uint32_t kRestTagMask = 0x1fffffu;
+__host__ __device__ constexpr uint64_t rec_rest(uint32_t tag, uint32_t vertex, uint32_t count, uint32_t zero) {
+    return ((uint64_t)(tag & kRestTagMask) << kRestTagShift) | ((uint64_t)zero << kRestZeroShift) |
+           ((uint64_t)count << kRestCountShift) | (vertex & 0xffffffu);
+}
+__host__ __device__ constexpr uint32_t rest_tag(uint64_t w) { return (uint32_t)(w >> kRestTagShift); }
+__host__ __device__ constexpr uint32_t rest_vertex(uint64_t w) { return (uint32_t)w & 0xffffffu; }
+__host__ __device__ constexpr uint32_t rest_count(uint64_t w) { return (uint32_t)(w >> kRestCountShift) & 0x7fffu; }
+__host__ __device__ constexpr uint32_t rest_zero(uint64_t w) { return (uint32_t)(w >> kRestZeroShift) & 1u; }
 
 template <typename X>
 __device__ __forceinline__ X ld_agent(const X* p) {
@@ -221,6 +241,41 @@ __device__ __forceinline__ uint32_t wave_scan32(uint32_t x) {
     const uint32_t r0 = lane_value(x, 15), r1 = lane_value(x, 31), r2 = lane_value(x, 47);
     const int row = wave_lane() >> 4;
     return x + (row >= 1 ? r0 : 0u) + (row >= 2 ? r1 : 0u) + (row >= 3 ? r2 : 0u);
+}
+
+// The same for 32-bit values, in six DPP steps and one v_readlane: the rows'
+// results are passed on by row_bcast15 / row_bcast31 (lane 15 of a row to the
+// next row, lane 31 to the upper half), so that lane 63 ends with the wave's.
+// A DPP operand needs no 64-bit compare and select: with reductions over 64-bit
+// keys a round of the whole-GPU solve (n=16384) took 1.1 us to publish and 0.8 us
+// to reduce the records, with these and ballots 0.5 and 0.4 to 0.6 us (one wave
+// runs straight-line code at about ten cycles an instruction).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp32(uint32_t old, uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_min32(uint32_t x) {
+    x = min(x, dpp32<0x111, 0xf>(~0u, x));
+    x = min(x, dpp32<0x112, 0xf>(~0u, x));
+    x = min(x, dpp32<0x114, 0xf>(~0u, x));
+    x = min(x, dpp32<0x118, 0xf>(~0u, x));
+    x = min(x, dpp32<0x142, 0xa>(~0u, x));  // row_bcast15 into rows 1 and 3
+    x = min(x, dpp32<0x143, 0xc>(~0u, x));  // row_bcast31 into rows 2 and 3
+    return lane_value(x, kWave - 1);
+}
+__device__ __forceinline__ uint32_t wave_prefix32(uint32_t x) {  // inclusive prefix sum
+    x += dpp32<0x111, 0xf>(0u, x);
+    x += dpp32<0x112, 0xf>(0u, x);
+    x += dpp32<0x114, 0xf>(0u, x);
+    x += dpp32<0x118, 0xf>(0u, x);
+    x += dpp32<0x142, 0xa>(0u, x);
+    x += dpp32<0x143, 0xc>(0u, x);
+    return x;
+}
+__device__ __forceinline__ uint64_t wave_mask(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+// set bits of a wave mask below this lane
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 // LDS scratch for block-wide reductions (one slot per wave).
@@ -383,13 +438,17 @@ __device__ __forceinline__ X key_min(X a, X b) {
 
 // Columns of the slice held by one thread: G groups of 4.  dist and pred stay in
 // registers for the whole solve and are written out once at the end (a8), so no
-// per-column output address is kept live across the rounds.
+// per-column output address is kept live across the rounds.  x is a column's
+// dist (at most INT32_MAX) while it is open, and with kSettled set once it is
+// settled; 0xffffffff for a position that is no column of the slice or matrix,
+// or that another thread owns.  So one unsigned comparison tells an open column,
+// a settled one never wins a minimum, and there is no visited mask to test.
+constexpr uint32_t kSettled = 0x80000000u;
 template <int G, typename E = int32_t>
 struct Cols {
-    uint32_t dist[G][4];
+    uint32_t x[G][4];
     int32_t pred[G][4];
     key_t<E> best[G][4];
-    uint32_t vis;  // bit 4k+j: visited, or not a column of the slice/matrix
 };
 
 // The matrix always lives in global memory (device or pinned host memory).
@@ -448,48 +507,64 @@ __device__ __forceinline__ void unpack<uint8_t>(const uint32_t& x, uint32_t (&w)
     w[3] = x >> 24;
 }
 
-// Rows list[r], list[r + P], ... of one column group (4 columns starting at p0
-// within each row) into `best`.  FULL: the 4 entries exist and are aligned for
-// one load; otherwise only the first `valid` are read, one by one.  NT: the
-// loads carry the nontemporal hint, for matrices streamed once per solve (the
-// whole-GPU solve) rather than reused from the caches across instances.
-template <int U, bool FULL, typename E, bool NT>
-__device__ __forceinline__ void stream_group(key_t<E> (&best)[4], const E* __restrict__ p0, int64_t ld,
-                                             int valid, const int32_t* list, int m, int first, int step) {
-    for (int i = first; i < m; i += step * U) {
-        // past the end of the list, repeat its last row: a duplicate cannot change a minimum
-        uint32_t uu[U];
+// Rows list[i], list[i + step], ... (U of them) of one column group (4 columns
+// starting at p0 within each row) into `best`; past the end of the list its last
+// row is repeated (a duplicate cannot change a minimum).  FULL: the 4 entries
+// exist and are aligned for one load; otherwise only the first `valid` are
+// read, one by one.  NT: the loads carry the nontemporal hint, for matrices
+// streamed once per solve (the whole-GPU solve) rather than reused from the
+// caches across instances.
+template <int U, bool FULL, typename E, bool NT, typename R>
+__device__ __forceinline__ void stream_batch(key_t<E> (&best)[4], const E* __restrict__ p0, int64_t ld, int valid,
+                                             const R* list, int m, int i, int step) {
+    uint32_t uu[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        const int idx = i + q * step;
+        uu[q] = (uint32_t)list[idx < m ? idx : m - 1];
+    }
+    uint32_t w[U][4];
+    if (FULL) {
+        // issue all U loads before using any of them: keeps U rows in flight per thread
+        typename Raw<E>::type raw[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            const int idx = i + q * step;
-            uu[q] = (uint32_t)list[idx < m ? idx : m - 1];
+            const global_ptr<typename Raw<E>::type> a =
+                reinterpret_cast<global_ptr<typename Raw<E>::type>>((global_ptr<E>)p0 + (int64_t)uu[q] * ld);
+            raw[q] = NT ? __builtin_nontemporal_load(a) : *a;
         }
-        uint32_t w[U][4];
-        if (FULL) {
-            // issue all U loads before using any of them: keeps U rows in flight per thread
-            typename Raw<E>::type raw[U];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int q = 0; q < U; ++q) {
-                const global_ptr<typename Raw<E>::type> a =
-                    reinterpret_cast<global_ptr<typename Raw<E>::type>>((global_ptr<E>)p0 + (int64_t)uu[q] * ld);
-                raw[q] = NT ? __builtin_nontemporal_load(a) : *a;
-            }
-            __builtin_amdgcn_sched_barrier(0);
+        for (int q = 0; q < U; ++q) unpack<E>(raw[q], w[q]);
+    } else {
 #pragma unroll
-            for (int q = 0; q < U; ++q) unpack<E>(raw[q], w[q]);
-        } else {
+        for (int q = 0; q < U; ++q) {
+            const global_ptr<E> p = (global_ptr<E>)p0 + (int64_t)uu[q] * ld;
 #pragma unroll
-            for (int q = 0; q < U; ++q) {
-                const global_ptr<E> p = (global_ptr<E>)p0 + (int64_t)uu[q] * ld;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) w[q][j] = j < valid ? (uint32_t)p[j] : absent_code<E>();
-            }
+            for (int j = 0; j < 4; ++j) w[q][j] = j < valid ? (uint32_t)p[j] : absent_code<E>();
         }
-#pragma unroll
-        for (int q = 0; q < U; ++q)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) best[j] = key_min(best[j], key_make<E>(w[q][j], uu[q]));
     }
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) best[j] = key_min(best[j], key_make<E>(w[q][j], uu[q]));
+}
+
+// Rows list[first], list[first + step], ... of one column group, U in flight,
+// for the partitions first = 0 .. step - 1.  A list that gives a partition only
+// one or two rows (small rounds) is read in a batch of that size: with eight loads
+// of the same row a one-row round's stream took 1.2 us, with one 0.8 us (n=4096,
+// 64 workgroups).
+template <int U, bool FULL, typename E, bool NT, typename R>
+__device__ __forceinline__ void stream_group(key_t<E> (&best)[4], const E* __restrict__ p0, int64_t ld,
+                                             int valid, const R* list, int m, int first, int step) {
+    if (m <= 2 * step) {
+        if (first >= m) return;
+        if (m <= step) stream_batch<1, FULL, E, NT>(best, p0, ld, valid, list, m, first, step);
+        else stream_batch<2, FULL, E, NT>(best, p0, ld, valid, list, m, first, step);
+        return;
+    }
+    for (int i = first; i < m; i += step * U) stream_batch<U, FULL, E, NT>(best, p0, ld, valid, list, m, i, step);
 }
 
 // Stream rows list[r], list[r + P], ... (m entries in `list`, partition r) of
@@ -498,10 +573,10 @@ __device__ __forceinline__ void stream_group(key_t<E> (&best)[4], const E* __res
 // matrix (<= S).  `vec`: row segments are aligned for whole-group loads (W
 // aligned, ld and the slice start multiples of 4); otherwise, and for a
 // partial last group, entries are read one by one.
-template <int G, int U, typename E, bool NT = false>
+template <int G, int U, typename E, bool NT = false, typename R = int32_t>
 __device__ __forceinline__ void stream_rows(Cols<G, E>& cs, const Layout& lo, const E* __restrict__ W,
                                             int64_t ld, int64_t col0, int width, bool vec,
-                                            const int32_t* list, int m) {
+                                            const R* list, int m) {
     // One column group at a time keeps only U x 4 weights live per thread.
 #pragma unroll
     for (int k = 0; k < G; ++k) {
@@ -591,48 +666,47 @@ __device__ __forceinline__ int local_col(const Layout& lo, int k, int j) {
     return 4 * (lo.c + k * lo.L) + j;
 }
 
-// Initialise the owned columns: dist = inf (0 at the source), pred = -1, not
-// visited; columns past the slice/matrix are flagged visited so they never take part.
+// Initialise the owned columns: dist = inf (0 at the source), pred = -1, open.
 template <int G, typename E>
 __device__ __forceinline__ void init_cols(Cols<G, E>& cs, const Layout& lo, int64_t col0, int width,
                                           int32_t src) {
-    cs.vis = 0;
 #pragma unroll
     for (int k = 0; k < G; ++k)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int v = local_col(lo, k, j);
             const bool mine = lo.r == 0 && k * lo.L + lo.c < lo.NG && v < width;
-            cs.dist[k][j] = (mine && col0 + v == src) ? 0u : kInf;
+            cs.x[k][j] = !mine ? 0xffffffffu : col0 + v == src ? 0u : kInf;
             cs.pred[k][j] = -1;
-            if (!mine) cs.vis |= 1u << (4 * k + j);
         }
     reset_best(cs);
 }
 
-// Lowest (dist, vertex) key among unvisited owned columns.
+// Settle the open columns at dist d (the round's bucket), or, with `step`, only
+// the one whose bit is in `only`; the mask of the columns settled.
 template <int G, typename E>
-__device__ __forceinline__ uint64_t local_argmin(const Cols<G, E>& cs, const Layout& lo, int64_t col0) {
-    uint64_t key = kNoKey;
-#pragma unroll
-    for (int k = 0; k < G; ++k)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (!(cs.vis >> (4 * k + j) & 1u))
-                key = umin64(key, make_key(cs.dist[k][j], (uint32_t)(col0 + local_col(lo, k, j))));
-    return key;
-}
-
-// Bitmask of unvisited owned columns whose dist equals d (the round's bucket).
-template <int G, typename E>
-__device__ __forceinline__ uint32_t bucket_mask(const Cols<G, E>& cs, uint32_t d) {
+__device__ __forceinline__ uint32_t settle(Cols<G, E>& cs, uint32_t d, bool step, uint32_t only) {
     uint32_t m = 0;
 #pragma unroll
     for (int k = 0; k < G; ++k)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (!(cs.vis >> (4 * k + j) & 1u) && cs.dist[k][j] == d) m |= 1u << (4 * k + j);
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t bit = 1u << (4 * k + j);
+            const bool take = cs.x[k][j] == d && (!step || (only & bit));
+            if (take) m |= bit;
+            cs.x[k][j] |= take ? kSettled : 0u;
+        }
     return m;
+}
+
+// Undo settle for the columns of its mask (a discarded round).
+template <int G, typename E>
+__device__ __forceinline__ void reopen(Cols<G, E>& cs, uint32_t mask) {
+#pragma unroll
+    for (int k = 0; k < G; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (mask >> (4 * k + j) & 1u) cs.x[k][j] &= ~kSettled;
 }
 
 // Candidate dist of a column from the round's minimum key (d + min weight);
@@ -648,52 +722,39 @@ __device__ __forceinline__ uint32_t candidate(key_t<E> best, uint32_t d, uint32_
     return d + w;  // d < 2^31-1 and w <= 2^31-1: no wrap
 }
 
-// Zero-weight hazard of a fused round: an unvisited vertex outside the bucket
-// (dist > d) reachable from the bucket by a weight-0 edge would join the bucket
-// during the round and change the order Algorithm 1 settles it in.
+// Dist of the open columns if the pending round (bucket dist d) is applied; a
+// position that is not open keeps its x, which is above every dist.  `neg` gets
+// its sign bit set if a negative weight was the best candidate of a column: every
+// owned column has met at least one row, so its key is a weight's.
+// With the bucket settled beforehand, a candidate equal to d exists exactly when
+// the bucket has a zero-weight edge to an open vertex outside it: such a vertex
+// would join the bucket during the round and change the order Algorithm 1
+// settles it in (the zero-weight hazard of a fused round).
 template <int G, typename E>
-__device__ __forceinline__ uint32_t zero_hazard(const Cols<G, E>& cs, uint32_t d) {
-    uint32_t z = 0;
-#pragma unroll
-    for (int k = 0; k < G; ++k)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (!(cs.vis >> (4 * k + j) & 1u) && cs.dist[k][j] > d &&
-                key_weight<E>(cs.best[k][j]) == 0u)
-                z = 1;
-    return z;
-}
-
-// Apply a fused round: the bucket (mask) becomes visited; every other unvisited
-// column takes its candidate if strictly smaller (pred = the candidate's row).
-template <int G, typename E>
-__device__ __forceinline__ uint32_t commit_fused(Cols<G, E>& cs, uint32_t d, uint32_t bucket) {
-    uint32_t neg = 0;
-    cs.vis |= bucket;
+__device__ __forceinline__ void candidates(const Cols<G, E>& cs, uint32_t d, uint32_t (&cand)[G][4], uint32_t& neg) {
 #pragma unroll
     for (int k = 0; k < G; ++k)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if (cs.vis >> (4 * k + j) & 1u) continue;
-            const uint32_t c = candidate<E>(cs.best[k][j], d, neg);
-            if (c < cs.dist[k][j]) {
-                cs.dist[k][j] = c;
-                cs.pred[k][j] = (int32_t)key_row<E>(cs.best[k][j]);
-            }
+            const uint32_t x = cs.x[k][j], w = key_weight<E>(cs.best[k][j]);
+            // saturating: a weight above INT32_MAX (a negative one) offers nothing
+            cand[k][j] = (int32_t)x >= 0 ? min(x, __builtin_elementwise_add_sat(d, w)) : x;
+            neg |= w & ~x;
         }
-    reset_best(cs);
-    return neg;
 }
 
-// Would-be dist of a column if the pending fused round were applied (kNoKey-style
-// sentinel 0xffffffff for columns that are visited or in the bucket).
+// Apply a round: every open column takes its candidate if strictly smaller
+// (pred = the candidate's row).
 template <int G, typename E>
-__device__ __forceinline__ uint32_t would_be(const Cols<G, E>& cs, int k, int j, uint32_t d,
-                                             uint32_t bucket, uint32_t& neg) {
-    const uint32_t bit = 1u << (4 * k + j);
-    if ((cs.vis | bucket) & bit) return 0xffffffffu;
-    const uint32_t c = candidate<E>(cs.best[k][j], d, neg);
-    return c < cs.dist[k][j] ? c : cs.dist[k][j];
+__device__ __forceinline__ void commit(Cols<G, E>& cs, const uint32_t (&cand)[G][4]) {
+#pragma unroll
+    for (int k = 0; k < G; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (cand[k][j] < cs.x[k][j]) cs.pred[k][j] = (int32_t)key_row<E>(cs.best[k][j]);
+            cs.x[k][j] = cand[k][j];
+        }
+    reset_best(cs);
 }
 
 // Write the owned dist and pred values out (a8: writeback): one 16-byte store
@@ -709,14 +770,14 @@ __device__ __forceinline__ void write_out(const Cols<G, E>& cs, const Layout& lo
         int32_t* dp = dist + col0 + v0;
         int32_t* pp = pred + col0 + v0;
         if (v0 + 3 < width && (((uintptr_t)dp | (uintptr_t)pp) & 15u) == 0) {
-            *reinterpret_cast<v4i*>(dp) = v4i{(int)cs.dist[k][0], (int)cs.dist[k][1], (int)cs.dist[k][2],
-                                              (int)cs.dist[k][3]};
+            *reinterpret_cast<v4i*>(dp) = v4i{(int)(cs.x[k][0] & kInf), (int)(cs.x[k][1] & kInf),
+                                              (int)(cs.x[k][2] & kInf), (int)(cs.x[k][3] & kInf)};
             *reinterpret_cast<v4i*>(pp) = v4i{cs.pred[k][0], cs.pred[k][1], cs.pred[k][2], cs.pred[k][3]};
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (v0 + j < width) {
-                    dp[j] = (int32_t)cs.dist[k][j];
+                    dp[j] = (int32_t)(cs.x[k][j] & kInf);
                     pp[j] = cs.pred[k][j];
                 }
         }

@@ -56,8 +56,9 @@ __global__ __launch_bounds__(T) void k_single(const int32_t* __restrict__ W, int
 
 // BAL: pair balancing of large rounds (solve_gang); chosen by the launcher for
 // graphs large enough to have them, since its code costs the small rounds a few
-// registers.
-template <int T, int G, int U, bool BAL>
+// registers.  NARROW: slices of at most 256 columns and at most 256 workgroups
+// (every n up to 65536 on 256 compute units), without the code of the others.
+template <int T, int G, int U, bool BAL, bool NARROW>
 __global__ __launch_bounds__(T) void k_grid(const int32_t* __restrict__ W, int64_t ld, int32_t n,
                                             int32_t src, int32_t* __restrict__ dist,
                                             int32_t* __restrict__ pred, uint32_t flags, int32_t S,
@@ -65,7 +66,7 @@ __global__ __launch_bounds__(T) void k_grid(const int32_t* __restrict__ W, int64
     SharedSolve<T>& sh = g_sh<T>;
     SolveStats st = {0, 0, 0, 0, 0};
     const uint32_t epoch = ld_agent(&ctl->epoch);
-    solve_gang<T, G, U, int32_t, true, BAL>(W, ld, n, src, dist, pred, (flags & kFlagVec) != 0, (flags & kFlagLiteral) != 0, S,
+    solve_gang<T, G, U, int32_t, true, BAL, NARROW>(W, ld, n, src, dist, pred, (flags & kFlagVec) != 0, (flags & kFlagLiteral) != 0, S,
                         blockIdx.x, gridDim.x, timeout, grid_words(words, gridDim.x, S), sh, st, ctl, epoch);
     finish_launch(ctl, st, blockIdx.x == 0);
 }
@@ -418,7 +419,7 @@ hipError_t launch_single(const SolveArgs& a, int threads, hipStream_t s) {
 
 int max_single_n() { return 4 * 4 * 1024; }
 
-template <int T, int G, int U, bool BAL>
+template <int T, int G, int U, bool BAL, bool NARROW = false>
 static hipError_t launch_grid_t(const SolveArgs& a, int nwg, int S, long long timeout, char* words, bool plain,
                                 hipStream_t s) {
     const int32_t* W = a.W;
@@ -429,18 +430,21 @@ static hipError_t launch_grid_t(const SolveArgs& a, int nwg, int S, long long ti
     uint32_t flags = a.flags;
     Ctl* ctl = a.ctl;
     if (plain) {
-        hipLaunchKernelGGL((k_grid<T, G, U, BAL>), dim3(nwg), dim3(T), 0, s, W, ld, n, src, dist, pred, flags, S,
+        hipLaunchKernelGGL((k_grid<T, G, U, BAL, NARROW>), dim3(nwg), dim3(T), 0, s, W, ld, n, src, dist, pred, flags, S,
                            timeout, ctl, words);
         return hipGetLastError();
     }
     void* args[] = {&W, &ld, &n, &src, &dist, &pred, &flags, &S, &timeout, &ctl, &words};
-    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_grid<T, G, U, BAL>), dim3(nwg),
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_grid<T, G, U, BAL, NARROW>), dim3(nwg),
                                       dim3(T), args, 0, s);
 }
 
 hipError_t launch_grid(const SolveArgs& a, int nwg, int S, long long timeout, char* words, bool plain, bool balance,
                        hipStream_t s) {
     const int groups = (S + 3) / 4;
+    if (groups <= kWave && nwg <= 4 * kWave)
+        return balance ? launch_grid_t<1024, 1, 8, true, true>(a, nwg, S, timeout, words, plain, s)
+                       : launch_grid_t<1024, 1, 8, false, true>(a, nwg, S, timeout, words, plain, s);
     if (!balance) {
         if (groups <= 1024) return launch_grid_t<1024, 1, 8, false>(a, nwg, S, timeout, words, plain, s);
         if (groups <= 2048) return launch_grid_t<1024, 2, 8, false>(a, nwg, S, timeout, words, plain, s);
@@ -457,10 +461,10 @@ int max_grid_slice() { return 4 * 4 * 1024; }
 
 int grid_occupancy(int slice, int* per_cu) {
     const int groups = (slice + 3) / 4;
-    // both balancing variants have the same launch bounds and LDS
-    const void* f = groups <= 1024 ? reinterpret_cast<const void*>(&k_grid<1024, 1, 8, true>)
-                  : groups <= 2048 ? reinterpret_cast<const void*>(&k_grid<1024, 2, 8, true>)
-                                   : reinterpret_cast<const void*>(&k_grid<1024, 4, 8, true>);
+    // every variant has the same launch bounds and LDS
+    const void* f = groups <= 1024 ? reinterpret_cast<const void*>(&k_grid<1024, 1, 8, true, false>)
+                  : groups <= 2048 ? reinterpret_cast<const void*>(&k_grid<1024, 2, 8, true, false>)
+                                   : reinterpret_cast<const void*>(&k_grid<1024, 4, 8, true, false>);
     return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, f, 1024, 0);
 }
 

@@ -6,29 +6,39 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "engine.h"
 #include "sssp_internal.h"
 
 namespace sssp {
 
 constexpr int kCap = 1024;  // bucket rows staged in LDS per chunk
+constexpr int kSingleMax = 16384;  // vertices of the largest one-workgroup solve (4 groups of 4 x 1024 threads)
 constexpr uint32_t kPairChunks = 8;  // chunks from which a round is balanced within pairs (solve_gang)
 constexpr uint32_t kPairUnit = 256;  // rows per claim unit of a balanced round
 
 template <int T>
 struct SharedSolve {
     Red<T> red;
-    int32_t list[kCap];
+    union {
+        int32_t list[kCap];
+        uint16_t list16[kSingleMax];  // solve_single: the whole bucket
+    };
     uint64_t mrg[4 * T];
     uint32_t pre[T];
     uint32_t cnt[T];
-    uint64_t rk;  // read_records results for the whole workgroup
+    uint64_t rk;  // results for the whole workgroup (lc.h, multi.h)
     uint32_t rz, rm;
+    struct alignas(16) {
+        uint32_t d, vert, rows, flags;
+    } res;  // read_records results for the whole workgroup
     uint32_t claim[2];    // chunk claims of a balanced round, broadcast by thread 0
-    uint32_t late;        // a member's record did not arrive in time (read_records)
     uint32_t stage_late;  // a bucket entry did not arrive in time (set once; the solve then ends)
     int32_t item;
     uint32_t flag;
+    uint64_t min3[3];   // solve_single: lowest key of a round, by round number mod 3
+    uint32_t count3[3];  // ... and its bucket's size
 };
 
 struct SolveStats {
@@ -52,6 +62,15 @@ __device__ __forceinline__ uint32_t owner_bit(const Layout& lo, int64_t v, int w
 
 // ---------------------------------------------------------------------------
 // One workgroup, whole row.
+//
+// A round settles the bucket, streams its rows (sh.list16), merges the row
+// partitions, and finds the next minimum and its bucket in one go.  It is bound
+// by that chain, not by bytes, so it has as few workgroup barriers as the data
+// needs: one when the merge is complete, one when the next minimum is known,
+// one when the next bucket is listed (in no particular order: a round's result
+// is a minimum over its rows).  When the owners fit in wave 0 (n <= 256) it finds
+// both by itself and the second barrier falls away.  (Nine barriers and four
+// block reductions before: n=256, p=0.1, 36 rounds, 97 us a call, now 70.)
 // ---------------------------------------------------------------------------
 template <int T, int G, int U, typename E>
 __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld, int32_t n, int32_t src,
@@ -61,70 +80,110 @@ __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld
     Cols<G, E> cs;
     init_cols(cs, lo, 0, n, src);
     clear_merge<T>(sh.mrg, 4 * T);
+    if (threadIdx.x < 3) {
+        sh.min3[threadIdx.x] = kNoKey;
+        sh.count3[threadIdx.x] = 0;
+    }
+    if (threadIdx.x == 0) sh.list16[0] = (uint16_t)src;
+    __syncthreads();
+    uint32_t d = 0, u0 = (uint32_t)src, M = 1;
+    bool redo = false;  // the round repeats the last one as one literal step (zero-weight hazard)
+    uint32_t slot = 0;  // exchanges so far mod 3
+    uint32_t neg = 0;
+    uint32_t cand[G][4];
     for (;;) {
-        // a2/a3: argmin over unvisited vertices, lowest index on ties
-        uint64_t key = local_argmin(cs, lo, 0);
-        uint32_t none = 0;
-        block_min_or<T>(key, none, sh.red);
-        const uint32_t d = (uint32_t)(key >> 32);
-        if (key == kNoKey || d >= kInf) break;  // a4: nothing reachable is left
-        const uint32_t u0 = (uint32_t)key;
-        const long long t_round = wall_clock64();
-        uint32_t bucket;
-        uint32_t M;
-        if (literal) {
-            bucket = owner_bit(lo, u0, n);
+        const long long t_round = trace ? wall_clock64() : 0;
+        const bool step = literal || redo;
+        const uint32_t bucket = settle(cs, d, step, step ? owner_bit(lo, (int64_t)u0, n) : 0u);
+        stream_rows<G, U, E>(cs, lo, W, ld, 0, n, vec, sh.list16, (int)M);
+        merge_partitions<T, G>(cs, lo, sh.mrg);
+        if (!redo) {
+            ++st.rounds;
+            if (trace && threadIdx.x == 0 && st.rounds <= (unsigned long long)kTraceCap) {
+                trace->trace_t[st.rounds - 1] = t_round;
+                trace->trace_m[st.rounds - 1] = M;
+            }
+        }
+        // the would-be state and its lowest (dist, vertex)
+        candidates(cs, d, cand, neg);
+        const bool owners = threadIdx.x < (unsigned)lo.L;  // whole waves, or the first lanes of wave 0
+        if (threadIdx.x < (unsigned)max(lo.L, kWave)) {
+            uint32_t dmin = 0xffffffffu;
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) dmin = min(dmin, cand[k][j]);
+            dmin = wave_min32(dmin);
+            uint32_t low = ~0u;
+#pragma unroll
+            for (int k = G - 1; k >= 0; --k)
+#pragma unroll
+                for (int j = 3; j >= 0; --j)
+                    if (cand[k][j] == dmin) low = (uint32_t)local_col(lo, k, j);
+            low = wave_min32(low);
+            if (wave_lane() == 0)
+                __hip_atomic_fetch_min(&sh.min3[slot], make_key(dmin, low), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        __syncthreads();
+        const uint64_t key = sh.min3[slot];
+        // the slot after the next one: its last readers passed the barrier before this one
+        const uint32_t after = slot == 0 ? 2 : slot - 1;
+        if (threadIdx.x == 0) {
+            sh.min3[after] = kNoKey;
+            sh.count3[after] = 0;
+        }
+        const uint32_t dn = (uint32_t)(key >> 32);
+        if (!step && dn == d) {
+            // zero-weight hazard: discard the fused round and settle only u0, the
+            // bucket's lowest vertex (one literal step)
+            ++st.fallbacks;
+            st.status |= kStatusZeroFallback;
+            reopen(cs, bucket);
+            reset_best(cs);
+            redo = true;
             M = 1;
-            if (threadIdx.x == 0) sh.list[0] = (int32_t)u0;
+            if (threadIdx.x == 0) sh.list16[0] = (uint16_t)u0;
             __syncthreads();
-            stream_rows<G, U, E>(cs, lo, W, ld, 0, n, vec, sh.list, 1);
+            slot = slot == 2 ? 0 : slot + 1;
+            continue;
+        }
+        redo = false;
+        // a5/a6: relax
+        if (lo.r == 0) commit(cs, cand);
+        else reset_best(cs);
+        st.settled += M;
+        if (dn >= kInf) break;  // a4: nothing reachable is left
+        d = dn;
+        u0 = (uint32_t)key;
+        // a2/a3: the next bucket
+        if (literal) {
+            M = 1;
+            if (threadIdx.x == 0) sh.list16[0] = (uint16_t)u0;
+            __syncthreads();
         } else {
-            bucket = bucket_mask(cs, d);
-            const uint32_t base = block_excl_scan<T>(__popc(bucket), M, sh.red);
-            for (uint32_t e0 = 0; e0 < M; e0 += kCap) {
-                uint32_t rank = base;
+            if (owners) {
 #pragma unroll
                 for (int k = 0; k < G; ++k)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (bucket >> (4 * k + j) & 1u) {
-                            if (rank >= e0 && rank < e0 + kCap)
-                                sh.list[rank - e0] = local_col(lo, k, j);
-                            ++rank;
-                        }
-                __syncthreads();
-                stream_rows<G, U, E>(cs, lo, W, ld, 0, n, vec, sh.list, (int)min((uint32_t)kCap, M - e0));
-                __syncthreads();
+                    for (int j = 0; j < 4; ++j) {
+                        const uint64_t at = wave_mask(cs.x[k][j] == d);
+                        if (!at) continue;
+                        uint32_t base = 0;
+                        const int lead = __ffsll((unsigned long long)at) - 1;
+                        if (wave_lane() == lead)
+                            base = __hip_atomic_fetch_add(&sh.count3[slot], (uint32_t)__popcll(at), __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_WORKGROUP);
+                        base = lane_value(base, lead);
+                        if (cs.x[k][j] == d) sh.list16[base + lanes_below(at)] = (uint16_t)local_col(lo, k, j);
+                    }
             }
+            __syncthreads();
+            M = sh.count3[slot];
         }
-        merge_partitions<T, G>(cs, lo, sh.mrg);
-        ++st.rounds;
-        if (trace && threadIdx.x == 0 && st.rounds <= (unsigned long long)kTraceCap) {
-            trace->trace_t[st.rounds - 1] = t_round;
-            trace->trace_m[st.rounds - 1] = M;
-        }
-        if (!literal) {
-            uint32_t z = lo.r == 0 ? zero_hazard(cs, d) : 0u;
-            uint64_t dummy = kNoKey;
-            block_min_or<T>(dummy, z, sh.red);
-            if (z) {
-                // discard the fused round; settle only u0 (one literal step)
-                ++st.fallbacks;
-                st.status |= kStatusZeroFallback;
-                reset_best(cs);
-                if (threadIdx.x == 0) sh.list[0] = (int32_t)u0;
-                __syncthreads();
-                stream_rows<G, U, E>(cs, lo, W, ld, 0, n, vec, sh.list, 1);
-                merge_partitions<T, G>(cs, lo, sh.mrg);
-                bucket = owner_bit(lo, u0, n);
-                M = 1;
-            }
-        }
-        // a5/a6: settle the bucket and relax
-        if (lo.r == 0) st.status |= commit_fused(cs, d, bucket);
-        else reset_best(cs);
-        st.settled += M;
+        slot = slot == 2 ? 0 : slot + 1;
     }
+    if (neg & kSettled) st.status |= kStatusNegWeight;
     write_out(cs, lo, 0, n, dist, pred);  // a8
     if (trace && threadIdx.x == 0) {
         const unsigned long long nr = st.rounds < (unsigned long long)kTraceCap ? st.rounds : kTraceCap;
@@ -248,27 +307,62 @@ __device__ __forceinline__ void clear_tagged(uint64_t* __restrict__ recs, uint64
 }
 
 // Publish this workgroup's record for exchange `tag`: the lowest (dist, vertex)
-// key among `cand` (one would-be dist per owned column, 0xffffffff = excluded),
-// the vertices of the slice at that dist (list entries; none if `entries` is
-// false) and the zero-weight hazard flag, every word tagged.  Nothing waits for
-// the stores: readers check each word's tag.
-template <int T, int G>
-__device__ __forceinline__ void publish(const uint32_t (&cand)[G][4], const Layout& lo, int64_t col0,
-                                        uint32_t zero, bool entries, uint32_t tag, uint64_t* __restrict__ recs,
-                                        int nwg, int g, uint64_t* __restrict__ list, SharedSolve<T>& sh) {
+// key among `cand` (one would-be dist per owned column; 0x80000000 and above =
+// settled or no column), the vertices of the slice at that dist (list entries;
+// none if `entries` is false) and, for a fused round of dist d, the zero-weight
+// hazard flag (a candidate still at d, see candidates), every word tagged.
+// Nothing waits for the stores: readers check each word's tag.
+template <int T, int G, bool NARROW>
+__device__ __forceinline__ void publish(const uint32_t (&cand)[G][4], const Layout& lo, int64_t col0, uint32_t d,
+                                        bool fused, bool entries, uint32_t tag, uint64_t* __restrict__ recs, int nwg,
+                                        int g, uint64_t* __restrict__ list, SharedSolve<T>& sh) {
+    uint64_t* rec = rec_word(recs, nwg, (tag - 1) & 1, 0, g);
+    if (NARROW || (G == 1 && lo.L <= kWave)) {
+        // the owners are lanes of wave 0, 4 ascending columns each: one 32-bit
+        // minimum, the rest from ballots
+        if (threadIdx.x >= kWave) return;
+        const uint32_t dmin = wave_min32(min(min(cand[0][0], cand[0][1]), min(cand[0][2], cand[0][3])));
+        uint64_t at[4];
+        uint32_t total = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            at[j] = wave_mask(cand[0][j] == dmin);  // of no interest when dmin >= kInf: the solve ends
+            total += (uint32_t)__popcll(at[j]);
+        }
+        // the lane of the lowest vertex stores the record
+        if (wave_lane() == (int)__builtin_ctzll(at[0] | at[1] | at[2] | at[3])) {
+            stress_delay(2u * tag);
+            const int j = cand[0][0] == dmin ? 0 : cand[0][1] == dmin ? 1 : cand[0][2] == dmin ? 2 : 3;
+            st_agent(&rec[kRecRest], rec_rest(tag, (uint32_t)(col0 + local_col(lo, 0, j)), total,
+                                              fused && dmin == d ? 1u : 0u));
+            st_agent(&rec[kRecDist], tag_word(tag, dmin));
+        }
+        if (entries) {
+            stress_delay(2u * tag + 1u);
+            uint32_t rank = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) rank += lanes_below(at[j]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (cand[0][j] == dmin)
+                    st_agent(&list[rank++], tag_word(tag, (uint32_t)(col0 + local_col(lo, 0, j))));
+        }
+        return;
+    }
+    if (NARROW) return;
     uint64_t key = kNoKey;
     if (lo.r == 0) {
 #pragma unroll
         for (int k = 0; k < G; ++k)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (cand[k][j] != 0xffffffffu)
-                    key = umin64(key, make_key(cand[k][j], (uint32_t)(col0 + local_col(lo, k, j))));
+                key = umin64(key, make_key(cand[k][j], (uint32_t)(col0 + local_col(lo, k, j))));
     }
-    owner_min_or<T>(key, zero, lo.L, sh.red);
+    uint32_t none = 0;
+    owner_min_or<T>(key, none, lo.L, sh.red);
     const uint32_t dmin = (uint32_t)(key >> 32);
     uint32_t mask = 0;
-    if (lo.r == 0 && key != kNoKey && dmin < kInf) {
+    if (lo.r == 0 && dmin < kInf) {
 #pragma unroll
         for (int k = 0; k < G; ++k)
 #pragma unroll
@@ -288,10 +382,8 @@ __device__ __forceinline__ void publish(const uint32_t (&cand)[G][4], const Layo
     }
     if (threadIdx.x == 0) {
         stress_delay(2u * tag);
-        const uint32_t slot = (tag - 1) & 1;
-        st_agent(rec_word(recs, nwg, slot, kRecVert, g), tag_word(tag, (uint32_t)key));
-        st_agent(rec_word(recs, nwg, slot, kRecCnt, g), tag_word(tag, (total << 1) | (zero ? 1u : 0u)));
-        st_agent(rec_word(recs, nwg, slot, kRecDist, g), tag_word(tag, (uint32_t)(key >> 32)));
+        st_agent(&rec[kRecRest], rec_rest(tag, (uint32_t)key, total, fused && dmin == d ? 1u : 0u));
+        st_agent(&rec[kRecDist], tag_word(tag, dmin));
     }
 }
 
@@ -312,129 +404,177 @@ __device__ __forceinline__ uint64_t wait_tag(const uint64_t* p, uint64_t w, uint
     }
 }
 
+// The wave's part of read_records: lane l polls members l + 64 k, k < KM, and the
+// wave leaves the exchange's result in sh.res and the bucket in sh.list (staged)
+// or its counts and offsets in sh.cnt / sh.pre.
+template <int T, int G, int KM>
+__device__ __forceinline__ void read_wave(uint64_t* recs, const uint64_t* __restrict__ rl, int S, int nwg,
+                                          uint32_t tag, long long timeout, SharedSolve<T>& sh, const Pub* stamps,
+                                          uint64_t stamp) {
+    const int l = wave_lane();  // not threadIdx.x: addresses hoisted out of the round loop would spill
+    uint32_t late = sh.stage_late;
+    // Every poll issues all of its loads before it checks any (member indexes
+    // clamped to the last member): a load per branch would be waited for before
+    // the next one, KM round trips per poll instead of one.  Polls back off (up to
+    // ~0.1 us apart) so that members waiting through a long round do not load the
+    // memory system the others are streaming from.  The clock is read from the
+    // first poll that misses a record on; a limit of 0 ends that poll.
+    long long t0 = 0;
+    unsigned naps = 0;
+    auto give_up = [&]() {
+        const long long now = wall_clock64();
+        if (t0 == 0) t0 = now;
+        if (now - t0 >= timeout) return true;
+        for (unsigned i = 0; i < naps; ++i) __builtin_amdgcn_s_sleep(1);
+        naps = naps ? (naps < 4 ? naps << 1 : naps) : 1;
+        return false;
+    };
+    if (stamps) {
+        for (;;) {
+            uint64_t sv[KM];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) sv[k] = ld_agent(&stamps[min(l + kWave * k, nwg - 1)].stamp);
+            bool there = true;
+#pragma unroll
+            for (int k = 0; k < KM; ++k) there = there && sv[k] == stamp;
+            if (!wave_mask(!there)) break;
+            if (give_up()) {
+                late = 1;
+                break;
+            }
+        }
+    }
+    const uint32_t rtag = tag & kRestTagMask;
+    uint64_t a[KM], r[KM];
+    for (;;) {
+#pragma unroll
+        for (int k = 0; k < KM; ++k) {
+            const uint64_t* w = rec_word(recs, nwg, (tag - 1) & 1, 0, min(l + kWave * k, nwg - 1));
+            a[k] = ld_agent(&w[kRecDist]);
+            r[k] = ld_agent(&w[kRecRest]);
+        }
+        bool there = true;
+#pragma unroll
+        for (int k = 0; k < KM; ++k) there = there && word_tag(a[k]) == tag && rest_tag(r[k]) == rtag;
+        if (!wave_mask(!there) || late) break;
+        if (give_up()) {
+            late = 1;
+            break;
+        }
+    }
+    late = wave_mask(late != 0) ? 1u : 0u;
+    uint32_t dist[KM], least = 0xffffffffu;
+#pragma unroll
+    for (int k = 0; k < KM; ++k) {
+        dist[k] = l + kWave * k < nwg ? (uint32_t)a[k] : 0xffffffffu;
+        least = min(least, dist[k]);
+    }
+    const uint32_t d = wave_min32(least);
+    // Members own ascending columns, so the bucket's lowest vertex is that of its
+    // lowest member.  The bucket is the concatenation of the bucket records' lists
+    // in position order, position 4 l + k holding member l + 64 k (entry_addr).
+    uint32_t low = 0, hazard = 0, local = 0, most = 0;
+    uint32_t c[KM];
+#pragma unroll
+    for (int k = KM - 1; k >= 0; --k) {
+        const uint64_t at = wave_mask(dist[k] == d);
+        if (at) low = lane_value(rest_vertex(r[k]), (int)__builtin_ctzll(at));
+        hazard |= rest_zero(r[k]);
+        c[k] = dist[k] == d ? rest_count(r[k]) : 0u;
+        local += c[k];
+        most = max(most, c[k]);
+    }
+    const uint32_t inc = wave_prefix32(local);
+    uint32_t run = inc - local;
+    const bool small = rl && !late && wave_mask(most > (G == 1 ? 2u : 1u)) == 0;
+    if (small) {
+        // at most 2 x 256 entries: they fit the staging list
+        if (G == 1 && wave_mask(most > 1u)) {
+            uint64_t w[KM];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) w[k] = c[k] > 1u ? ld_agent(&rl[(uint32_t)(l + kWave * k) * (uint32_t)S + 1]) : 0;
+            uint32_t pos = run;
+#pragma unroll
+            for (int k = 0; k < KM; ++k) {
+                if (c[k] > 1u) {
+                    uint32_t miss = 0;
+                    const uint64_t e =
+                        wait_tag(&rl[(uint32_t)(l + kWave * k) * (uint32_t)S + 1], w[k], tag, timeout, miss);
+                    // a time-out stages a valid row; the solve then ends with the time-out status
+                    sh.list[pos + 1] = (int32_t)(miss ? rest_vertex(r[k]) : (uint32_t)e);
+                    if (miss) sh.stage_late = 1u;
+                }
+                pos += c[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < KM; ++k) {
+            if (c[k]) sh.list[run] = (int32_t)rest_vertex(r[k]);
+            run += c[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            sh.pre[4 * l + k] = run;
+            sh.cnt[4 * l + k] = k < KM ? c[k < KM ? k : 0] : 0u;
+            if (k < KM) run += c[k < KM ? k : 0];
+        }
+    }
+    hazard = wave_mask(hazard != 0) ? 1u : 0u;
+    if (l == kWave - 1) {  // one 16-byte store here, one load in every thread
+        sh.res.d = d;
+        sh.res.vert = low;
+        sh.res.rows = inc;
+        sh.res.flags = hazard | (small ? 2u : 0u) | (late << 2);
+    }
+}
+
 // Exchange `tag` from the reader's side: waits for the gang's nwg tagged records
 // of its slot and reduces them.  `stamps` (the solve's first exchange only):
 // each member's tagged words are read only after its stamp, which it stored
 // once its cleared words were in place, has been seen (in an earlier poll, so
 // the tagged loads are issued after the stamp load returned).
-// K = the lowest key, Z = the OR of the hazard flags; for the round's bucket
-// (records whose key has dist d = K >> 32) each record's count and offset go to
+// d_out, u_out = the lowest key's dist and vertex, Z = the OR of the hazard
+// flags; for the round's bucket (records whose key has dist d) each record's count and offset go to
 // sh.cnt / sh.pre and their sum to M.  Wave 0 polls and reduces (lane l takes
-// members l, l + 64, l + 128, l + 192, so that each load instruction reads 64
-// consecutive words) and shares the results through LDS after one workgroup
-// barrier; gangs of more than 256 members take a block-wide path.  Returns
-// false (K = no key, M = 0) if a member's record did not arrive within
-// `timeout` ticks.
-template <int T>
-__device__ __forceinline__ bool read_records(uint64_t* recs, int nwg, uint32_t tag, long long timeout,
-                                             SharedSolve<T>& sh, uint64_t& K, uint32_t& Z, uint32_t& M,
+// members l, l + 64, l + 128, l + 192) and shares the results through LDS after
+// one workgroup barrier; gangs of more than 256 members take a block-wide path.
+// `rl` (null: no entries wanted): the gang's lists of this exchange.  When no
+// member has more than two bucket vertices (one, where a thread holds several
+// column groups and the list's order is not the vertices') the wave stages the
+// whole bucket in sh.list itself, the first entry of each member from its
+// record, and *staged tells: small rounds are bound by their chain of memory
+// and LDS round trips, and this takes the entry lookup, its load and one barrier
+// off it.  (Bare kernel, 64 workgroups, n=4096, p=0.002, 962 rounds: 4.84 ms before the
+// records' layout, the 32-bit reductions, the short batches and the staging, 2.92 ms
+// with them; n=16384, p=0.01, 17 rounds: 305 and 265 us.)  Returns false if a member's record, or an entry of the last round's bucket
+// (sh.stage_late), did not arrive within `timeout` ticks.
+template <int T, int G, bool NARROW>
+__device__ __forceinline__ bool read_records(uint64_t* recs, const uint64_t* __restrict__ rl, int S, int nwg,
+                                             uint32_t tag, long long timeout, SharedSolve<T>& sh, uint32_t& d_out,
+                                             uint32_t& u_out, uint32_t& Z, uint32_t& M, bool& staged,
                                              const Pub* stamps, uint64_t stamp) {
-    const uint32_t slot = (tag - 1) & 1;
-    const uint64_t* rd = rec_word(recs, nwg, slot, kRecDist, 0);
-    const uint64_t* rv = rec_word(recs, nwg, slot, kRecVert, 0);
-    const uint64_t* rc = rec_word(recs, nwg, slot, kRecCnt, 0);
-    if (nwg <= 4 * kWave) {
+    staged = false;
+    if (NARROW || nwg <= 4 * kWave) {
         if (threadIdx.x < kWave) {
-            const int l = (int)threadIdx.x;
-            uint64_t key[4];
-            uint32_t cnt[4];
-            uint32_t want = 0, f = 0, late = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                key[k] = kNoKey;
-                cnt[k] = 0;
-                if (l + kWave * k < nwg) want |= 1u << k;
-            }
-            // Every poll issues all of its loads before it checks any (member indexes
-            // clamped to the last member): a load per branch would be waited for
-            // before the next one, four round trips per poll instead of one.  Polls
-            // back off (up to ~0.1 us apart) so that members waiting through a long
-            // round do not load the memory system the others are streaming from.
-            const long long t0 = wall_clock64();
-            unsigned naps = 0;
-            if (stamps) {
-                uint32_t need = want;
-                for (;;) {
-                    uint64_t sv[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) sv[k] = ld_agent(&stamps[min(l + kWave * k, nwg - 1)].stamp);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (sv[k] == stamp) need &= ~(1u << k);
-                    if (!need) break;
-                    if (wall_clock64() - t0 > timeout) {
-                        late = 1;
-                        want = 0;
-                        break;
-                    }
-                    for (unsigned i = 0; i < naps; ++i) __builtin_amdgcn_s_sleep(1);
-                    naps = naps ? (naps < 4 ? naps << 1 : naps) : 1;
-                }
-            }
-            while (want) {
-                uint64_t a[4], b[4], c[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int m = min(l + kWave * k, nwg - 1);
-                    a[k] = ld_agent(&rd[m]);
-                    b[k] = ld_agent(&rv[m]);
-                    c[k] = ld_agent(&rc[m]);
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if ((want >> k & 1u) && word_tag(a[k]) == tag && word_tag(b[k]) == tag && word_tag(c[k]) == tag) {
-                        key[k] = make_key((uint32_t)a[k], (uint32_t)b[k]);
-                        cnt[k] = (uint32_t)c[k] >> 1;
-                        f |= (uint32_t)c[k] & 1u;
-                        want &= ~(1u << k);
-                    }
-                if (!want) break;
-                if (wall_clock64() - t0 > timeout) {
-                    late = 1;
-                    break;
-                }
-                for (unsigned i = 0; i < naps; ++i) __builtin_amdgcn_s_sleep(1);
-                naps = naps ? (naps < 4 ? naps << 1 : naps) : 1;
-            }
-            uint64_t kmin = kNoKey;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) kmin = umin64(kmin, key[k]);
-            kmin = wave_min64(kmin);
-            f = wave_or32(f);
-            late = wave_or32(late);
-            const uint32_t d = (uint32_t)(kmin >> 32);
-            // The bucket is the concatenation of the bucket records' lists in
-            // position order, position 4 l + k holding member l + 64 k (see
-            // entry_addr): one scan over the lanes' sums.
-            uint32_t c[4], local = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                c[k] = (key[k] == kNoKey || (uint32_t)(key[k] >> 32) != d) ? 0u : cnt[k];
-                local += c[k];
-            }
-            const uint32_t inc = wave_scan32(local);
-            uint32_t run = inc - local;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                sh.pre[4 * l + k] = run;
-                sh.cnt[4 * l + k] = c[k];
-                run += c[k];
-            }
-            if (l == 0) {
-                sh.rk = late ? kNoKey : kmin;
-                sh.rz = f;
-                sh.rm = late ? 0u : lane_value(inc, kWave - 1);
-                sh.late = late;
-            }
+            // members 64 to 255 of a gang of at most 64 do not exist
+            if (nwg <= kWave) read_wave<T, G, 1>(recs, rl, S, nwg, tag, timeout, sh, stamps, stamp);
+            else read_wave<T, G, 4>(recs, rl, S, nwg, tag, timeout, sh, stamps, stamp);
         }
         __syncthreads();
         // the same in every thread: scalar registers
-        K = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(sh.rk >> 32)) << 32) |
-            (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)sh.rk);
-        Z = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.rz);
-        M = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.rm);
-        return __builtin_amdgcn_readfirstlane((int)sh.late) == 0;
+        const auto res = sh.res;
+        d_out = (uint32_t)__builtin_amdgcn_readfirstlane((int)res.d);
+        u_out = (uint32_t)__builtin_amdgcn_readfirstlane((int)res.vert);
+        M = (uint32_t)__builtin_amdgcn_readfirstlane((int)res.rows);
+        const uint32_t z = (uint32_t)__builtin_amdgcn_readfirstlane((int)res.flags);
+        Z = z & 1u;
+        staged = (z & 2u) != 0;
+        return (z & 4u) == 0;
     }
+    const uint32_t slot = (tag - 1) & 1;
+    const uint32_t rtag = tag & kRestTagMask;
+    if (NARROW) return false;
     uint64_t key = kNoKey;
     uint32_t c = 0, f = 0, late = 0;
     if ((int)threadIdx.x < nwg) {
@@ -447,31 +587,37 @@ __device__ __forceinline__ bool read_records(uint64_t* recs, int nwg, uint32_t t
                     break;
                 }
         }
-        const uint64_t a = wait_tag(&rd[m], ld_agent(&rd[m]), tag, timeout, late);
-        const uint64_t b = wait_tag(&rv[m], ld_agent(&rv[m]), tag, timeout, late);
-        const uint64_t w = wait_tag(&rc[m], ld_agent(&rc[m]), tag, timeout, late);
-        key = make_key((uint32_t)a, (uint32_t)b);
-        c = (uint32_t)w >> 1;
-        f = ((uint32_t)w & 1u) | (late << 1);
+        const uint64_t* w = rec_word(recs, nwg, slot, 0, m);
+        const uint64_t a = wait_tag(&w[kRecDist], ld_agent(&w[kRecDist]), tag, timeout, late);
+        uint64_t r = ld_agent(&w[kRecRest]);
+        const long long t1 = wall_clock64();
+        while (rest_tag(r) != rtag) {
+            if (wall_clock64() - t1 > timeout) {
+                late = 1;
+                break;
+            }
+            r = ld_agent(&w[kRecRest]);
+        }
+        key = make_key((uint32_t)a, rest_vertex(r));
+        c = rest_count(r);
+        f = rest_zero(r) | (late << 1);
     }
-    K = key;
+    if (threadIdx.x == 0 && sh.stage_late) f |= 2u;
+    uint64_t K = key;
     Z = f;
     block_min_or<T>(K, Z, sh.red);
-    if (key == kNoKey || (uint32_t)(key >> 32) != (uint32_t)(K >> 32)) c = 0;
+    d_out = (uint32_t)(K >> 32);
+    u_out = (uint32_t)K;
+    if (key == kNoKey || (uint32_t)(key >> 32) != d_out) c = 0;
     const uint32_t pre = block_excl_scan<T>(c, M, sh.red);
     if ((int)threadIdx.x < nwg) {
         sh.pre[threadIdx.x] = pre;
         sh.cnt[threadIdx.x] = c;
     }
-    if (threadIdx.x == 0) sh.late = (Z >> 1) & 1u;
     __syncthreads();
-    if (Z & 2u) {
-        K = kNoKey;
-        M = 0;
-        return false;
-    }
+    const bool ok = (Z & 2u) == 0;
     Z &= 1u;
-    return true;
+    return ok;
 }
 
 // Address of entry e of the round's bucket, the concatenation of the lists of
@@ -519,20 +665,22 @@ __device__ __forceinline__ const uint64_t* entry_addr(const SharedSolve<T>& sh, 
 // follows the round that used it, when both members' claims on it have
 // returned, and before its next publish (the partner claims on it again only
 // after that publish).
-template <int T, int G, int U, typename E, bool NT = false, bool BAL = false>
+template <int T, int G, int U, typename E, bool NT = false, bool BAL = false, bool NARROW = false>
 __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, int32_t n, int32_t src,
                            int32_t* __restrict__ dist, int32_t* __restrict__ pred, bool vec, bool literal,
                            int S, int g, int nwg, long long timeout, GangWords gw, SharedSolve<T>& sh,
                            SolveStats& st, Ctl* trace, uint32_t epoch, uint32_t b0 = 0) {
     static_assert(T == kCap, "one staged bucket entry per thread");
     static_assert(!BAL || sizeof(E) == 4, "pair balancing keeps 64-bit keys");
+    static_assert(!NARROW || G == 1, "narrow slices have one column group per lane");
     const int64_t col0 = (int64_t)g * S;
     const int width = (int)max((int64_t)0, min((int64_t)S, (int64_t)n - col0));
     const Layout lo = make_layout<T>(S);
     Cols<G, E> cs;
     init_cols(cs, lo, col0, width, src);
     clear_merge<T>(sh.mrg, 4 * T);
-    auto list_of = [&](uint32_t x, int m) { return gw.lists + ((size_t)((x - 1) & 1) * nwg + m) * S; };
+    // nwg * S words fit 32 bits: at most 1024 members of 16384 columns
+    auto list_of = [&](uint32_t x, int m) { return gw.lists + (((x - 1) & 1u) * (uint32_t)nwg + (uint32_t)m) * (uint32_t)S; };
 
     uint32_t b = b0;  // exchanges passed
     bool ok = true;
@@ -561,178 +709,170 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
     // member's view: no exchange precedes it.
     uint32_t d = 0, u0 = (uint32_t)src, M = 1;
     bool first = true;
+    bool staged = false;  // the bucket is in sh.list already (read_records)
+    bool redo = false;    // the round repeats the last one as one literal step (zero-weight hazard)
+    uint32_t rounds = 0, settled = 0, fallbacks = 0, neg = 0;
+    const bool tracer = trace && g == 0 && threadIdx.x == 0;
     uint32_t cand[G][4];
     for (;;) {
-        ++st.rounds;
-        const long long t_round = wall_clock64();
-        uint32_t bucket;
-        if (literal) {
-            M = 1;
-            bucket = owner_bit(lo, (int64_t)u0 - col0, width);
-            if (threadIdx.x == 0) sh.list[0] = (int32_t)u0;
-            __syncthreads();
-            stream_rows<G, U, E, NT>(cs, lo, W, ld, col0, width, vec, sh.list, 1);
-        } else {
-            bucket = bucket_mask(cs, d);
-            const uint64_t* rl = list_of(b, 0);
-            // entry e of the bucket into sh.list[threadIdx.x]; w: its word as loaded
-            auto stage = [&](uint32_t e, uint64_t w) {
-                uint32_t late = 0;
-                if (word_tag(w) != b) w = wait_tag(entry_addr<T>(sh, rl, nwg, S, e), w, b, timeout, late);
-                // a time-out stages a valid row; the solve then ends with the time-out status
-                sh.list[threadIdx.x] = late ? (int32_t)u0 : (int32_t)(uint32_t)w;
-                if (late) sh.stage_late = 1u;
-            };
-            const uint32_t C = (M + kCap - 1) / kCap;
-            if (paired && C >= kPairChunks) {
-                const uint32_t slot = b & 1;
-                const uint32_t tag = b + 1;  // the exchange this round publishes
-                key_t<E>* keep = reinterpret_cast<key_t<E>*>(sh.mrg + 2 * T);
-                uint32_t own = 0;
-                for (int side = 0; side < 2; ++side) {
-                    const int m = side ? pg : g;
-                    const int64_t c0 = (int64_t)m * S;
-                    const int wd = (int)max((int64_t)0, min((int64_t)S, (int64_t)n - c0));
-                    uint32_t* ctr = &gw.ctr[4 * m + slot];
-                    // claims count units of kPairUnit rows: the owner takes a staging
-                    // chunk (kCap rows) at a time from the front, the helper one unit at
-                    // a time from the back
-                    constexpr uint32_t kChunkUnits = (uint32_t)kCap / kPairUnit;
-                    const uint32_t units = (M + kPairUnit - 1) / kPairUnit;
-                    uint32_t left = units;  // units unclaimed when the last decoded claim was made
-                    // rows [begin, begin + count) of a claim of `n` units (the counter
-                    // before it in `old`); count 0 if it came too late.  A front claim stops
-                    // at the back claims made before it; later back claims see its whole
-                    // increment and stay clear.
-                    auto rows_of = [&](uint32_t old, uint32_t nu, uint32_t& begin) -> uint32_t {
-                        const uint32_t f = old & 0xffffu, h = old >> 16;
-                        begin = 0;
-                        left = f + h >= units ? 0u : units - f - h;
-                        if (!left) return 0u;
-                        const uint32_t u0 = side ? units - 1 - h : f;
-                        const uint32_t u1 = side ? u0 + 1 : min(f + nu, units - h);
-                        begin = u0 * kPairUnit;
-                        return min(u1 * kPairUnit, M) - begin;
-                    };
-                    // the owner claims whole staging chunks, single units once few are
-                    // left (so that it reserves little for the helper to wait behind);
-                    // the helper always claims single units
-                    auto units_next = [&]() { return side || left <= 3 * kChunkUnits ? 1u : kChunkUnits; };
-                    auto inc_of = [&](uint32_t nu) { return side ? 0x10000u : nu; };
-                    if (side == 1) {
-                        // keep this member's candidates while it streams rows for the partner
-                        merge_partitions<T, G>(cs, lo, sh.mrg);
-                        if (lo.r == 0)
+        if (!redo) ++rounds;
+        const long long t_round = tracer ? wall_clock64() : 0;
+        // a literal step's one row, or a bucket that read_records staged: in sh.list already
+        const bool step = literal || redo;
+        if (step) M = 1;
+        const uint32_t bucket = settle(cs, d, step, step ? owner_bit(lo, (int64_t)u0 - col0, width) : 0u);
+        if (step && threadIdx.x == 0) sh.list[0] = (int32_t)u0;
+        const bool ready = step || staged;
+        const uint64_t* rl = list_of(b, 0);
+        // entry e of the bucket into sh.list[threadIdx.x]; w: its word as loaded
+        auto stage = [&](uint32_t e, uint64_t w) {
+            uint32_t late = 0;
+            if (word_tag(w) != b) w = wait_tag(entry_addr<T>(sh, rl, nwg, S, e), w, b, timeout, late);
+            // a time-out stages a valid row; the solve then ends with the time-out status
+            sh.list[threadIdx.x] = late ? (int32_t)u0 : (int32_t)(uint32_t)w;
+            if (late) sh.stage_late = 1u;
+        };
+        const uint32_t C = (M + kCap - 1) / kCap;
+        if (paired && C >= kPairChunks) {
+            const uint32_t slot = b & 1;
+            const uint32_t tag = b + 1;  // the exchange this round publishes
+            key_t<E>* keep = reinterpret_cast<key_t<E>*>(sh.mrg + 2 * T);
+            uint32_t own = 0;
+            for (int side = 0; side < 2; ++side) {
+                const int m = side ? pg : g;
+                const int64_t c0 = (int64_t)m * S;
+                const int wd = (int)max((int64_t)0, min((int64_t)S, (int64_t)n - c0));
+                uint32_t* ctr = &gw.ctr[4 * m + slot];
+                // claims count units of kPairUnit rows: the owner takes a staging
+                // chunk (kCap rows) at a time from the front, the helper one unit at
+                // a time from the back
+                constexpr uint32_t kChunkUnits = (uint32_t)kCap / kPairUnit;
+                const uint32_t units = (M + kPairUnit - 1) / kPairUnit;
+                uint32_t left = units;  // units unclaimed when the last decoded claim was made
+                // rows [begin, begin + count) of a claim of `n` units (the counter
+                // before it in `old`); count 0 if it came too late.  A front claim stops
+                // at the back claims made before it; later back claims see its whole
+                // increment and stay clear.
+                auto rows_of = [&](uint32_t old, uint32_t nu, uint32_t& begin) -> uint32_t {
+                    const uint32_t f = old & 0xffffu, h = old >> 16;
+                    begin = 0;
+                    left = f + h >= units ? 0u : units - f - h;
+                    if (!left) return 0u;
+                    const uint32_t u0 = side ? units - 1 - h : f;
+                    const uint32_t u1 = side ? u0 + 1 : min(f + nu, units - h);
+                    begin = u0 * kPairUnit;
+                    return min(u1 * kPairUnit, M) - begin;
+                };
+                // the owner claims whole staging chunks, single units once few are
+                // left (so that it reserves little for the helper to wait behind);
+                // the helper always claims single units
+                auto units_next = [&]() { return side || left <= 3 * kChunkUnits ? 1u : kChunkUnits; };
+                auto inc_of = [&](uint32_t nu) { return side ? 0x10000u : nu; };
+                if (side == 1) {
+                    // keep this member's candidates while it streams rows for the partner
+                    merge_partitions<T, G>(cs, lo, sh.mrg);
+                    if (lo.r == 0)
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) keep[j * lo.L + lo.c] = cs.best[0][j];
-                        reset_best(cs);
-                    }
-                    const uint32_t nu0 = units_next();
-                    if (threadIdx.x == 0) {
-                        if (side == 0) stress_delay(4u * tag + 3u);  // late starters: partners steal
-                        sh.claim[0] = __hip_atomic_fetch_add(ctr, inc_of(nu0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        sh.claim[1] = __hip_atomic_fetch_add(ctr, inc_of(nu0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                    __syncthreads();
-                    uint32_t kb = 0, nb = 0;
-                    uint32_t kcnt = rows_of((uint32_t)__builtin_amdgcn_readfirstlane((int)sh.claim[0]), nu0, kb);
-                    uint32_t ncnt = rows_of((uint32_t)__builtin_amdgcn_readfirstlane((int)sh.claim[1]), nu0, nb);
-                    uint32_t chunks = 0;  // rows streamed on this side
-                    uint64_t w = 0;
-                    if (threadIdx.x < kcnt) w = ld_agent(entry_addr<T>(sh, rl, nwg, S, kb + threadIdx.x));
-                    while (kcnt) {
-                        if (threadIdx.x < kcnt) stage(kb + threadIdx.x, w);
-                        __syncthreads();
-                        uint32_t a = 0xffffffffu;  // no further claim: nothing is left after the next one
-                        const uint32_t nua = units_next();
-                        if (ncnt) {
-                            if (threadIdx.x < ncnt) w = ld_agent(entry_addr<T>(sh, rl, nwg, S, nb + threadIdx.x));
-                            if (threadIdx.x == 0)
-                                a = __hip_atomic_fetch_add(ctr, inc_of(nua), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        }
-                        stream_rows<G, U, E, NT>(cs, lo, W, ld, c0, wd, vec, sh.list, (int)kcnt);
-                        if (threadIdx.x == 0) sh.claim[0] = a;
-                        __syncthreads();
-                        chunks += kcnt;
-                        kb = nb;
-                        kcnt = ncnt;
-                        ncnt = rows_of((uint32_t)__builtin_amdgcn_readfirstlane((int)sh.claim[0]), nua, nb);
-                    }
-                    if (side == 0) {
-                        own = chunks;
-                        continue;
-                    }
-                    if (chunks) {
-                        // the partner's share of its own columns: partial minima, then the
-                        // tagged done word once they are in memory
-                        merge_partitions<T, G>(cs, lo, sh.mrg);
-                        if (lo.r == 0)
-#pragma unroll
-                            for (int j = 0; j < 4; ++j)
-                                st_agent(&gw.part[(size_t)pg * S + 4 * lo.c + j], (uint64_t)cs.best[0][j]);
-                        __builtin_amdgcn_s_waitcnt(0);
-                        __syncthreads();
-                        if (threadIdx.x == 0) st_agent(&gw.done[2 * pg], tag_word(tag, chunks));
-                    }
-                    // back to this member's own candidates
-                    if (lo.r == 0) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) cs.best[0][j] = keep[j * lo.L + lo.c];
-                    } else {
-                        reset_best(cs);
-                    }
+                        for (int j = 0; j < 4; ++j) keep[j * lo.L + lo.c] = cs.best[0][j];
+                    reset_best(cs);
                 }
-                if (own < M && lo.r == 0) {
-                    // the partner streamed the rest of this member's chunks: its partial minima
-                    uint32_t late = 0;
-                    (void)wait_tag(&gw.done[2 * g], ld_agent(&gw.done[2 * g]), tag, timeout, late);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        cs.best[0][j] = key_min(cs.best[0][j], (key_t<E>)ld_agent(&gw.part[(size_t)g * S + 4 * lo.c + j]));
-                    if (late) sh.stage_late = 1u;
+                const uint32_t nu0 = units_next();
+                if (threadIdx.x == 0) {
+                    if (side == 0) stress_delay(4u * tag + 3u);  // late starters: partners steal
+                    sh.claim[0] = __hip_atomic_fetch_add(ctr, inc_of(nu0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    sh.claim[1] = __hip_atomic_fetch_add(ctr, inc_of(nu0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-                used |= 1u << slot;
-            } else {
-                // stage the bucket chunk by chunk; the next chunk's entries are loaded
-                // while the current chunk's rows stream (the first round's one entry,
-                // the source, is not loaded)
-                uint64_t nxt = first ? tag_word(b, u0)
-                             : threadIdx.x < M ? ld_agent(entry_addr<T>(sh, rl, nwg, S, threadIdx.x)) : 0;
-                for (uint32_t e0 = 0; e0 < M; e0 += kCap) {
-                    const uint32_t e = e0 + threadIdx.x;
-                    if (e < M) stage(e, nxt);
+                __syncthreads();
+                uint32_t kb = 0, nb = 0;
+                uint32_t kcnt = rows_of((uint32_t)__builtin_amdgcn_readfirstlane((int)sh.claim[0]), nu0, kb);
+                uint32_t ncnt = rows_of((uint32_t)__builtin_amdgcn_readfirstlane((int)sh.claim[1]), nu0, nb);
+                uint32_t chunks = 0;  // rows streamed on this side
+                uint64_t w = 0;
+                if (threadIdx.x < kcnt) w = ld_agent(entry_addr<T>(sh, rl, nwg, S, kb + threadIdx.x));
+                while (kcnt) {
+                    if (threadIdx.x < kcnt) stage(kb + threadIdx.x, w);
                     __syncthreads();
-                    if (e + kCap < M) nxt = ld_agent(entry_addr<T>(sh, rl, nwg, S, e + kCap));
-                    stream_rows<G, U, E, NT>(cs, lo, W, ld, col0, width, vec, sh.list,
-                                             (int)min((uint32_t)kCap, M - e0));
+                    uint32_t a = 0xffffffffu;  // no further claim: nothing is left after the next one
+                    const uint32_t nua = units_next();
+                    if (ncnt) {
+                        if (threadIdx.x < ncnt) w = ld_agent(entry_addr<T>(sh, rl, nwg, S, nb + threadIdx.x));
+                        if (threadIdx.x == 0)
+                            a = __hip_atomic_fetch_add(ctr, inc_of(nua), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    stream_rows<G, U, E, NT>(cs, lo, W, ld, c0, wd, vec, sh.list, (int)kcnt);
+                    if (threadIdx.x == 0) sh.claim[0] = a;
                     __syncthreads();
+                    chunks += kcnt;
+                    kb = nb;
+                    kcnt = ncnt;
+                    ncnt = rows_of((uint32_t)__builtin_amdgcn_readfirstlane((int)sh.claim[0]), nua, nb);
+                }
+                if (side == 0) {
+                    own = chunks;
+                    continue;
+                }
+                if (chunks) {
+                    // the partner's share of its own columns: partial minima, then the
+                    // tagged done word once they are in memory
+                    merge_partitions<T, G>(cs, lo, sh.mrg);
+                    if (lo.r == 0)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            st_agent(&gw.part[(size_t)pg * S + 4 * lo.c + j], (uint64_t)cs.best[0][j]);
+                    __builtin_amdgcn_s_waitcnt(0);
+                    __syncthreads();
+                    if (threadIdx.x == 0) st_agent(&gw.done[2 * pg], tag_word(tag, chunks));
+                }
+                // back to this member's own candidates
+                if (lo.r == 0) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) cs.best[0][j] = keep[j * lo.L + lo.c];
+                } else {
+                    reset_best(cs);
                 }
             }
+            if (own < M && lo.r == 0) {
+                // the partner streamed the rest of this member's chunks: its partial minima
+                uint32_t late = 0;
+                (void)wait_tag(&gw.done[2 * g], ld_agent(&gw.done[2 * g]), tag, timeout, late);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    cs.best[0][j] = key_min(cs.best[0][j], (key_t<E>)ld_agent(&gw.part[(size_t)g * S + 4 * lo.c + j]));
+                if (late) sh.stage_late = 1u;
+            }
+            used |= 1u << slot;
+        } else {
+            // stage the bucket chunk by chunk; the next chunk's entries are loaded
+            // while the current chunk's rows stream (the first round's one entry,
+            // the source, is not loaded)
+            uint64_t nxt = first ? tag_word(b, u0)
+                         : !ready && threadIdx.x < M ? ld_agent(entry_addr<T>(sh, rl, nwg, S, threadIdx.x)) : 0;
+            for (uint32_t e0 = 0; e0 < M; e0 += kCap) {
+                const uint32_t e = e0 + threadIdx.x;
+                if (!ready && e < M) stage(e, nxt);
+                if (!staged || step) __syncthreads();  // a staged bucket: read_records ended with a barrier
+                if (e + kCap < M) nxt = ld_agent(entry_addr<T>(sh, rl, nwg, S, e + kCap));
+                stream_rows<G, U, E, NT>(cs, lo, W, ld, col0, width, vec, sh.list,
+                                         (int)min((uint32_t)kCap, M - e0));
+                __syncthreads();
+            }
         }
-        merge_partitions<T, G>(cs, lo, sh.mrg);
-        if (sh.stage_late) {
-            ok = false;
-            break;
-        }
-        if (trace && g == 0 && threadIdx.x == 0 && st.rounds <= (unsigned long long)kTraceCap) {
-            trace->trace_t[st.rounds - 1] = t_round;
-            trace->trace_m[st.rounds - 1] = M;
+        // a single row went to partition 0, whose threads own the columns
+        if (M > 1) merge_partitions<T, G>(cs, lo, sh.mrg);
+        if (tracer && !redo && rounds <= (uint32_t)kTraceCap) {
+            trace->trace_t[rounds - 1] = t_round;
+            trace->trace_m[rounds - 1] = M;
         }
 
-        // would-be state if this round is applied; publish it with the hazard flag
-        uint32_t neg = 0;
-#pragma unroll
-        for (int k = 0; k < G; ++k)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) cand[k][j] = would_be(cs, k, j, d, bucket, neg);
-        st.status |= neg;
-        const uint32_t zero = (!literal && lo.r == 0) ? zero_hazard(cs, d) : 0u;
+        // would-be state if this round is applied (threads that own no column have
+        // x = 0xffffffff, so theirs is no candidate)
+        candidates(cs, d, cand, neg);
         ++b;
         if (BAL) asm volatile("" ::"v"(reset_old));  // a counter reset has completed before this publish
-        publish<T, G>(cand, lo, col0, zero, !literal, b, gw.recs, nwg, g, list_of(b, g), sh);
-        uint64_t K;
-        uint32_t Z, M_rec;
-        ok = read_records<T>(gw.recs, nwg, b, timeout, sh, K, Z, M_rec, first ? stamps1 : nullptr, stamp1);
+        publish<T, G, NARROW>(cand, lo, col0, d, !step, !literal, b, gw.recs, nwg, g, list_of(b, g), sh);
+        uint32_t Z, M_rec, d_next, u_next;
+        ok = read_records<T, G, NARROW>(gw.recs, literal ? nullptr : list_of(b, 0), S, nwg, b, timeout, sh, d_next,
+                                        u_next, Z, M_rec, staged, first ? stamps1 : nullptr, stamp1);
         first = false;
         if (!ok) break;
         if (BAL && (used >> ((b - 1) & 1) & 1u)) {
@@ -745,43 +885,33 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
         if (Z) {
             // the fused round read a zero-weight edge out of its bucket: discard it
             // and settle only the bucket's lowest-index vertex (one literal step)
-            ++st.fallbacks;
+            ++fallbacks;
             st.status |= kStatusZeroFallback;
+            reopen(cs, bucket);
             reset_best(cs);
-            if (threadIdx.x == 0) sh.list[0] = (int32_t)u0;
-            __syncthreads();
-            stream_rows<G, U, E, NT>(cs, lo, W, ld, col0, width, vec, sh.list, 1);
-            merge_partitions<T, G>(cs, lo, sh.mrg);
-            if (lo.r == 0) st.status |= commit_fused(cs, d, owner_bit(lo, (int64_t)u0 - col0, width));
-            else reset_best(cs);
-            st.settled += 1;
-#pragma unroll
-            for (int k = 0; k < G; ++k)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    cand[k][j] = (cs.vis >> (4 * k + j) & 1u) ? 0xffffffffu : cs.dist[k][j];
-            ++b;
-            if (BAL) asm volatile("" ::"v"(reset_old));
-            publish<T, G>(cand, lo, col0, 0u, !literal, b, gw.recs, nwg, g, list_of(b, g), sh);
-            ok = read_records<T>(gw.recs, nwg, b, timeout, sh, K, Z, M_rec, nullptr, 0);
-            if (!ok) break;
-        } else {
-            if (lo.r == 0) st.status |= commit_fused(cs, d, bucket);
-            else reset_best(cs);
-            st.settled += M;
+            redo = true;
+            continue;
         }
-        d = (uint32_t)(K >> 32);
-        if (K == kNoKey || d >= kInf) break;
-        u0 = (uint32_t)K;
+        redo = false;
+        if (lo.r == 0) commit(cs, cand);
+        else reset_best(cs);
+        settled += M;
+        d = d_next;
+        if (d >= kInf) break;
+        u0 = u_next;
         M = M_rec;
     }
+    st.rounds += rounds;
+    st.settled += settled;
+    st.fallbacks += fallbacks;
+    if (neg & kSettled) st.status |= kStatusNegWeight;
     if (!ok) st.status |= kStatusTimeout;
     write_out(cs, lo, col0, width, dist, pred);
     st.barriers += b;
-    if (trace && g == 0 && threadIdx.x == 0) {
-        const unsigned long long nr = st.rounds < (unsigned long long)kTraceCap ? st.rounds : kTraceCap;
+    if (tracer) {
+        const uint32_t nr = min(rounds, (uint32_t)kTraceCap);
         trace->trace_t[nr] = wall_clock64();
-        trace->trace_n = (uint32_t)nr;
+        trace->trace_n = nr;
     }
     uint32_t s = st.status;
     uint64_t dummy = kNoKey;
