@@ -146,8 +146,6 @@ int single_crossover() {
     return 1024;
 }
 
-bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
-
 int check_solve_args(const int32_t* W, int64_t ld, int32_t n, int32_t src, const int32_t* dist,
                      const int32_t* pred) {
     if (!W || !dist || !pred) return fail(SSSP_EINVAL, "null buffer (W=%p dist=%p pred=%p)", (const void*)W,
@@ -248,7 +246,6 @@ int solve(const int32_t* W, int64_t ld, int32_t n, int32_t src, int32_t* dist, i
     rc = get_scratch(stream, &sc, &di);
     if (rc) return rc;
     SolveArgs a{W, ld, n, src, dist, pred, flags & SSSP_FLAG_LITERAL, sc->ctl};
-    if (aligned16(W) && ld % 4 == 0) a.flags |= kFlagVec;
     const bool single = !lc && ((flags & SSSP_FLAG_SINGLE) ||
                                 (!(flags & SSSP_FLAG_GRID) && n <= single_crossover()));
     hipError_t e;

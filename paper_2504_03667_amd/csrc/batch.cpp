@@ -53,10 +53,6 @@ struct Build {
     int32_t group_items = 0;
 };
 
-bool aligned(const void* p, int64_t ld, int elem) {
-    return ((uintptr_t)p % (4 * (uintptr_t)elem)) == 0 && ld % 4 == 0;
-}
-
 // Instances of one matrix shared by at least this many sources fill the GPU by
 // themselves: each is solved by one workgroup (no gang exchange), and they are
 // queued after the other instances, whose gangs are bound by their chains of
@@ -67,7 +63,7 @@ constexpr int32_t kSharedSources = 32;
 // times the rows of a Dijkstra solve, so it is spread over many workgroups.
 constexpr int32_t kLcColumns = 256;
 
-// Lockstep groups (multi.h): matrices up to this n; slices of 512..4096 columns.
+// Lockstep groups (multi.h): matrices of 4 vertices up to this n; slices of 512..4096 columns.
 constexpr int32_t kGroupMaxN = 16384;
 
 // Shape of a group of up to `want` sources on an n-vertex matrix with slices of
@@ -137,7 +133,6 @@ int build(const sssp_instance* inst, const Source* src, int32_t count, int32_t s
                 b.elem = src[ids[a]].elem;
                 b.n = I0.n;
                 b.src = -1;
-                b.vec = aligned(b.W, b.ld, b.elem) ? 1 : 0;
                 b.method = kMethodGroup;
                 b.K = k;
                 b.S = S;
@@ -170,7 +165,6 @@ int build(const sssp_instance* inst, const Source* src, int32_t count, int32_t s
         b.pred = I.pred;
         b.n = I.n;
         b.src = I.src;
-        b.vec = aligned(b.W, b.ld, b.elem) ? 1 : 0;
         const bool use_lc = lc && lc[order[k]] && !shared[order[k]];
         b.method = use_lc ? kMethodLabelCorrecting : kMethodDijkstra;
         if (!use_lc && (I.n <= single_max_n || shared[order[k]])) {
@@ -565,7 +559,9 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
         p->group_ok.assign(count, 0);
         for (const auto& kv : by_matrix) {
             const sssp_instance& I = inst[kv.second.front()];
-            if ((int32_t)kv.second.size() < kSharedSources || I.n > kGroupMaxN || I.n > max_batch_single_n()) continue;
+            if ((int32_t)kv.second.size() < kSharedSources || I.n > kGroupMaxN || I.n > max_batch_single_n() ||
+                I.n < 4)
+                continue;
             int32_t wmin = 0, wmax = 0, woff = 0;
             auto cit = seen.find(kv.first);
             if (cit != seen.end()) {

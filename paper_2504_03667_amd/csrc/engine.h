@@ -426,11 +426,6 @@ __device__ __forceinline__ uint32_t key_row(key_t<E> k) {
     if constexpr (sizeof(E) == 4) return (uint32_t)k;
     else return k & 0xffffu;
 }
-// Entry value standing for "no column here" when a partial group is read.
-template <typename E>
-__device__ __forceinline__ uint32_t absent_code() {
-    return sizeof(E) == 4 ? kInf : 0xffffu;
-}
 template <typename X>
 __device__ __forceinline__ X key_min(X a, X b) {
     return b < a ? b : a;
@@ -465,13 +460,20 @@ using global_ptr = const T*;
 #endif
 
 // One column group as loaded (16, 8 or 4 bytes) and its widening to uint32.
+// Rows of the caller's int32 matrix start at any multiple of 4 bytes (an odd n
+// or row stride): the hardware takes a 16-byte load there, so the type carries
+// that alignment and every stride has the same loads.  (With one load per entry
+// for rows not 16-byte aligned, n=5001 took 166 us, now 125, and a batch of 24
+// graphs of any n up to 6000, one workgroup each, 7.2 ms, now 2.6.)  Rows of compact
+// copies are multiples of 16 entries.
 template <typename E>
 struct Raw;
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 template <>
 struct Raw<int32_t> {
-    typedef v4i type;
+    typedef v4i_any type;
 };
 template <>
 struct Raw<uint16_t> {
@@ -485,7 +487,7 @@ struct Raw<uint8_t> {
 template <typename E>
 __device__ __forceinline__ void unpack(const typename Raw<E>::type& x, uint32_t (&w)[4]);
 template <>
-__device__ __forceinline__ void unpack<int32_t>(const v4i& x, uint32_t (&w)[4]) {
+__device__ __forceinline__ void unpack<int32_t>(const v4i_any& x, uint32_t (&w)[4]) {
     w[0] = (uint32_t)x.x;
     w[1] = (uint32_t)x.y;
     w[2] = (uint32_t)x.z;
@@ -507,15 +509,52 @@ __device__ __forceinline__ void unpack<uint8_t>(const uint32_t& x, uint32_t (&w)
     w[3] = x >> 24;
 }
 
+// A group of 4 columns of which only the first 4 - s exist (the last one of an
+// int32 matrix whose n is not a multiple of 4) is read as the 4 columns that end
+// with the row, s columns to the left of its own: its keys are moved up by s
+// before a pass over the rows and back down after it, which drops the
+// neighbour's.  Compact copies need no shift: their rows are padded with the
+// no-edge code.
+template <typename E>
+__device__ __forceinline__ int group_shift(int v0, int width) {
+    return sizeof(E) == 4 ? max(0, v0 + 4 - width) : 0;
+}
+template <typename X>
+__device__ __forceinline__ void shift_up(X (&v)[4], int s, X none) {
+    if (s & 1) {
+        v[3] = v[2];
+        v[2] = v[1];
+        v[1] = v[0];
+        v[0] = none;
+    }
+    if (s & 2) {
+        v[3] = v[1];
+        v[2] = v[0];
+        v[1] = v[0] = none;
+    }
+}
+template <typename X>
+__device__ __forceinline__ void shift_down(X (&v)[4], int s, X none) {
+    if (s & 1) {
+        v[0] = v[1];
+        v[1] = v[2];
+        v[2] = v[3];
+        v[3] = none;
+    }
+    if (s & 2) {
+        v[0] = v[2];
+        v[1] = v[3];
+        v[2] = v[3] = none;
+    }
+}
+
 // Rows list[i], list[i + step], ... (U of them) of one column group (4 columns
 // starting at p0 within each row) into `best`; past the end of the list its last
-// row is repeated (a duplicate cannot change a minimum).  FULL: the 4 entries
-// exist and are aligned for one load; otherwise only the first `valid` are
-// read, one by one.  NT: the loads carry the nontemporal hint, for matrices
-// streamed once per solve (the whole-GPU solve) rather than reused from the
-// caches across instances.
-template <int U, bool FULL, typename E, bool NT, typename R>
-__device__ __forceinline__ void stream_batch(key_t<E> (&best)[4], const E* __restrict__ p0, int64_t ld, int valid,
+// row is repeated (a duplicate cannot change a minimum).  NT: the loads carry
+// the nontemporal hint, for matrices streamed once per solve (the whole-GPU
+// solve) rather than reused from the caches across instances.
+template <int U, typename E, bool NT, typename R>
+__device__ __forceinline__ void stream_batch(key_t<E> (&best)[4], const E* __restrict__ p0, int64_t ld,
                                              const R* list, int m, int i, int step) {
     uint32_t uu[U];
 #pragma unroll
@@ -523,31 +562,22 @@ __device__ __forceinline__ void stream_batch(key_t<E> (&best)[4], const E* __res
         const int idx = i + q * step;
         uu[q] = (uint32_t)list[idx < m ? idx : m - 1];
     }
-    uint32_t w[U][4];
-    if (FULL) {
-        // issue all U loads before using any of them: keeps U rows in flight per thread
-        typename Raw<E>::type raw[U];
+    // issue all U loads before using any of them: keeps U rows in flight per thread
+    typename Raw<E>::type raw[U];
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const global_ptr<typename Raw<E>::type> a =
-                reinterpret_cast<global_ptr<typename Raw<E>::type>>((global_ptr<E>)p0 + (int64_t)uu[q] * ld);
-            raw[q] = NT ? __builtin_nontemporal_load(a) : *a;
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < U; ++q) unpack<E>(raw[q], w[q]);
-    } else {
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const global_ptr<E> p = (global_ptr<E>)p0 + (int64_t)uu[q] * ld;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) w[q][j] = j < valid ? (uint32_t)p[j] : absent_code<E>();
-        }
+    for (int q = 0; q < U; ++q) {
+        const global_ptr<typename Raw<E>::type> a =
+            reinterpret_cast<global_ptr<typename Raw<E>::type>>((global_ptr<E>)p0 + (int64_t)uu[q] * ld);
+        raw[q] = NT ? __builtin_nontemporal_load(a) : *a;
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int q = 0; q < U; ++q)
+    for (int q = 0; q < U; ++q) {
+        uint32_t w[4];
+        unpack<E>(raw[q], w);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) best[j] = key_min(best[j], key_make<E>(w[q][j], uu[q]));
+        for (int j = 0; j < 4; ++j) best[j] = key_min(best[j], key_make<E>(w[j], uu[q]));
+    }
 }
 
 // Rows list[first], list[first + step], ... of one column group, U in flight,
@@ -555,38 +585,42 @@ __device__ __forceinline__ void stream_batch(key_t<E> (&best)[4], const E* __res
 // one or two rows (small rounds) is read in a batch of that size: with eight loads
 // of the same row a one-row round's stream took 1.2 us, with one 0.8 us (n=4096,
 // 64 workgroups).
-template <int U, bool FULL, typename E, bool NT, typename R>
+template <int U, typename E, bool NT, typename R>
 __device__ __forceinline__ void stream_group(key_t<E> (&best)[4], const E* __restrict__ p0, int64_t ld,
-                                             int valid, const R* list, int m, int first, int step) {
+                                             const R* list, int m, int first, int step) {
     if (m <= 2 * step) {
         if (first >= m) return;
-        if (m <= step) stream_batch<1, FULL, E, NT>(best, p0, ld, valid, list, m, first, step);
-        else stream_batch<2, FULL, E, NT>(best, p0, ld, valid, list, m, first, step);
+        if (m <= step) stream_batch<1, E, NT>(best, p0, ld, list, m, first, step);
+        else stream_batch<2, E, NT>(best, p0, ld, list, m, first, step);
         return;
     }
-    for (int i = first; i < m; i += step * U) stream_batch<U, FULL, E, NT>(best, p0, ld, valid, list, m, i, step);
+    for (int i = first; i < m; i += step * U) stream_batch<U, E, NT>(best, p0, ld, list, m, i, step);
 }
 
 // Stream rows list[r], list[r + P], ... (m entries in `list`, partition r) of
 // the matrix restricted to the slice into the running per-column minima, U rows
 // in flight per thread.  `width` = columns of the slice that exist in the
-// matrix (<= S).  `vec`: row segments are aligned for whole-group loads (W
-// aligned, ld and the slice start multiples of 4); otherwise, and for a
-// partial last group, entries are read one by one.
+// matrix (<= S).
 template <int G, int U, typename E, bool NT = false, typename R = int32_t>
 __device__ __forceinline__ void stream_rows(Cols<G, E>& cs, const Layout& lo, const E* __restrict__ W,
-                                            int64_t ld, int64_t col0, int width, bool vec,
-                                            const R* list, int m) {
+                                            int64_t ld, int64_t col0, int width, const R* list, int m) {
     // One column group at a time keeps only U x 4 weights live per thread.
 #pragma unroll
     for (int k = 0; k < G; ++k) {
         const int v0 = 4 * (lo.c + k * lo.L);
         if (v0 >= width) continue;
-        const E* p0 = W + col0 + v0;
-        if (vec && v0 + 3 < width)
-            stream_group<U, true, E, NT>(cs.best[k], p0, ld, 4, list, m, lo.r, lo.P);
-        else
-            stream_group<U, false, E, NT>(cs.best[k], p0, ld, min(4, width - v0), list, m, lo.r, lo.P);
+        const int s = group_shift<E>(v0, width);
+        if (col0 + v0 < s) {  // a matrix of fewer than 4 columns
+            for (int i = lo.r; i < m; i += lo.P)
+                for (int j = 0; j < 3; ++j)
+                    if (j < width)
+                        cs.best[k][j] = key_min(cs.best[k][j], key_make<E>((uint32_t)W[(int64_t)list[i] * ld + j],
+                                                                           (uint32_t)list[i]));
+            continue;
+        }
+        if (s) shift_up(cs.best[k], s, key_none<E>());
+        stream_group<U, E, NT>(cs.best[k], W + (col0 + v0 - s), ld, list, m, lo.r, lo.P);
+        if (s) shift_down(cs.best[k], s, key_none<E>());
     }
 }
 

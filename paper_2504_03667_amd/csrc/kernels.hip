@@ -40,8 +40,7 @@ __global__ __launch_bounds__(T) void k_single(const int32_t* __restrict__ W, int
                                               Ctl* __restrict__ ctl) {
     SharedSolve<T>& sh = g_sh<T>;
     SolveStats st = {0, 0, 0, 0, 0};
-    const bool vec = (flags & kFlagVec) != 0;
-    solve_single<T, G, U, int32_t>(W, ld, n, src, dist, pred, vec, (flags & kFlagLiteral) != 0, sh, st, ctl);
+    solve_single<T, G, U, int32_t>(W, ld, n, src, dist, pred, (flags & kFlagLiteral) != 0, sh, st, ctl);
     uint32_t s = st.status;
     uint64_t dummy = kNoKey;
     block_min_or<T>(dummy, s, sh.red);
@@ -66,7 +65,7 @@ __global__ __launch_bounds__(T) void k_grid(const int32_t* __restrict__ W, int64
     SharedSolve<T>& sh = g_sh<T>;
     SolveStats st = {0, 0, 0, 0, 0};
     const uint32_t epoch = ld_agent(&ctl->epoch);
-    solve_gang<T, G, U, int32_t, true, BAL, NARROW>(W, ld, n, src, dist, pred, (flags & kFlagVec) != 0, (flags & kFlagLiteral) != 0, S,
+    solve_gang<T, G, U, int32_t, true, BAL, NARROW>(W, ld, n, src, dist, pred, (flags & kFlagLiteral) != 0, S,
                         blockIdx.x, gridDim.x, timeout, grid_words(words, gridDim.x, S), sh, st, ctl, epoch);
     finish_launch(ctl, st, blockIdx.x == 0);
 }
@@ -88,7 +87,7 @@ template <int T, int G, typename E>
 __device__ __attribute__((noinline)) SolveStats single_variant(BatchItem I, bool literal) {
     SolveStats st = {0, 0, 0, 0, 0};
     solve_single<T, G, rows_in_flight<E>(), E>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred,
-                                              I.vec != 0, literal,
+                                              literal,
                              g_sh<T>, st, nullptr);
     uint32_t s = st.status;
     uint64_t dummy = kNoKey;
@@ -102,7 +101,7 @@ __device__ __attribute__((noinline)) SolveStats gang_variant(BatchItem I, int pa
                                                              Bar* bw, char* arena, uint32_t epoch) {
     SolveStats st = {0, 0, 0, 0, 0};
     solve_gang<T, G, rows_in_flight<E>(), E>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred,
-                                            I.vec != 0, literal, I.S, part, I.parts, timeout,
+                                            literal, I.S, part, I.parts, timeout,
                                             gang_words(arena + I.scratch_off, I.parts, I.S), g_sh<T>, st, nullptr, epoch);
     if (threadIdx.x == 0) gang_leave(bw, (uint32_t)I.parts);
     return st;
@@ -118,12 +117,12 @@ __device__ __attribute__((noinline)) SolveStats lc_variant(BatchItem I, int part
     const GangWords gw = gang_words(arena + I.scratch_off, I.parts, I.S);
     uint32_t b = 0;
     const int r = solve_lc<T, G, 8, E, false>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred,
-                                              I.vec != 0, I.S, part, I.parts, timeout, bw, gw.pubs, gw.lists, g_sh<T>,
+                                              I.S, part, I.parts, timeout, bw, gw.pubs, gw.lists, g_sh<T>,
                                               g_lc<T>, st, b, epoch, nullptr);
     if (r == kLcFallback) {
         ++st.fallbacks;
         st.status |= kStatusZeroFallback;
-        solve_gang<T, G, 8, E>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred, I.vec != 0, false,
+        solve_gang<T, G, 8, E>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred, false,
                                I.S, part, I.parts, timeout, gw, g_sh<T>, st, nullptr, epoch, b);
     } else {
         if (r == kLcTimeout) st.status |= kStatusTimeout;
@@ -147,7 +146,7 @@ __device__ __attribute__((noinline)) SolveStats group_variant(BatchItem I, int p
     uint64_t* recs = reinterpret_cast<uint64_t*>(arena + I.scratch_off);
     uint32_t* lists = reinterpret_cast<uint32_t*>(recs + 2 * (size_t)I.parts * rw);
     solve_multi<T, KP, E>(static_cast<const E*>(I.W), I.ld, I.n, static_cast<const MultiSrc*>(I.group), I.K,
-                          I.vec != 0, I.S, part, I.parts, timeout, recs, lists, g_sh<T>, g_mh<T>, st, epoch);
+                          I.S, part, I.parts, timeout, recs, lists, g_sh<T>, g_mh<T>, st, epoch);
     if (threadIdx.x == 0) gang_leave(bw, (uint32_t)I.parts);
     return st;
 }

@@ -50,9 +50,9 @@ __host__ __device__ constexpr uint64_t lc_entry(uint32_t d, uint32_t v) { return
 
 // Loads of U rows (list[i], list[i + step], ...) of one column group, widened;
 // past the end of the list the last row repeats (harmless for a minimum).
-template <int U, bool FULL, typename E, bool NT>
+template <int U, typename E, bool NT>
 __device__ __forceinline__ void lc_load(uint32_t (&w)[U][4], uint32_t (&uu)[U], uint32_t (&du)[U],
-                                        const E* __restrict__ p0, int64_t ld, int valid, const int32_t* list,
+                                        const E* __restrict__ p0, int64_t ld, const int32_t* list,
                                         const uint32_t* dl, int m, int i, int step) {
 #pragma unroll
     for (int q = 0; q < U; ++q) {
@@ -61,41 +61,32 @@ __device__ __forceinline__ void lc_load(uint32_t (&w)[U][4], uint32_t (&uu)[U], 
         uu[q] = (uint32_t)list[ii];
         du[q] = dl[ii];
     }
-    if (FULL) {
-        typename Raw<E>::type raw[U];
+    typename Raw<E>::type raw[U];
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const global_ptr<typename Raw<E>::type> a =
-                reinterpret_cast<global_ptr<typename Raw<E>::type>>((global_ptr<E>)p0 + (int64_t)uu[q] * ld);
-            raw[q] = NT ? __builtin_nontemporal_load(a) : *a;
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int q = 0; q < U; ++q) {
+        const global_ptr<typename Raw<E>::type> a =
+            reinterpret_cast<global_ptr<typename Raw<E>::type>>((global_ptr<E>)p0 + (int64_t)uu[q] * ld);
+        raw[q] = NT ? __builtin_nontemporal_load(a) : *a;
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            unpack<E>(raw[q], w[q]);
+    for (int q = 0; q < U; ++q) {
+        unpack<E>(raw[q], w[q]);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) w[q][j] = widen<E>(w[q][j]);  // compact codes -> weights
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const global_ptr<E> p = (global_ptr<E>)p0 + (int64_t)uu[q] * ld;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) w[q][j] = j < valid ? widen<E>((uint32_t)p[j]) : kInf;
-        }
+        for (int j = 0; j < 4; ++j) w[q][j] = widen<E>(w[q][j]);  // compact codes -> weights
     }
 }
 
 // Sweep: best[j] = min over the rows u of dist(u) + W[u][v].  No edge
 // (INT32_MAX) and negative weights (> INT32_MAX as uint32) offer nothing; a
 // negative weight sets *neg.  dist(u) < INT32_MAX and W < INT32_MAX: no wrap.
-template <int U, bool FULL, typename E, bool NT>
+template <int U, typename E, bool NT>
 __device__ __forceinline__ void lc_sweep_group(uint32_t (&best)[4], const E* __restrict__ p0, int64_t ld,
-                                               int valid, const int32_t* list, const uint32_t* dl, int m,
-                                               int first, int step, uint32_t& neg) {
+                                               const int32_t* list, const uint32_t* dl, int m, int first, int step,
+                                               uint32_t& neg) {
     for (int i = first; i < m; i += step * U) {
         uint32_t w[U][4], uu[U], du[U];
-        lc_load<U, FULL, E, NT>(w, uu, du, p0, ld, valid, list, dl, m, i, step);
+        lc_load<U, E, NT>(w, uu, du, p0, ld, list, dl, m, i, step);
 #pragma unroll
         for (int q = 0; q < U; ++q)
 #pragma unroll
@@ -112,13 +103,13 @@ __device__ __forceinline__ void lc_sweep_group(uint32_t (&best)[4], const E* __r
 // which no sum reaches).  Row v itself is tight when W[v][v] = 0; its key
 // (dist[v], v) loses to any tight u with a positive weight (dist(u) < dist[v]),
 // and a tight u with weight 0 sets *zero, so it never decides a pred.
-template <int U, bool FULL, typename E, bool NT>
+template <int U, typename E, bool NT>
 __device__ __forceinline__ void lc_pred_group(uint64_t (&key)[4], const uint32_t (&dv)[4], uint32_t v0,
-                                              const E* __restrict__ p0, int64_t ld, int valid, const int32_t* list,
+                                              const E* __restrict__ p0, int64_t ld, const int32_t* list,
                                               const uint32_t* dl, int m, int first, int step, uint32_t& zero) {
     for (int i = first; i < m; i += step * U) {
         uint32_t w[U][4], uu[U], du[U];
-        lc_load<U, FULL, E, NT>(w, uu, du, p0, ld, valid, list, dl, m, i, step);
+        lc_load<U, E, NT>(w, uu, du, p0, ld, list, dl, m, i, step);
 #pragma unroll
         for (int q = 0; q < U; ++q)
 #pragma unroll
@@ -132,38 +123,60 @@ __device__ __forceinline__ void lc_pred_group(uint64_t (&key)[4], const uint32_t
     }
 }
 
-// One pass of the staged rows over this thread's column groups.
+// One pass of the staged rows over this thread's column groups (partial last
+// groups as in stream_rows).
 template <int G, int U, typename E, bool NT>
 __device__ __forceinline__ void lc_sweep_rows(uint32_t (&best)[G][4], const Layout& lo, const E* __restrict__ W,
-                                              int64_t ld, int64_t col0, int width, bool vec, const int32_t* list,
+                                              int64_t ld, int64_t col0, int width, const int32_t* list,
                                               const uint32_t* dl, int m, uint32_t& neg) {
 #pragma unroll
     for (int k = 0; k < G; ++k) {
         const int v0 = 4 * (lo.c + k * lo.L);
         if (v0 >= width) continue;
-        const E* p0 = W + col0 + v0;
-        if (vec && v0 + 3 < width)
-            lc_sweep_group<U, true, E, NT>(best[k], p0, ld, 4, list, dl, m, lo.r, lo.P, neg);
-        else
-            lc_sweep_group<U, false, E, NT>(best[k], p0, ld, min(4, width - v0), list, dl, m, lo.r, lo.P, neg);
+        const int s = group_shift<E>(v0, width);
+        if (col0 + v0 < s) {  // a matrix of fewer than 4 columns
+            for (int i = lo.r; i < m; i += lo.P)
+                for (int j = 0; j < 3; ++j) {
+                    const uint32_t w = j < width ? (uint32_t)W[(int64_t)list[i] * ld + j] : kInf;
+                    neg |= w > kInf ? kStatusNegWeight : 0u;
+                    if (w < kInf) best[k][j] = min(best[k][j], dl[i] + w);
+                }
+            continue;
+        }
+        if (s) shift_up(best[k], s, 0xffffffffu);
+        lc_sweep_group<U, E, NT>(best[k], W + (col0 + v0 - s), ld, list, dl, m, lo.r, lo.P, neg);
+        if (s) shift_down(best[k], s, 0xffffffffu);
     }
 }
 
 template <int G, int U, typename E, bool NT>
 __device__ __forceinline__ void lc_pred_rows(uint64_t (&key)[G][4], const uint32_t (&dv)[G][4], const Layout& lo,
-                                             const E* __restrict__ W, int64_t ld, int64_t col0, int width, bool vec,
+                                             const E* __restrict__ W, int64_t ld, int64_t col0, int width,
                                              const int32_t* list, const uint32_t* dl, int m, uint32_t& zero) {
 #pragma unroll
     for (int k = 0; k < G; ++k) {
         const int v0 = 4 * (lo.c + k * lo.L);
         if (v0 >= width) continue;
-        const E* p0 = W + col0 + v0;
-        if (vec && v0 + 3 < width)
-            lc_pred_group<U, true, E, NT>(key[k], dv[k], (uint32_t)(col0 + v0), p0, ld, 4, list, dl, m, lo.r, lo.P,
-                                          zero);
-        else
-            lc_pred_group<U, false, E, NT>(key[k], dv[k], (uint32_t)(col0 + v0), p0, ld, min(4, width - v0), list,
-                                           dl, m, lo.r, lo.P, zero);
+        const int s = group_shift<E>(v0, width);
+        if (col0 + v0 < s) {  // a matrix of fewer than 4 columns
+            for (int i = lo.r; i < m; i += lo.P)
+                for (int j = 0; j < 3; ++j) {
+                    const uint32_t w = j < width ? (uint32_t)W[(int64_t)list[i] * ld + j] : kInf;
+                    if (w >= kInf || dl[i] + w != dv[k][j]) continue;
+                    key[k][j] = umin64(key[k][j], lc_entry(dl[i], (uint32_t)list[i]));
+                    if (w == 0u && list[i] != j) zero = 1u;
+                }
+            continue;
+        }
+        // a neighbour's column, dropped afterwards, is tight to nothing
+        uint32_t dt[4] = {dv[k][0], dv[k][1], dv[k][2], dv[k][3]};
+        if (s) {
+            shift_up(dt, s, 0xffffffffu);
+            shift_up(key[k], s, kNoKey);
+        }
+        lc_pred_group<U, E, NT>(key[k], dt, (uint32_t)(col0 + v0 - s), W + (col0 + v0 - s), ld, list, dl, m, lo.r,
+                                lo.P, zero);
+        if (s) shift_down(key[k], s, kNoKey);
     }
 }
 
@@ -327,7 +340,7 @@ enum LcResult { kLcDone = 0, kLcTimeout = 1, kLcFallback = 2 };
 // epoch stamps this launch's records (see gang_exchange).
 template <int T, int G, int U, typename E, bool NT>
 __device__ __forceinline__ int solve_lc(const E* __restrict__ W, int64_t ld, int32_t n, int32_t src,
-                                        int32_t* __restrict__ dist, int32_t* __restrict__ pred, bool vec, int S,
+                                        int32_t* __restrict__ dist, int32_t* __restrict__ pred, int S,
                                         int g, int nwg, long long timeout, Bar* bw, Pub* __restrict__ pubs,
                                         uint64_t* __restrict__ lists, SharedSolve<T>& sh, SharedLC<T>& lc,
                                         SolveStats& st, uint32_t& b, uint32_t epoch, Ctl* trace) {
@@ -375,7 +388,7 @@ __device__ __forceinline__ int solve_lc(const E* __restrict__ W, int64_t ld, int
 #pragma unroll
             for (int j = 0; j < 4; ++j) best[k][j] = 0xffffffffu;
         lc_stream<T>(slot_list(s), nwg, S, M, sh, lc, [&](int m) {
-            lc_sweep_rows<G, U, E, NT>(best, lo, W, ld, col0, width, vec, sh.list, lc.dl, m, neg);
+            lc_sweep_rows<G, U, E, NT>(best, lo, W, ld, col0, width, sh.list, lc.dl, m, neg);
         });
         lc_merge32<T, G>(best, lo, sh.mrg);
         if (trace && g == 0 && threadIdx.x == 0 && st.rounds <= (unsigned long long)kTraceCap) {
@@ -439,7 +452,7 @@ __device__ __forceinline__ int solve_lc(const E* __restrict__ W, int64_t ld, int
         for (int j = 0; j < 4; ++j) key[k][j] = kNoKey;
     uint32_t zero = 0;
     lc_stream<T>(slot_list((b - 1) & 1), nwg, S, R, sh, lc, [&](int m) {
-        lc_pred_rows<G, U, E, NT>(key, dt, lo, W, ld, col0, width, vec, sh.list, lc.dl, m, zero);
+        lc_pred_rows<G, U, E, NT>(key, dt, lo, W, ld, col0, width, sh.list, lc.dl, m, zero);
     });
     lc_merge64<T, G>(key, lo, sh.mrg);
     // agree on the tight-zero-edge verdict before writing anything

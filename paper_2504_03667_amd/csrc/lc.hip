@@ -18,10 +18,9 @@ __global__ __launch_bounds__(T) void k_lc(const int32_t* __restrict__ W, int64_t
     SharedSolve<T>& sh = g_sh<T>;
     SolveStats st = {0, 0, 0, 0, 0};
     uint32_t b = 0;
-    const bool vec = (flags & kFlagVec) != 0;
     const uint32_t epoch = ld_agent(&ctl->epoch);
     const GangWords gw = grid_words(words, gridDim.x, S);
-    const int r = solve_lc<T, G, U, int32_t, true>(W, ld, n, src, dist, pred, vec, S, blockIdx.x, gridDim.x, timeout,
+    const int r = solve_lc<T, G, U, int32_t, true>(W, ld, n, src, dist, pred, S, blockIdx.x, gridDim.x, timeout,
                                                    &ctl->b, gw.pubs, gw.lists, sh, g_lc<T>, st, b, epoch, ctl);
     if (r == kLcTimeout) {
         st.status |= kStatusTimeout;
@@ -31,7 +30,7 @@ __global__ __launch_bounds__(T) void k_lc(const int32_t* __restrict__ W, int64_t
         // so solve again with the Dijkstra rounds (which handle zero weights)
         ++st.fallbacks;
         st.status |= kStatusZeroFallback;
-        solve_gang<T, G, U, int32_t, true>(W, ld, n, src, dist, pred, vec, false, S, blockIdx.x, gridDim.x, timeout,
+        solve_gang<T, G, U, int32_t, true>(W, ld, n, src, dist, pred, false, S, blockIdx.x, gridDim.x, timeout,
                                            gw, sh, st, ctl, epoch, b);
     } else {
         st.barriers += b;

@@ -102,7 +102,7 @@ __device__ __forceinline__ uint32_t segment_sum32(uint32_t x, int L) {
 // words; lists: 2 * nwg * S entries.  Returns false if an exchange timed out.
 template <int T, int KP, typename E>
 __device__ __forceinline__ bool solve_multi(const E* __restrict__ W, int64_t ld, int32_t n,
-                                            const MultiSrc* __restrict__ srcs, int K, bool vec, int S, int g, int nwg,
+                                            const MultiSrc* __restrict__ srcs, int K, int S, int g, int nwg,
                                             long long timeout, uint64_t* __restrict__ recs,
                                             uint32_t* __restrict__ lists, SharedSolve<T>& sh, SharedMulti<T>& mh,
                                             SolveStats& st, uint32_t epoch) {
@@ -299,9 +299,13 @@ __device__ __forceinline__ bool solve_multi(const E* __restrict__ W, int64_t ld,
             __syncthreads();
             const int m = (int)min((uint32_t)kCap, M - e0);
             constexpr int U = KP <= 2 ? 8 : 4;  // rows in flight (fewer when a thread holds 4 sources)
-            if (mycols && mine) {
+            if (mycols && mine && 4 * lo.c < width) {
                 const int v0 = 4 * lo.c;
-                const bool full = vec && v0 + 3 < width;
+                const int s = group_shift<E>(v0, width);  // n >= 4: see stream_rows
+#pragma unroll
+                for (int i = 0; i < KP; ++i)
+                    if (s) shift_up(best[i], s, key_none<E>());
+                const E* p0 = W + (col0 + v0 - s);
                 for (int i0 = 0; i0 < m; i0 += U) {
                     uint32_t row[U], msk[U];
 #pragma unroll
@@ -311,28 +315,18 @@ __device__ __forceinline__ bool solve_multi(const E* __restrict__ W, int64_t ld,
                         row[u] = idx < m ? (uint32_t)sh.list[idx] : 0u;
                     }
                     uint32_t w[U][4];
-                    if (full) {
-                        typename Raw<E>::type raw[U];
+                    typename Raw<E>::type raw[U];
 #pragma unroll
-                        for (int u = 0; u < U; ++u)
-                            if (msk[u]) {
-                                const global_ptr<typename Raw<E>::type> a = reinterpret_cast<global_ptr<typename Raw<E>::type>>(
-                                    (global_ptr<E>)W + (int64_t)row[u] * ld + col0 + v0);
-                                raw[u] = *a;
-                            }
-                        __builtin_amdgcn_sched_barrier(0);
+                    for (int u = 0; u < U; ++u)
+                        if (msk[u]) {
+                            const global_ptr<typename Raw<E>::type> a =
+                                reinterpret_cast<global_ptr<typename Raw<E>::type>>((global_ptr<E>)p0 + (int64_t)row[u] * ld);
+                            raw[u] = *a;
+                        }
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int u = 0; u < U; ++u)
-                            if (msk[u]) unpack<E>(raw[u], w[u]);
-                    } else {
-#pragma unroll
-                        for (int u = 0; u < U; ++u)
-                            if (msk[u]) {
-                                const global_ptr<E> p = (global_ptr<E>)W + (int64_t)row[u] * ld + col0 + v0;
-#pragma unroll
-                                for (int j = 0; j < 4; ++j) w[u][j] = v0 + j < width ? (uint32_t)p[j] : absent_code<E>();
-                            }
-                    }
+                    for (int u = 0; u < U; ++u)
+                        if (msk[u]) unpack<E>(raw[u], w[u]);
 #pragma unroll
                     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -341,6 +335,9 @@ __device__ __forceinline__ bool solve_multi(const E* __restrict__ W, int64_t ld,
 #pragma unroll
                                 for (int j = 0; j < 4; ++j) best[i][j] = key_min(best[i][j], key_make<E>(w[u][j], row[u]));
                 }
+#pragma unroll
+                for (int i = 0; i < KP; ++i)
+                    if (s) shift_down(best[i], s, key_none<E>());
             }
             __syncthreads();
         }

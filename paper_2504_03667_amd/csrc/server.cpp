@@ -334,7 +334,6 @@ struct sssp_server {
                 it.W = g.Ws;
                 it.ld = g.lds;
                 it.elem = g.elem;
-                it.vec = ((uintptr_t)g.Ws % (4 * (uintptr_t)g.elem)) == 0 && g.lds % 4 == 0;
                 it.dist = q.dist;
                 it.pred = q.pred;
                 it.n = g.n;

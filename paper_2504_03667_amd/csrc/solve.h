@@ -74,7 +74,7 @@ __device__ __forceinline__ uint32_t owner_bit(const Layout& lo, int64_t v, int w
 // ---------------------------------------------------------------------------
 template <int T, int G, int U, typename E>
 __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld, int32_t n, int32_t src,
-                             int32_t* __restrict__ dist, int32_t* __restrict__ pred, bool vec,
+                             int32_t* __restrict__ dist, int32_t* __restrict__ pred,
                              bool literal, SharedSolve<T>& sh, SolveStats& st, Ctl* trace) {
     const Layout lo = make_layout<T>(n);
     Cols<G, E> cs;
@@ -95,7 +95,7 @@ __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld
         const long long t_round = trace ? wall_clock64() : 0;
         const bool step = literal || redo;
         const uint32_t bucket = settle(cs, d, step, step ? owner_bit(lo, (int64_t)u0, n) : 0u);
-        stream_rows<G, U, E>(cs, lo, W, ld, 0, n, vec, sh.list16, (int)M);
+        stream_rows<G, U, E>(cs, lo, W, ld, 0, n, sh.list16, (int)M);
         merge_partitions<T, G>(cs, lo, sh.mrg);
         if (!redo) {
             ++st.rounds;
@@ -667,7 +667,7 @@ __device__ __forceinline__ const uint64_t* entry_addr(const SharedSolve<T>& sh, 
 // after that publish).
 template <int T, int G, int U, typename E, bool NT = false, bool BAL = false, bool NARROW = false>
 __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, int32_t n, int32_t src,
-                           int32_t* __restrict__ dist, int32_t* __restrict__ pred, bool vec, bool literal,
+                           int32_t* __restrict__ dist, int32_t* __restrict__ pred, bool literal,
                            int S, int g, int nwg, long long timeout, GangWords gw, SharedSolve<T>& sh,
                            SolveStats& st, Ctl* trace, uint32_t epoch, uint32_t b0 = 0) {
     static_assert(T == kCap, "one staged bucket entry per thread");
@@ -799,7 +799,7 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
                         if (threadIdx.x == 0)
                             a = __hip_atomic_fetch_add(ctr, inc_of(nua), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
-                    stream_rows<G, U, E, NT>(cs, lo, W, ld, c0, wd, vec, sh.list, (int)kcnt);
+                    stream_rows<G, U, E, NT>(cs, lo, W, ld, c0, wd, sh.list, (int)kcnt);
                     if (threadIdx.x == 0) sh.claim[0] = a;
                     __syncthreads();
                     chunks += kcnt;
@@ -852,7 +852,7 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
                 if (!ready && e < M) stage(e, nxt);
                 if (!staged || step) __syncthreads();  // a staged bucket: read_records ended with a barrier
                 if (e + kCap < M) nxt = ld_agent(entry_addr<T>(sh, rl, nwg, S, e + kCap));
-                stream_rows<G, U, E, NT>(cs, lo, W, ld, col0, width, vec, sh.list,
+                stream_rows<G, U, E, NT>(cs, lo, W, ld, col0, width, sh.list,
                                          (int)min((uint32_t)kCap, M - e0));
                 __syncthreads();
             }

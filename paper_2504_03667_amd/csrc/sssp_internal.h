@@ -11,9 +11,8 @@ struct Ctl;
 struct Pub;
 struct Bar;
 
-// internal flag bits, above the public SSSP_FLAG_* bits
+// flag bits as the kernels read them
 constexpr uint32_t kFlagLiteral = SSSP_FLAG_LITERAL;
-constexpr uint32_t kFlagVec = 1u << 16;  // rows are 16-byte aligned: 128-bit loads
 
 struct SolveArgs {
     const int32_t* W;
@@ -60,7 +59,6 @@ struct BatchItem {
     int32_t n;
     int32_t src;
     int32_t elem;        // 4: the caller's int32 matrix; 2 / 1: an exact compact copy
-    int32_t vec;         // rows aligned for whole-group loads
     int32_t parts;       // workgroups that solve it (1: one workgroup alone; > 1: a gang)
     int32_t S;           // columns per gang member
     int32_t method;      // kMethodDijkstra, kMethodLabelCorrecting or kMethodGroup
