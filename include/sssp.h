@@ -63,7 +63,9 @@ extern "C" {
 /* flags for sssp_dense_solve_ex / batched calls */
 #define SSSP_FLAG_LITERAL 1u  /* settle one vertex per round: Algorithm 1 exactly as printed */
 #define SSSP_FLAG_SINGLE 2u   /* force the one-workgroup kernel */
-#define SSSP_FLAG_GRID 4u     /* force the persistent whole-GPU kernel */
+#define SSSP_FLAG_GRID 4u     /* force the persistent whole-GPU kernel; with either flag every settled
+                                 vertex's row is read (measurements of Algorithm 1's whole loop),
+                                 otherwise rows that can no longer lower a dist are left out */
 #define SSSP_FLAG_COMPACT 8u  /* plans and servers: stream an exact uint8/uint16 copy of each graph
                                  whose weights all fit (built once, owned by the plan or server) */
 #define SSSP_FLAG_LABEL_CORRECTING 16u
@@ -79,7 +81,7 @@ extern "C" {
 
 /* statistics of a finished launch (sssp_last_status `stats`, 4 entries) */
 #define SSSP_STAT_ROUNDS 0     /* rounds (one bucket of equal-dist vertices, or one vertex, each) */
-#define SSSP_STAT_SETTLED 1    /* vertices settled with finite dist = matrix rows relaxed */
+#define SSSP_STAT_SETTLED 1    /* vertices settled with finite dist = the rows Algorithm 1 relaxes */
 #define SSSP_STAT_FALLBACKS 2  /* rounds redone as one literal step because of zero weights */
 #define SSSP_STAT_BARRIERS 3   /* grid barriers passed (whole-GPU kernel) */
 
@@ -160,8 +162,9 @@ int sssp_last_status(void* stream, int32_t* status, int64_t* stats);
 /*
  * Per-round trace of the last one-workgroup or whole-GPU solve on `stream`
  * (synchronises it): t_ns[i] = start of round i in ns after the start of
- * round 0, t_ns[count] = end of the solve, rows[i] = matrix rows streamed in
- * round i (rows[count] = -1).  Writes min(count + 1, cap) entries; *count gets
+ * round 0, t_ns[count] = end of the solve, rows[i] = vertices settled in round i,
+ * whose rows it streams (those that can lower no dist excepted, see
+ * SSSP_FLAG_GRID) (rows[count] = -1).  Writes min(count + 1, cap) entries; *count gets
  * the number of rounds recorded (at most 256).  A debugging and tuning aid.
  */
 int sssp_last_trace(void* stream, int64_t* t_ns, int32_t* rows, int32_t cap, int32_t* count);
@@ -441,7 +444,7 @@ typedef struct sssp_query_info {
     int32_t status;       /* SSSP_STATUS_* bits of its solve */
     int32_t parts;        /* workgroups that solved it */
     int32_t rounds;
-    int64_t settled;      /* rows relaxed */
+    int64_t settled;      /* vertices settled (label-correcting: rows streamed) */
     int64_t t_submit_ns;  /* sssp_server_now_ns() clock */
     int64_t t_admit_ns;
     int64_t t_done_ns;    /* when the host saw the completion record */

@@ -245,7 +245,7 @@ int solve(const int32_t* W, int64_t ld, int32_t n, int32_t src, int32_t* dist, i
     DeviceInfo di;
     rc = get_scratch(stream, &sc, &di);
     if (rc) return rc;
-    SolveArgs a{W, ld, n, src, dist, pred, flags & SSSP_FLAG_LITERAL, sc->ctl};
+    SolveArgs a{W, ld, n, src, dist, pred, kernel_flags(flags), sc->ctl};
     const bool single = !lc && ((flags & SSSP_FLAG_SINGLE) ||
                                 (!(flags & SSSP_FLAG_GRID) && n <= single_crossover()));
     hipError_t e;

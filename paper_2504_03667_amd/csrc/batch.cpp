@@ -42,6 +42,7 @@ struct Source {
     const void* W;
     int64_t ld;
     int elem;
+    int32_t wmin;  // of a compact copy: its smallest off-diagonal weight; else 0
 };
 
 struct Build {
@@ -161,6 +162,7 @@ int build(const sssp_instance* inst, const Source* src, int32_t count, int32_t s
         b.W = src[order[k]].W;
         b.ld = src[order[k]].ld;
         b.elem = src[order[k]].elem;
+        b.wmin = src[order[k]].wmin;
         b.dist = I.dist;
         b.pred = I.pred;
         b.n = I.n;
@@ -418,7 +420,7 @@ int sssp_batch_layout(const sssp_instance* inst, int32_t count, uint32_t flags, 
         return err(SSSP_EINVAL, "single_max_n %d above the limit %d", single_max_n, max_batch_single_n());
     if (gang_columns % 4) return err(SSSP_EINVAL, "gang_columns %d is not a multiple of 4", gang_columns);
     std::vector<Source> src(count);
-    for (int32_t i = 0; i < count; ++i) src[i] = Source{inst[i].W, inst[i].ld, 4};
+    for (int32_t i = 0; i < count; ++i) src[i] = Source{inst[i].W, inst[i].ld, 4, 0};
     std::vector<char> lc;
     if (flags & SSSP_FLAG_LABEL_CORRECTING) lc.assign(count, 1);
     Build b;
@@ -460,7 +462,7 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     if (batch_occupancy(&per_cu) != 0 || per_cu < 1) return err(SSSP_EDEVICE, "batched kernel does not fit a CU");
     int nwg = tuning && tuning->workgroups ? std::min(tuning->workgroups, per_cu * cus) : per_cu * cus;
     std::vector<Source> src(count);
-    for (int32_t i = 0; i < count; ++i) src[i] = Source{inst[i].W, inst[i].ld, 4};
+    for (int32_t i = 0; i < count; ++i) src[i] = Source{inst[i].W, inst[i].ld, 4, 0};
     Build b;
     std::vector<char> lc;
     if (flags & SSSP_FLAG_LABEL_CORRECTING) lc.assign(count, 1);
@@ -532,7 +534,7 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
     // exact compact copies of the distinct matrices, when asked for and when they fit
     std::map<std::pair<const int32_t*, int64_t>, int> seen;
     for (int32_t i = 0; i < count; ++i) {
-        p->src[i] = Source{inst[i].W, inst[i].ld, 4};
+        p->src[i] = Source{inst[i].W, inst[i].ld, 4, 0};
         if (!(flags & SSSP_FLAG_COMPACT)) continue;
         auto key = std::make_pair(inst[i].W, inst[i].ld);
         auto it = seen.find(key);
@@ -548,7 +550,7 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
             }
         }
         const CompactCopy& c = p->copies[it->second];
-        if (c.elem < 4) p->src[i] = Source{c.data, c.ld, c.elem};
+        if (c.elem < 4) p->src[i] = Source{c.data, c.ld, c.elem, c.woff};
     }
     // matrices whose shared instances may run in lockstep groups: n <= kGroupMaxN and
     // every off-diagonal weight >= 1 (fused rounds then never fall back)

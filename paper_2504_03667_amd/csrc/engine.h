@@ -216,6 +216,10 @@ __device__ __forceinline__ uint64_t lane_value64(uint64_t x, int l) {
     return ((uint64_t)lane_value((uint32_t)(x >> 32), l) << 32) | lane_value((uint32_t)x, l);
 }
 
+// A value that is the same in every lane, moved to a scalar register (so that
+// branches and loops on it are scalar).
+__device__ __forceinline__ uint32_t scalar(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+
 // minimum over the wave, in every lane
 __device__ __forceinline__ uint64_t wave_min64(uint64_t x) {
     x = umin64(x, row_shr64<1>(x));
@@ -597,6 +601,23 @@ __device__ __forceinline__ void stream_group(key_t<E> (&best)[4], const E* __res
     for (int i = first; i < m; i += step * U) stream_batch<U, E, NT>(best, p0, ld, list, m, i, step);
 }
 
+// Can a row of a round of dist d lower one of a group's 4 columns?  Only an open
+// column above d + wmin, the smallest weight known (0 for the caller's matrices:
+// weights are not negative and an improvement is strict).  (One subtraction per column: values up to d + wmin wrap to the top,
+// settled ones and those that are no column come out above the open ones.)
+__device__ __forceinline__ bool group_open(const uint32_t (&x)[4], uint32_t d, uint32_t wmin) {
+    const uint32_t lim = d + wmin;
+    const uint32_t t = min(min(x[0] - (lim + 1u), x[1] - (lim + 1u)), min(x[2] - (lim + 1u), x[3] - (lim + 1u)));
+    return lim < kInf && t < kInf - lim;
+}
+template <int G>
+__device__ __forceinline__ uint32_t groups_open(const uint32_t (&x)[G][4], uint32_t d, uint32_t wmin) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < G; ++k) m |= (group_open(x[k], d, wmin) ? 1u : 0u) << k;
+    return m;
+}
+
 // Stream rows list[r], list[r + P], ... (m entries in `list`, partition r) of
 // the matrix restricted to the slice into the running per-column minima, U rows
 // in flight per thread.  `width` = columns of the slice that exist in the
@@ -621,6 +642,61 @@ __device__ __forceinline__ void stream_rows(Cols<G, E>& cs, const Layout& lo, co
         if (s) shift_up(cs.best[k], s, key_none<E>());
         stream_group<U, E, NT>(cs.best[k], W + (col0 + v0 - s), ld, list, m, lo.r, lo.P);
         if (s) shift_down(cs.best[k], s, key_none<E>());
+    }
+}
+
+// Rounds of many rows with few groups left to lower (the stragglers of a dense
+// graph): the workgroup's threads take a row each instead of a group each, so
+// that 64 lanes of a wave are at work on one group and not one.  By rows, a
+// partition waits for its rows in batches of 8, about m / 12 P microseconds
+// (measured: 0.7 us a batch); by groups, about 1 + m / 2048 for each of the ng.
+// (n=65536, p=0.5, sources with a few vertices beyond the large last bucket:
+// 2.5 ms without, 1.2 with.)
+constexpr uint32_t kSparseGroups = 16;
+__device__ __forceinline__ bool sparse_round(uint32_t ng, uint32_t m, int P) {
+    return ng <= kSparseGroups && m > 64u && (uint64_t)ng * (2048u + m) * (12u * (uint32_t)P) < (uint64_t)m * 2048u;
+}
+
+// One group (its 4 columns starting at local column v0) of such a round: row(e)
+// is the e-th of the m rows; the group's four keys go to out[0..3] (LDS, all
+// ones between rounds).
+template <int T, typename E, bool NT, typename Row>
+__device__ __forceinline__ void stream_sparse(const E* __restrict__ W, int64_t ld, int64_t col0, int width, int v0,
+                                              int m, Row row, key_t<E>* out) {
+    constexpr int U = 4;
+    const int s = group_shift<E>(v0, width);
+    const E* p0 = W + (col0 + v0 - s);  // m > 64 rows: at least 4 columns
+    key_t<E> best[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) best[j] = key_none<E>();
+    for (int i = (int)threadIdx.x; i < m; i += T * U) {
+        uint32_t uu[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) uu[q] = row(min(i + q * T, m - 1));
+        typename Raw<E>::type raw[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const global_ptr<typename Raw<E>::type> a =
+                reinterpret_cast<global_ptr<typename Raw<E>::type>>((global_ptr<E>)p0 + (int64_t)uu[q] * ld);
+            raw[q] = NT ? __builtin_nontemporal_load(a) : *a;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            uint32_t w[4];
+            unpack<E>(raw[q], w);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) best[j] = key_min(best[j], key_make<E>(w[j], uu[q]));
+        }
+    }
+    if (s) shift_down(best, s, key_none<E>());
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        key_t<E> b;
+        if constexpr (sizeof(E) == 4) b = wave_min64(best[j]);
+        else b = wave_min32(best[j]);
+        if (wave_lane() == 0)
+            __hip_atomic_fetch_min(&out[j], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 }
 
@@ -758,14 +834,16 @@ __device__ __forceinline__ uint32_t candidate(key_t<E> best, uint32_t d, uint32_
 
 // Dist of the open columns if the pending round (bucket dist d) is applied; a
 // position that is not open keeps its x, which is above every dist.  `neg` gets
-// its sign bit set if a negative weight was the best candidate of a column: every
-// owned column has met at least one row, so its key is a weight's.
+// its sign bit set if a negative weight was the best candidate of a column, in a
+// round that read rows (`met`): every open column above d has then met one, so its
+// key is a weight's.
 // With the bucket settled beforehand, a candidate equal to d exists exactly when
 // the bucket has a zero-weight edge to an open vertex outside it: such a vertex
 // would join the bucket during the round and change the order Algorithm 1
 // settles it in (the zero-weight hazard of a fused round).
 template <int G, typename E>
-__device__ __forceinline__ void candidates(const Cols<G, E>& cs, uint32_t d, uint32_t (&cand)[G][4], uint32_t& neg) {
+__device__ __forceinline__ void candidates(const Cols<G, E>& cs, uint32_t d, bool met, uint32_t (&cand)[G][4],
+                                           uint32_t& neg) {
 #pragma unroll
     for (int k = 0; k < G; ++k)
 #pragma unroll
@@ -773,7 +851,7 @@ __device__ __forceinline__ void candidates(const Cols<G, E>& cs, uint32_t d, uin
             const uint32_t x = cs.x[k][j], w = key_weight<E>(cs.best[k][j]);
             // saturating: a weight above INT32_MAX (a negative one) offers nothing
             cand[k][j] = (int32_t)x >= 0 ? min(x, __builtin_elementwise_add_sat(d, w)) : x;
-            neg |= w & ~x;
+            neg |= met ? w & ~x : 0u;
         }
 }
 

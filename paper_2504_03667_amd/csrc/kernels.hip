@@ -40,7 +40,8 @@ __global__ __launch_bounds__(T) void k_single(const int32_t* __restrict__ W, int
                                               Ctl* __restrict__ ctl) {
     SharedSolve<T>& sh = g_sh<T>;
     SolveStats st = {0, 0, 0, 0, 0};
-    solve_single<T, G, U, int32_t>(W, ld, n, src, dist, pred, (flags & kFlagLiteral) != 0, sh, st, ctl);
+    solve_single<T, G, U, int32_t>(W, ld, n, src, dist, pred, (flags & kFlagLiteral) != 0, (flags & kFlagEveryRow) != 0, 0u,
+                                    sh, st, ctl);
     uint32_t s = st.status;
     uint64_t dummy = kNoKey;
     block_min_or<T>(dummy, s, sh.red);
@@ -65,7 +66,8 @@ __global__ __launch_bounds__(T) void k_grid(const int32_t* __restrict__ W, int64
     SharedSolve<T>& sh = g_sh<T>;
     SolveStats st = {0, 0, 0, 0, 0};
     const uint32_t epoch = ld_agent(&ctl->epoch);
-    solve_gang<T, G, U, int32_t, true, BAL, NARROW>(W, ld, n, src, dist, pred, (flags & kFlagLiteral) != 0, S,
+    solve_gang<T, G, U, int32_t, true, BAL, NARROW>(W, ld, n, src, dist, pred, (flags & kFlagLiteral) != 0,
+                        (flags & kFlagEveryRow) != 0, 0u, S,
                         blockIdx.x, gridDim.x, timeout, grid_words(words, gridDim.x, S), sh, st, ctl, epoch);
     finish_launch(ctl, st, blockIdx.x == 0);
 }
@@ -87,8 +89,7 @@ template <int T, int G, typename E>
 __device__ __attribute__((noinline)) SolveStats single_variant(BatchItem I, bool literal) {
     SolveStats st = {0, 0, 0, 0, 0};
     solve_single<T, G, rows_in_flight<E>(), E>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred,
-                                              literal,
-                             g_sh<T>, st, nullptr);
+                                              literal, false, (uint32_t)I.wmin, g_sh<T>, st, nullptr);
     uint32_t s = st.status;
     uint64_t dummy = kNoKey;
     block_min_or<T>(dummy, s, g_sh<T>.red);
@@ -101,7 +102,7 @@ __device__ __attribute__((noinline)) SolveStats gang_variant(BatchItem I, int pa
                                                              Bar* bw, char* arena, uint32_t epoch) {
     SolveStats st = {0, 0, 0, 0, 0};
     solve_gang<T, G, rows_in_flight<E>(), E>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred,
-                                            literal, I.S, part, I.parts, timeout,
+                                            literal, false, (uint32_t)I.wmin, I.S, part, I.parts, timeout,
                                             gang_words(arena + I.scratch_off, I.parts, I.S), g_sh<T>, st, nullptr, epoch);
     if (threadIdx.x == 0) gang_leave(bw, (uint32_t)I.parts);
     return st;
@@ -122,7 +123,7 @@ __device__ __attribute__((noinline)) SolveStats lc_variant(BatchItem I, int part
     if (r == kLcFallback) {
         ++st.fallbacks;
         st.status |= kStatusZeroFallback;
-        solve_gang<T, G, 8, E>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred, false,
+        solve_gang<T, G, 8, E>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred, false, false, (uint32_t)I.wmin,
                                I.S, part, I.parts, timeout, gw, g_sh<T>, st, nullptr, epoch, b);
     } else {
         if (r == kLcTimeout) st.status |= kStatusTimeout;

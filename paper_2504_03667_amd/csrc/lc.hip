@@ -30,7 +30,7 @@ __global__ __launch_bounds__(T) void k_lc(const int32_t* __restrict__ W, int64_t
         // so solve again with the Dijkstra rounds (which handle zero weights)
         ++st.fallbacks;
         st.status |= kStatusZeroFallback;
-        solve_gang<T, G, U, int32_t, true>(W, ld, n, src, dist, pred, false, S, blockIdx.x, gridDim.x, timeout,
+        solve_gang<T, G, U, int32_t, true>(W, ld, n, src, dist, pred, false, false, 0u, S, blockIdx.x, gridDim.x, timeout,
                                            gw, sh, st, ctl, epoch, b);
     } else {
         st.barriers += b;

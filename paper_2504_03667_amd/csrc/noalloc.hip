@@ -91,7 +91,7 @@ extern "C" int sssp_dense_solve_noalloc(const int32_t* W, int64_t ld, int32_t n,
     rc = device_props(&cus, &khz);
     if (rc) return rc;
     Ctl* ctl = reinterpret_cast<Ctl*>(base);
-    SolveArgs a{W, ld, n, src, dist, pred, flags & SSSP_FLAG_LITERAL, ctl};
+    SolveArgs a{W, ld, n, src, dist, pred, kernel_flags(flags), ctl};
     const bool single = (flags & SSSP_FLAG_SINGLE) || (!(flags & SSSP_FLAG_GRID) && n <= single_max_default());
     hipError_t e;
     if (single) {

@@ -61,6 +61,7 @@ struct Graph {
     const void* Ws;    // what is streamed: W, or the server's compact copy
     int64_t lds;
     int32_t elem;
+    int32_t wmin;      // of a compact copy: its smallest off-diagonal weight; else 0
     void* owned;       // compact copy to free on destroy
     int32_t lc_forced = 0;   // every query label-correcting
     int32_t max_rounds = 0;  // most rounds a completed Dijkstra query of it took
@@ -334,6 +335,7 @@ struct sssp_server {
                 it.W = g.Ws;
                 it.ld = g.lds;
                 it.elem = g.elem;
+                it.wmin = g.wmin;
                 it.dist = q.dist;
                 it.pred = q.pred;
                 it.n = g.n;
@@ -560,7 +562,7 @@ int sssp_server_add_graph_ex(sssp_server* s, const int32_t* W, int64_t ld, int32
         s->plan(n, kMethodDijkstra, &parts, &S);
         if (S > max_serve_slice()) return err(SSSP_EUNSUPPORTED, "n=%d is too large for this server", n);
     }
-    Graph g{W, ld, n, W, ld, 4, nullptr};
+    Graph g{W, ld, n, W, ld, 4, 0, nullptr};
     if (flags & SSSP_FLAG_COMPACT) {
         // built on a stream of its own: the server's stream holds the resident kernel
         hipStream_t cs = nullptr;
@@ -570,7 +572,7 @@ int sssp_server_add_graph_ex(sssp_server* s, const int32_t* W, int64_t ld, int32
         const int rc = make_compact(W, ld, n, cs, &c);
         (void)hipStreamDestroy(cs);
         if (rc) return rc;
-        if (c.elem < 4) g = Graph{W, ld, n, c.data, c.ld, c.elem, c.data};
+        if (c.elem < 4) g = Graph{W, ld, n, c.data, c.ld, c.elem, c.woff, c.data};
     }
     g.lc_forced = (flags & SSSP_FLAG_LABEL_CORRECTING) ? 1 : 0;
     std::lock_guard<std::mutex> lk(s->mu);

@@ -33,13 +33,62 @@ struct SharedSolve {
     struct alignas(16) {
         uint32_t d, vert, rows, flags;
     } res;  // read_records results for the whole workgroup
+    uint64_t res_need;  // ... and, for narrow slices, the lanes whose group the next round reads
     uint32_t claim[2];    // chunk claims of a balanced round, broadcast by thread 0
     uint32_t stage_late;  // a bucket entry did not arrive in time (set once; the solve then ends)
     int32_t item;
     uint32_t flag;
-    uint64_t min3[3];   // solve_single: lowest key of a round, by round number mod 3
+    uint64_t min3[3];    // solve_single: lowest key of a round, by round number mod 3
     uint32_t count3[3];  // ... and its bucket's size
+    uint32_t open3[3];   // groups a round can lower, by round number mod 3 (also solve_gang)
+    uint32_t listed;     // ... of a sparse round, how many are in group
+    uint16_t group[kSparseGroups];  // ... and which (local column / 4)
+    uint64_t sparse[4 * kSparseGroups];  // their keys in a sparse round, all ones between rounds
 };
+
+// The owners (the threads below L: whole waves, or lanes of wave 0) count the
+// groups that a round at d can lower in open3[slot]; ordered before its readers by
+// a workgroup barrier.
+template <int T, int G>
+__device__ __forceinline__ void count_groups(const uint32_t (&x)[G][4], uint32_t d, uint32_t wmin, uint32_t slot,
+                                             SharedSolve<T>& sh) {
+    uint32_t count = 0;
+#pragma unroll
+    for (int k = 0; k < G; ++k) count += (uint32_t)__popcll(wave_mask(group_open(x[k], d, wmin)));
+    if (count && (threadIdx.x & (kWave - 1)) == 0)
+        __hip_atomic_fetch_add(&sh.open3[slot], count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// ... and list a sparse round's in sh.group, in any order (sh.listed: zero before,
+// and again afterwards by the caller).
+template <int T, int G>
+__device__ __forceinline__ void list_groups(const uint32_t (&x)[G][4], uint32_t d, uint32_t wmin, const Layout& lo,
+                                            SharedSolve<T>& sh) {
+    if (lo.r == 0)
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+            if (group_open(x[k], d, wmin))
+                sh.group[__hip_atomic_fetch_add(&sh.listed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] =
+                    (uint16_t)(lo.c + k * lo.L);
+    __syncthreads();
+}
+
+// The keys of a sparse round's groups (sh.group) to their owners; ordered after
+// the streaming by a workgroup barrier.
+template <int T, int G, typename E>
+__device__ __forceinline__ void take_sparse(Cols<G, E>& cs, const Layout& lo, uint32_t ng, SharedSolve<T>& sh) {
+    if (lo.r != 0) return;
+    key_t<E>* sp = reinterpret_cast<key_t<E>*>(sh.sparse);
+    for (uint32_t i = 0; i < ng; ++i)
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+            if ((int)sh.group[i] == lo.c + k * lo.L)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    cs.best[k][j] = sp[4 * i + j];
+                    sp[4 * i + j] = key_none<E>();
+                }
+}
 
 struct SolveStats {
     unsigned long long rounds, settled, fallbacks, barriers;
@@ -61,6 +110,19 @@ __device__ __forceinline__ uint32_t owner_bit(const Layout& lo, int64_t v, int w
 }
 
 // ---------------------------------------------------------------------------
+// What cannot change the result is not read.  A row of a bucket at d can lower
+// only open vertices above d (above d + wmin, where a smallest weight is known:
+// compact copies), so a round reads no row once there is none, and only the column
+// groups that hold one when they are few against the rows (sparse_round).  (Masking
+// the other lanes in every round was slower: n=1024, one workgroup, cold caches,
+// 163 us against 155; the batches of rows, not their bytes, take the time.)  Where weights are small against
+// the vertices' degrees the last buckets hold most vertices and few are left:
+// n=65536, p=0.5, weights up to 1000 has 36152 of its 65536 rows in the last
+// bucket or the last but one (2.53 ms reading every row, 1.17 so).  `every_row` (a
+// solve that asks for one kernel by its flag: measurements of Algorithm 1's whole
+// loop) reads every row whole; so does literal mode.
+//
+// ---------------------------------------------------------------------------
 // One workgroup, whole row.
 //
 // A round settles the bucket, streams its rows (sh.list16), merges the row
@@ -75,7 +137,9 @@ __device__ __forceinline__ uint32_t owner_bit(const Layout& lo, int64_t v, int w
 template <int T, int G, int U, typename E>
 __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld, int32_t n, int32_t src,
                              int32_t* __restrict__ dist, int32_t* __restrict__ pred,
-                             bool literal, SharedSolve<T>& sh, SolveStats& st, Ctl* trace) {
+                             bool literal, bool every_row, uint32_t wmin, SharedSolve<T>& sh, SolveStats& st,
+                             Ctl* trace) {
+    every_row |= literal;
     const Layout lo = make_layout<T>(n);
     Cols<G, E> cs;
     init_cols(cs, lo, 0, n, src);
@@ -83,11 +147,15 @@ __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld
     if (threadIdx.x < 3) {
         sh.min3[threadIdx.x] = kNoKey;
         sh.count3[threadIdx.x] = 0;
+        sh.open3[threadIdx.x] = 0;
     }
+    if (threadIdx.x < 4 * kSparseGroups) sh.sparse[threadIdx.x] = kNoKey;
+    if (threadIdx.x == 0) sh.listed = 0;
     if (threadIdx.x == 0) sh.list16[0] = (uint16_t)src;
     __syncthreads();
     uint32_t d = 0, u0 = (uint32_t)src, M = 1;
     bool redo = false;  // the round repeats the last one as one literal step (zero-weight hazard)
+    uint32_t ng = ~0u;  // groups the round can lower
     uint32_t slot = 0;  // exchanges so far mod 3
     uint32_t neg = 0;
     uint32_t cand[G][4];
@@ -95,8 +163,19 @@ __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld
         const long long t_round = trace ? wall_clock64() : 0;
         const bool step = literal || redo;
         const uint32_t bucket = settle(cs, d, step, step ? owner_bit(lo, (int64_t)u0, n) : 0u);
-        stream_rows<G, U, E>(cs, lo, W, ld, 0, n, sh.list16, (int)M);
-        merge_partitions<T, G>(cs, lo, sh.mrg);
+        if (!step && sparse_round(ng, M, lo.P)) {
+            list_groups<T, G>(cs.x, d, wmin, lo, sh);
+            for (uint32_t i = 0; i < ng; ++i)
+                stream_sparse<T, E, false>(W, ld, 0, n, 4 * (int)sh.group[i], (int)M,
+                                           [&](int e) { return (uint32_t)sh.list16[e]; },
+                                           reinterpret_cast<key_t<E>*>(sh.sparse) + 4 * i);
+            __syncthreads();
+            if (threadIdx.x == 0) sh.listed = 0;
+            take_sparse<T, G, E>(cs, lo, ng, sh);
+        } else if (ng) {
+            stream_rows<G, U, E>(cs, lo, W, ld, 0, n, sh.list16, (int)M);
+            merge_partitions<T, G>(cs, lo, sh.mrg);
+        }
         if (!redo) {
             ++st.rounds;
             if (trace && threadIdx.x == 0 && st.rounds <= (unsigned long long)kTraceCap) {
@@ -105,7 +184,7 @@ __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld
             }
         }
         // the would-be state and its lowest (dist, vertex)
-        candidates(cs, d, cand, neg);
+        candidates(cs, d, ng != 0u, cand, neg);
         const bool owners = threadIdx.x < (unsigned)lo.L;  // whole waves, or the first lanes of wave 0
         if (threadIdx.x < (unsigned)max(lo.L, kWave)) {
             uint32_t dmin = 0xffffffffu;
@@ -127,13 +206,14 @@ __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld
         }
         __syncthreads();
         const uint64_t key = sh.min3[slot];
+        const uint32_t dn = scalar((uint32_t)(key >> 32));
         // the slot after the next one: its last readers passed the barrier before this one
         const uint32_t after = slot == 0 ? 2 : slot - 1;
         if (threadIdx.x == 0) {
             sh.min3[after] = kNoKey;
             sh.count3[after] = 0;
+            sh.open3[after] = 0;
         }
-        const uint32_t dn = (uint32_t)(key >> 32);
         if (!step && dn == d) {
             // zero-weight hazard: discard the fused round and settle only u0, the
             // bucket's lowest vertex (one literal step)
@@ -155,7 +235,7 @@ __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld
         st.settled += M;
         if (dn >= kInf) break;  // a4: nothing reachable is left
         d = dn;
-        u0 = (uint32_t)key;
+        u0 = scalar((uint32_t)key);
         // a2/a3: the next bucket
         if (literal) {
             M = 1;
@@ -163,6 +243,7 @@ __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld
             __syncthreads();
         } else {
             if (owners) {
+                if (!every_row) count_groups<T, G>(cs.x, d, wmin, slot, sh);
 #pragma unroll
                 for (int k = 0; k < G; ++k)
 #pragma unroll
@@ -179,7 +260,20 @@ __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld
                     }
             }
             __syncthreads();
-            M = sh.count3[slot];
+            M = scalar(sh.count3[slot]);
+            if (!every_row) {
+                ng = scalar(sh.open3[slot]);
+                if (ng == 0 && wmin == 0u) {
+                    // the last bucket: its rows have nothing left to lower
+                    ++st.rounds;
+                    st.settled += M;
+                    if (trace && threadIdx.x == 0 && st.rounds <= (unsigned long long)kTraceCap) {
+                        trace->trace_t[st.rounds - 1] = wall_clock64();
+                        trace->trace_m[st.rounds - 1] = M;
+                    }
+                    break;
+                }
+            }
         }
         slot = slot == 2 ? 0 : slot + 1;
     }
@@ -407,10 +501,10 @@ __device__ __forceinline__ uint64_t wait_tag(const uint64_t* p, uint64_t w, uint
 // The wave's part of read_records: lane l polls members l + 64 k, k < KM, and the
 // wave leaves the exchange's result in sh.res and the bucket in sh.list (staged)
 // or its counts and offsets in sh.cnt / sh.pre.
-template <int T, int G, int KM>
+template <int T, int G, bool NARROW, int KM>
 __device__ __forceinline__ void read_wave(uint64_t* recs, const uint64_t* __restrict__ rl, int S, int nwg,
                                           uint32_t tag, long long timeout, SharedSolve<T>& sh, const Pub* stamps,
-                                          uint64_t stamp) {
+                                          uint64_t stamp, const uint32_t (&cand)[G][4]) {
     const int l = wave_lane();  // not threadIdx.x: addresses hoisted out of the round loop would spill
     uint32_t late = sh.stage_late;
     // Every poll issues all of its loads before it checks any (member indexes
@@ -521,11 +615,14 @@ __device__ __forceinline__ void read_wave(uint64_t* recs, const uint64_t* __rest
         }
     }
     hazard = wave_mask(hazard != 0) ? 1u : 0u;
+    // the slice's owners are lanes of this wave: their groups the next round reads
+    const uint64_t open = NARROW ? wave_mask(group_open(cand[0], d, 0u)) : 0ull;
     if (l == kWave - 1) {  // one 16-byte store here, one load in every thread
         sh.res.d = d;
         sh.res.vert = low;
         sh.res.rows = inc;
         sh.res.flags = hazard | (small ? 2u : 0u) | (late << 2);
+        if (NARROW) sh.res_need = open;
     }
 }
 
@@ -552,24 +649,28 @@ __device__ __forceinline__ void read_wave(uint64_t* recs, const uint64_t* __rest
 template <int T, int G, bool NARROW>
 __device__ __forceinline__ bool read_records(uint64_t* recs, const uint64_t* __restrict__ rl, int S, int nwg,
                                              uint32_t tag, long long timeout, SharedSolve<T>& sh, uint32_t& d_out,
-                                             uint32_t& u_out, uint32_t& Z, uint32_t& M, bool& staged,
-                                             const Pub* stamps, uint64_t stamp) {
+                                             uint32_t& u_out, uint32_t& Z, uint32_t& M, bool& staged, uint64_t& open,
+                                             const Pub* stamps, uint64_t stamp, const uint32_t (&cand)[G][4]) {
     staged = false;
     if (NARROW || nwg <= 4 * kWave) {
         if (threadIdx.x < kWave) {
             // members 64 to 255 of a gang of at most 64 do not exist
-            if (nwg <= kWave) read_wave<T, G, 1>(recs, rl, S, nwg, tag, timeout, sh, stamps, stamp);
-            else read_wave<T, G, 4>(recs, rl, S, nwg, tag, timeout, sh, stamps, stamp);
+            if (nwg <= kWave) read_wave<T, G, NARROW, 1>(recs, rl, S, nwg, tag, timeout, sh, stamps, stamp, cand);
+            else read_wave<T, G, NARROW, 4>(recs, rl, S, nwg, tag, timeout, sh, stamps, stamp, cand);
         }
         __syncthreads();
         // the same in every thread: scalar registers
         const auto res = sh.res;
-        d_out = (uint32_t)__builtin_amdgcn_readfirstlane((int)res.d);
-        u_out = (uint32_t)__builtin_amdgcn_readfirstlane((int)res.vert);
-        M = (uint32_t)__builtin_amdgcn_readfirstlane((int)res.rows);
-        const uint32_t z = (uint32_t)__builtin_amdgcn_readfirstlane((int)res.flags);
+        d_out = scalar(res.d);
+        u_out = scalar(res.vert);
+        M = scalar(res.rows);
+        const uint32_t z = scalar(res.flags);
         Z = z & 1u;
         staged = (z & 2u) != 0;
+        if (NARROW) {
+            const uint64_t o = sh.res_need;
+            open = ((uint64_t)scalar((uint32_t)(o >> 32)) << 32) | scalar((uint32_t)o);
+        }
         return (z & 4u) == 0;
     }
     const uint32_t slot = (tag - 1) & 1;
@@ -668,11 +769,13 @@ __device__ __forceinline__ const uint64_t* entry_addr(const SharedSolve<T>& sh, 
 template <int T, int G, int U, typename E, bool NT = false, bool BAL = false, bool NARROW = false>
 __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, int32_t n, int32_t src,
                            int32_t* __restrict__ dist, int32_t* __restrict__ pred, bool literal,
-                           int S, int g, int nwg, long long timeout, GangWords gw, SharedSolve<T>& sh,
-                           SolveStats& st, Ctl* trace, uint32_t epoch, uint32_t b0 = 0) {
+                           bool every_row, uint32_t wmin, int S, int g, int nwg, long long timeout, GangWords gw,
+                           SharedSolve<T>& sh, SolveStats& st, Ctl* trace, uint32_t epoch, uint32_t b0 = 0) {
     static_assert(T == kCap, "one staged bucket entry per thread");
     static_assert(!BAL || sizeof(E) == 4, "pair balancing keeps 64-bit keys");
-    static_assert(!NARROW || G == 1, "narrow slices have one column group per lane");
+    static_assert(!NARROW || (G == 1 && sizeof(E) == 4), "narrow slices: one column group per lane of the caller's matrix");
+    if (sizeof(E) == 4) wmin = 0u;  // no smallest weight is known of the caller's matrix
+    every_row |= literal;
     const int64_t col0 = (int64_t)g * S;
     const int width = (int)max((int64_t)0, min((int64_t)S, (int64_t)n - col0));
     const Layout lo = make_layout<T>(S);
@@ -697,6 +800,9 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
     const uint64_t stamp1 = exchange_stamp((uint32_t)__builtin_amdgcn_readfirstlane((int)epoch), b0 + 1);
     const Pub* stamps1 = gw.pubs + (size_t)(b0 & 1) * nwg;
     if (threadIdx.x == 0) sh.stage_late = 0u;
+    if (threadIdx.x < 3) sh.open3[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) sh.listed = 0u;
+    if (threadIdx.x < 4 * kSparseGroups) sh.sparse[threadIdx.x] = kNoKey;
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -710,6 +816,10 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
     uint32_t d = 0, u0 = (uint32_t)src, M = 1;
     bool first = true;
     bool staged = false;  // the bucket is in sh.list already (read_records)
+    // groups of the slice that the round can lower, and (narrow slices) the lanes that
+    // own them
+    uint32_t ng = ~0u, slot3 = 0;
+    uint64_t open = ~0ull;
     bool redo = false;    // the round repeats the last one as one literal step (zero-weight hazard)
     uint32_t rounds = 0, settled = 0, fallbacks = 0, neg = 0;
     const bool tracer = trace && g == 0 && threadIdx.x == 0;
@@ -733,7 +843,50 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
             if (late) sh.stage_late = 1u;
         };
         const uint32_t C = (M + kCap - 1) / kCap;
-        if (paired && C >= kPairChunks) {
+        const bool sparse = !step && sparse_round(ng, M, lo.P);
+        if (paired && C >= kPairChunks && (ng == 0 || sparse)) {
+            // leave the partner none of this member's rows to claim
+            used |= 1u << (b & 1);
+            if (threadIdx.x == 0)
+                __hip_atomic_fetch_add(&gw.ctr[4 * g + (b & 1)], (M + kPairUnit - 1) / kPairUnit, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (ng == 0) {
+            // nothing in this slice can be lowered
+        } else if (sparse) {
+            auto row = [&](int e) -> uint32_t {
+                if (staged) return (uint32_t)sh.list[e];
+                const uint64_t* a = entry_addr<T>(sh, rl, nwg, S, (uint32_t)e);
+                uint32_t late = 0;
+                const uint64_t w = wait_tag(a, ld_agent(a), b, timeout, late);
+                if (late) sh.stage_late = 1u;
+                return late ? u0 : (uint32_t)w;
+            };
+            key_t<E>* sp = reinterpret_cast<key_t<E>*>(sh.sparse);
+            if (NARROW) {
+                uint32_t i = 0;
+                for (uint64_t o = open; o; o &= o - 1, ++i)
+                    stream_sparse<T, E, NT>(W, ld, col0, width, 4 * (int)__builtin_ctzll(o), (int)M, row, sp + 4 * i);
+            } else {
+                list_groups<T, G>(cs.x, d, wmin, lo, sh);
+                for (uint32_t i = 0; i < ng; ++i)
+                    stream_sparse<T, E, NT>(W, ld, col0, width, 4 * (int)sh.group[i], (int)M, row, sp + 4 * i);
+            }
+            __syncthreads();
+            if (NARROW) {
+                if (threadIdx.x < kWave && (open >> threadIdx.x & 1ull)) {
+                    const uint32_t i = lanes_below(open);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        cs.best[0][j] = sp[4 * i + j];
+                        sp[4 * i + j] = key_none<E>();
+                    }
+                }
+            } else {
+                if (threadIdx.x == 0) sh.listed = 0u;
+                take_sparse<T, G, E>(cs, lo, ng, sh);
+            }
+        } else if (paired && C >= kPairChunks) {
             const uint32_t slot = b & 1;
             const uint32_t tag = b + 1;  // the exchange this round publishes
             key_t<E>* keep = reinterpret_cast<key_t<E>*>(sh.mrg + 2 * T);
@@ -858,7 +1011,7 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
             }
         }
         // a single row went to partition 0, whose threads own the columns
-        if (M > 1) merge_partitions<T, G>(cs, lo, sh.mrg);
+        if (M > 1 && ng && !sparse) merge_partitions<T, G>(cs, lo, sh.mrg);
         if (tracer && !redo && rounds <= (uint32_t)kTraceCap) {
             trace->trace_t[rounds - 1] = t_round;
             trace->trace_m[rounds - 1] = M;
@@ -866,13 +1019,14 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
 
         // would-be state if this round is applied (threads that own no column have
         // x = 0xffffffff, so theirs is no candidate)
-        candidates(cs, d, cand, neg);
+        candidates(cs, d, ng != 0u, cand, neg);
         ++b;
         if (BAL) asm volatile("" ::"v"(reset_old));  // a counter reset has completed before this publish
         publish<T, G, NARROW>(cand, lo, col0, d, !step, !literal, b, gw.recs, nwg, g, list_of(b, g), sh);
         uint32_t Z, M_rec, d_next, u_next;
+        uint64_t open_next = 0;
         ok = read_records<T, G, NARROW>(gw.recs, literal ? nullptr : list_of(b, 0), S, nwg, b, timeout, sh, d_next,
-                                        u_next, Z, M_rec, staged, first ? stamps1 : nullptr, stamp1);
+                                        u_next, Z, M_rec, staged, open_next, first ? stamps1 : nullptr, stamp1, cand);
         first = false;
         if (!ok) break;
         if (BAL && (used >> ((b - 1) & 1) & 1u)) {
@@ -900,6 +1054,23 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
         if (d >= kInf) break;
         u0 = u_next;
         M = M_rec;
+        if (!every_row) {
+            if (NARROW) {
+                open = open_next;
+                ng = (uint32_t)__popcll(open);
+            } else if (8u * (uint64_t)((uint32_t)n - settled - M) < (uint32_t)n) {
+                // counted through LDS; not worth the barrier while an eighth of the
+                // vertices is open beyond the bucket
+                const uint32_t after = slot3 == 2 ? 0 : slot3 + 1;
+                if (threadIdx.x == 0) sh.open3[after] = 0u;
+                if (threadIdx.x < (unsigned)lo.L) count_groups<T, G>(cs.x, d, wmin, slot3, sh);
+                __syncthreads();
+                ng = scalar(sh.open3[slot3]);
+                slot3 = after;
+            } else {
+                ng = ~0u;
+            }
+        }
     }
     st.rounds += rounds;
     st.settled += settled;
