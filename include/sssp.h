@@ -172,9 +172,10 @@ int sssp_last_trace(void* stream, int64_t* t_ns, int32_t* rows, int32_t cap, int
 /*
  * Batched solve: `count` independent instances (host array of descriptors
  * pointing at device buffers; instances may share W) in ONE persistent launch
- * in which workgroups pull work from a ticket counter, largest instance first:
- * an instance with n <= sssp_batch_max_n() is solved by one workgroup, a
- * larger one by a gang of workgroups that split its columns.  With
+ * in which workgroups pull work from a ticket counter, largest instance first.
+ * Few instances are split over gangs of workgroups so that all run at once on the
+ * whole GPU; with more, an instance with n <= sssp_batch_max_n() is solved by one
+ * workgroup, a larger one by a gang of workgroups that split its columns.  With
  * SSSP_FLAG_LABEL_CORRECTING every instance whose matrix is not shared by 32
  * or more instances is solved with the label-correcting method (see that
  * flag) by a gang of 256-column slices.  Asynchronous.
@@ -196,7 +197,7 @@ int32_t sssp_batch_max_n(void);
  * keeps the fastest, and captures the launch into a hipGraph.  A launch
  * replays the graph on `stream`: one persistent kernel for all instances.
  * Instances of a matrix shared by 32 or more instances are solved by one
- * workgroup each, or, when that matrix has n <= 16384 and no off-diagonal
+ * workgroup each (split like the others where that is measured faster), or, when that matrix has n <= 16384 and no off-diagonal
  * weight below 1, in groups of `group_sources` sources run in lockstep by a
  * gang (shared-row relaxation: each round reads a row once for every source
  * of the group whose current bucket holds it; same dist/pred as alone); the
@@ -229,9 +230,8 @@ typedef struct sssp_plan_info {
     int32_t group_candidates;            /* instances whose matrix qualified for them */
 } sssp_plan_info;
 
-/* How a batched launch splits its instances (the item order and gang shapes of
- * sssp_dense_solve_batched / sssp_batch_plan_create for the given shape
- * parameters), computed on the host: it touches no device and reads none of the
+/* How a batched launch with the given shape parameters splits its instances (the
+ * item order and gang shapes), computed on the host: it touches no device and reads none of the
  * buffers, only checks the instances' arguments as those calls do.  Entry k of
  * out (count entries) is the k-th item of the launch: largest n first, then the
  * instances of a matrix shared by at least 32 of them (each solved by one

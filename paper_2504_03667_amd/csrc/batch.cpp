@@ -20,6 +20,7 @@ int set_error(int code, const char* msg);
 const char* last_error_text();
 int stream_ctl(hipStream_t stream, Ctl** out, int* cus, long long* clock_khz);
 int check_instance(const sssp_instance& I, int idx);
+int served_workgroups(int device);  // server.cpp
 }  // namespace sssp
 
 using namespace sssp;
@@ -60,6 +61,36 @@ struct Build {
 // rounds and start first; the shared ones fill the workgroups the gangs leave.
 constexpr int32_t kSharedSources = 32;
 
+// Members of the largest gang that a launch may use by its own choice.  A gang
+// waits for all of its members, and the launch is an ordinary one beside whatever
+// else runs: with live servers' kernels on `served` of the compute units and up to
+// four launches dispatched at a time (HIP's hardware queues), one of them holds at
+// least a quarter of the rest, so gangs of at most that many members always form.
+int32_t gang_cap(int32_t cus, int32_t served, int32_t nwg) {
+    return std::max(0, std::min((cus - served) / 4, nwg / 2));
+}
+
+// Columns per member (and largest n solved by one workgroup) that split a set of
+// instances so that all their workgroups run at once: the narrowest of 64 to 4096
+// whose parts, at most `cap` an instance, fit the nwg workgroups, or 0 when not even
+// 4096 does or gangs are not allowed (then the instances fill the GPU one workgroup
+// each).  A compute unit alone streams rows at 25 to 60 GB/s, so few instances on
+// one workgroup each leave most of the memory's 7 TB/s idle: 24 graphs of up to
+// 6000 vertices 2.6 ms, split 0.57.
+int32_t concurrent_columns(const sssp_instance* inst, int32_t count, int32_t nwg, int32_t cap) {
+    if (cap < 2) return 0;
+    for (int32_t c = 64; c <= 4096; c *= 2) {
+        int64_t parts = 0;
+        bool fits = true;
+        for (int32_t i = 0; i < count && parts <= nwg; ++i) {
+            parts += std::min<int64_t>(((int64_t)inst[i].n + c - 1) / c, cap);
+            fits = fits && (int64_t)inst[i].n <= (int64_t)cap * max_batch_slice();
+        }
+        if (fits && parts <= nwg) return c;
+    }
+    return 0;
+}
+
 // Columns per gang member of a label-correcting instance: its sweeps read 3-5
 // times the rows of a Dijkstra solve, so it is spread over many workgroups.
 constexpr int32_t kLcColumns = 256;
@@ -85,6 +116,8 @@ void group_shape(int32_t n, int32_t want, int32_t cols, int32_t* S, int32_t* par
 // with n > single_max_n is split into parts of at most gang_columns columns
 // solved by a gang of workgroups.  lc (may be null): per instance, solve it
 // with the label-correcting method (never for shared matrices).
+// split: instances of shared matrices are split like the others (when there are
+// not enough of them to fill the GPU by themselves).
 // group_k > 1 (with group_ok marking the eligible instances): instances of a
 // shared matrix are solved group_k at a time in lockstep by gangs of group_cols
 // columns per member (kMethodGroup items, queued between the other instances
@@ -92,14 +125,14 @@ void group_shape(int32_t n, int32_t want, int32_t cols, int32_t* S, int32_t* par
 int build(const sssp_instance* inst, const Source* src, int32_t count, int32_t single_max_n,
           int32_t gang_columns, int32_t max_parts, Build* out, const char* lc = nullptr,
           std::vector<int32_t>* order_out = nullptr, int32_t group_k = 0, int32_t group_cols = 0,
-          const char* group_ok = nullptr) {
+          const char* group_ok = nullptr, bool split = false) {
     std::vector<int32_t> order(count);
     for (int32_t i = 0; i < count; ++i) order[i] = i;
     std::map<std::pair<const void*, int64_t>, int32_t> uses;
     for (int32_t i = 0; i < count; ++i) ++uses[{src[i].W, src[i].ld}];
     std::vector<char> shared(count);
     for (int32_t i = 0; i < count; ++i)
-        shared[i] = uses[{src[i].W, src[i].ld}] >= kSharedSources && inst[i].n <= max_batch_single_n();
+        shared[i] = !split && uses[{src[i].W, src[i].ld}] >= kSharedSources && inst[i].n <= max_batch_single_n();
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
         if (shared[x] != shared[y]) return shared[x] < shared[y];
         return inst[x].n > inst[y].n;
@@ -301,8 +334,8 @@ struct sssp_batch_plan {
     int upload(int32_t single_max_n, int32_t gang_columns, int32_t group_k = 0, int32_t group_cols = 0) {
         Build b;
         int rc = ::build(inst.data(), src.data(), (int32_t)inst.size(), single_max_n, gang_columns,
-                         std::max(2, nwg / 2), &b, lc.empty() ? nullptr : lc.data(), nullptr, group_k, group_cols,
-                         group_ok.empty() ? nullptr : group_ok.data());
+                         split ? cap : std::max(2, nwg / 2), &b, lc.empty() ? nullptr : lc.data(), nullptr, group_k, group_cols,
+                         group_ok.empty() ? nullptr : group_ok.data(), split);
         if (rc) return rc;
         lc_items = 0;
         for (const BatchItem& it : b.items) lc_items += it.method == kMethodLabelCorrecting;
@@ -341,6 +374,8 @@ struct sssp_batch_plan {
 
     int32_t lc_items = 0;
     int32_t group_items = 0;
+    bool split = false;  // instances of shared matrices are split too (see build) ...
+    int32_t cap = 0;     // ... over gangs of at most this many members
 
     // Median-free timing of the uploaded configuration: best of 2 launches after a
     // warm-up (ms), or a negative value on a launch error (e set).
@@ -466,8 +501,16 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     Build b;
     std::vector<char> lc;
     if (flags & SSSP_FLAG_LABEL_CORRECTING) lc.assign(count, 1);
-    rc = build(inst, src.data(), count, max_batch_single_n(), 4096, std::max(2, nwg / 2), &b,
-               lc.empty() ? nullptr : lc.data());
+    // label-correcting instances have their own split; literal steps are an exchange
+    // each, which one workgroup does not need
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const int32_t cap = gang_cap(cus, served_workgroups(dev), nwg);
+    const int32_t cols = flags & (SSSP_FLAG_LABEL_CORRECTING | SSSP_FLAG_LITERAL)
+                             ? 0 : concurrent_columns(inst, count, nwg, cap);
+    rc = build(inst, src.data(), count, cols ? cols : max_batch_single_n(), cols ? cols : 4096,
+               cols ? cap : std::max(2, nwg / 2), &b,
+               lc.empty() ? nullptr : lc.data(), nullptr, 0, 0, nullptr, cols != 0);
     if (rc) return rc;
     nwg = std::max(1, std::min<int>(nwg, (int)b.parts.size()));
     if (nwg < b.max_parts) nwg = b.max_parts;
@@ -584,16 +627,23 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
     // with a given number of columns per member; measured, fastest kept
     struct Cand {
         int32_t single_max_n, gang_columns;
+        bool split;
     };
     std::vector<Cand> cands;
     int32_t nmax = 0;
     for (auto& I : p->inst) nmax = std::max(nmax, I.n);
     if (tuning && tuning->single_max_n > 0) {
-        cands.push_back(Cand{tuning->single_max_n, tuning->gang_columns > 0 ? tuning->gang_columns : 4096});
+        cands.push_back(Cand{tuning->single_max_n, tuning->gang_columns > 0 ? tuning->gang_columns : 4096, false});
     } else {
-        if (nmax <= max_batch_single_n()) cands.push_back(Cand{max_batch_single_n(), 4096});
+        if (nmax <= max_batch_single_n()) cands.push_back(Cand{max_batch_single_n(), 4096, false});
         for (int32_t c : {4096, 2048, 1024, 512, 256})
-            if (c < nmax) cands.push_back(Cand{c, c});
+            if (c < nmax) cands.push_back(Cand{c, c, false});
+        // every instance split (those of shared matrices too): where all run at once, and
+        // twice and four times as wide
+        p->cap = gang_cap(cus, 0, p->nwg);
+        if (const int32_t c0 = concurrent_columns(inst, count, p->nwg, p->cap))
+            for (int32_t c : {c0, 2 * c0, 4 * c0})
+                if (c <= 4096 && c < nmax) cands.push_back(Cand{c, c, true});
     }
     double best_ms = 1e30;
     Cand best = cands.front();
@@ -602,6 +652,7 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
         (void)hipEventCreate(&ev0);
         (void)hipEventCreate(&ev1);
         for (const Cand& c : cands) {
+            p->split = c.split;
             rc = p->upload(c.single_max_n, c.gang_columns);
             if (rc) continue;
             const float ms = p->time_launches(s, ev0, ev1, e);
@@ -618,6 +669,7 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
         }
         // label-correcting candidates: distinct matrices (not shared by many
         // instances) whose solve needs many rounds; kept if the launch is faster
+        p->split = best.split;
         rc = lc_candidates(p, s);
         if (rc) {
             (void)hipEventDestroy(ev0);
@@ -656,6 +708,7 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
             (void)hipEventCreate(&ev0);
             (void)hipEventCreate(&ev1);
             auto measure = [&](const GroupCand& g, float* ms) -> int {
+                p->split = false;  // groups are of shared matrices' instances
                 int r = p->upload(best.single_max_n, best.gang_columns, g.k, g.cols);
                 if (r) return r;
                 *ms = p->time_launches(s, ev0, ev1, e);
@@ -689,6 +742,7 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
             (void)hipEventDestroy(ev1);
         }
     }
+    p->split = best.split && gbest.k < 2;
     if (gbest.cols % 4 || (gbest.k && (gbest.cols < 512 || gbest.cols > 4096)))
         return fail(err(SSSP_EINVAL, "group_columns %d: a multiple of 4 in [512, 4096]", gbest.cols));
     rc = p->upload(best.single_max_n, best.gang_columns, gbest.k, gbest.cols);

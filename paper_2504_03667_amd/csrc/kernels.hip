@@ -97,11 +97,11 @@ __device__ __attribute__((noinline)) SolveStats single_variant(BatchItem I, bool
     return st;
 }
 
-template <int T, int G, typename E>
+template <int T, int G, typename E, bool NARROW = false>
 __device__ __attribute__((noinline)) SolveStats gang_variant(BatchItem I, int part, bool literal, long long timeout,
                                                              Bar* bw, char* arena, uint32_t epoch) {
     SolveStats st = {0, 0, 0, 0, 0};
-    solve_gang<T, G, rows_in_flight<E>(), E>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred,
+    solve_gang<T, G, rows_in_flight<E>(), E, false, false, NARROW>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred,
                                             literal, false, (uint32_t)I.wmin, I.S, part, I.parts, timeout,
                                             gang_words(arena + I.scratch_off, I.parts, I.S), g_sh<T>, st, nullptr, epoch);
     if (threadIdx.x == 0) gang_leave(bw, (uint32_t)I.parts);
@@ -187,6 +187,8 @@ template <int T, typename E>
 __device__ __forceinline__ SolveStats gang_by_size(const BatchItem& I, int part, bool literal, long long timeout,
                                                    Bar* bw, char* arena, uint32_t epoch) {
     const int groups = (I.S + 3) / 4;
+    if (groups <= kWave && I.parts <= 4 * kWave)
+        return gang_variant<T, 1, E, true>(I, part, literal, timeout, bw, arena, epoch);
     if (groups <= T) return gang_variant<T, 1, E>(I, part, literal, timeout, bw, arena, epoch);
     if (groups <= 2 * T) return gang_variant<T, 2, E>(I, part, literal, timeout, bw, arena, epoch);
     return gang_variant<T, 4, E>(I, part, literal, timeout, bw, arena, epoch);

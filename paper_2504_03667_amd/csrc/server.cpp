@@ -31,9 +31,17 @@
 #include "engine.h"
 #include "sssp_internal.h"
 
+namespace {
+// Workgroups of the live servers' kernels, per device.
+constexpr int kMaxDevices = 64;
+std::atomic<int> g_served[kMaxDevices];
+}  // namespace
+
 namespace sssp {
 int set_error(int code, const char* msg);  // api.cpp
-}
+
+int served_workgroups(int device) { return device >= 0 && device < kMaxDevices ? g_served[device].load() : 0; }
+}  // namespace sssp
 
 using namespace sssp;
 
@@ -229,6 +237,7 @@ struct sssp_server {
     sssp_server_config cfg{};
     hipStream_t stream = nullptr;
     int nwg = 0;
+    bool counted = false;  // its workgroups are in g_served
     long long clock_khz = 100000;
     // pinned host memory shared with the kernel
     ServeControl* ctl = nullptr;
@@ -471,6 +480,7 @@ int host_alloc(X** p, size_t count, const char* what) {
 }
 
 void release_all(sssp_server* s) {
+    if (s->counted) g_served[s->device] -= s->nwg;
     for (auto& g : s->graphs)
         if (g.owned) (void)hipFree(g.owned);
     if (s->stream) (void)hipStreamDestroy(s->stream);
@@ -546,6 +556,10 @@ int sssp_server_create(const sssp_server_config* cfg_in, sssp_server** out) {
     if (e != hipSuccess) return release_all(s), err(SSSP_EDEVICE, "hipStreamCreate: %s", hipGetErrorString(e));
     e = hipDeviceSynchronize();  // scratch initialised before the kernel starts
     if (e != hipSuccess) return release_all(s), err(SSSP_EDEVICE, "hipDeviceSynchronize: %s", hipGetErrorString(e));
+    if (s->device < kMaxDevices) {
+        g_served[s->device] += s->nwg;
+        s->counted = true;
+    }
     if (!s->launch()) return release_all(s), err(SSSP_EDEVICE, "launching the serving kernel failed");
     s->th = std::thread([s] { s->loop(); });
     *out = s;

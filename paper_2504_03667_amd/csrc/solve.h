@@ -503,7 +503,7 @@ __device__ __forceinline__ uint64_t wait_tag(const uint64_t* p, uint64_t w, uint
 // or its counts and offsets in sh.cnt / sh.pre.
 template <int T, int G, bool NARROW, int KM>
 __device__ __forceinline__ void read_wave(uint64_t* recs, const uint64_t* __restrict__ rl, int S, int nwg,
-                                          uint32_t tag, long long timeout, SharedSolve<T>& sh, const Pub* stamps,
+                                          uint32_t wmin, uint32_t tag, long long timeout, SharedSolve<T>& sh, const Pub* stamps,
                                           uint64_t stamp, const uint32_t (&cand)[G][4]) {
     const int l = wave_lane();  // not threadIdx.x: addresses hoisted out of the round loop would spill
     uint32_t late = sh.stage_late;
@@ -616,7 +616,7 @@ __device__ __forceinline__ void read_wave(uint64_t* recs, const uint64_t* __rest
     }
     hazard = wave_mask(hazard != 0) ? 1u : 0u;
     // the slice's owners are lanes of this wave: their groups the next round reads
-    const uint64_t open = NARROW ? wave_mask(group_open(cand[0], d, 0u)) : 0ull;
+    const uint64_t open = NARROW ? wave_mask(group_open(cand[0], d, wmin)) : 0ull;
     if (l == kWave - 1) {  // one 16-byte store here, one load in every thread
         sh.res.d = d;
         sh.res.vert = low;
@@ -648,15 +648,16 @@ __device__ __forceinline__ void read_wave(uint64_t* recs, const uint64_t* __rest
 // (sh.stage_late), did not arrive within `timeout` ticks.
 template <int T, int G, bool NARROW>
 __device__ __forceinline__ bool read_records(uint64_t* recs, const uint64_t* __restrict__ rl, int S, int nwg,
-                                             uint32_t tag, long long timeout, SharedSolve<T>& sh, uint32_t& d_out,
+                                             uint32_t wmin, uint32_t tag, long long timeout, SharedSolve<T>& sh,
+                                             uint32_t& d_out,
                                              uint32_t& u_out, uint32_t& Z, uint32_t& M, bool& staged, uint64_t& open,
                                              const Pub* stamps, uint64_t stamp, const uint32_t (&cand)[G][4]) {
     staged = false;
     if (NARROW || nwg <= 4 * kWave) {
         if (threadIdx.x < kWave) {
             // members 64 to 255 of a gang of at most 64 do not exist
-            if (nwg <= kWave) read_wave<T, G, NARROW, 1>(recs, rl, S, nwg, tag, timeout, sh, stamps, stamp, cand);
-            else read_wave<T, G, NARROW, 4>(recs, rl, S, nwg, tag, timeout, sh, stamps, stamp, cand);
+            if (nwg <= kWave) read_wave<T, G, NARROW, 1>(recs, rl, S, nwg, wmin, tag, timeout, sh, stamps, stamp, cand);
+            else read_wave<T, G, NARROW, 4>(recs, rl, S, nwg, wmin, tag, timeout, sh, stamps, stamp, cand);
         }
         __syncthreads();
         // the same in every thread: scalar registers
@@ -773,7 +774,7 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
                            SharedSolve<T>& sh, SolveStats& st, Ctl* trace, uint32_t epoch, uint32_t b0 = 0) {
     static_assert(T == kCap, "one staged bucket entry per thread");
     static_assert(!BAL || sizeof(E) == 4, "pair balancing keeps 64-bit keys");
-    static_assert(!NARROW || (G == 1 && sizeof(E) == 4), "narrow slices: one column group per lane of the caller's matrix");
+    static_assert(!NARROW || G == 1, "narrow slices have one column group per lane");
     if (sizeof(E) == 4) wmin = 0u;  // no smallest weight is known of the caller's matrix
     every_row |= literal;
     const int64_t col0 = (int64_t)g * S;
@@ -1025,7 +1026,7 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
         publish<T, G, NARROW>(cand, lo, col0, d, !step, !literal, b, gw.recs, nwg, g, list_of(b, g), sh);
         uint32_t Z, M_rec, d_next, u_next;
         uint64_t open_next = 0;
-        ok = read_records<T, G, NARROW>(gw.recs, literal ? nullptr : list_of(b, 0), S, nwg, b, timeout, sh, d_next,
+        ok = read_records<T, G, NARROW>(gw.recs, literal ? nullptr : list_of(b, 0), S, nwg, wmin, b, timeout, sh, d_next,
                                         u_next, Z, M_rec, staged, open_next, first ? stamps1 : nullptr, stamp1, cand);
         first = false;
         if (!ok) break;
