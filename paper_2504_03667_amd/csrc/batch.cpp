@@ -334,7 +334,7 @@ struct sssp_batch_plan {
     int upload(int32_t single_max_n, int32_t gang_columns, int32_t group_k = 0, int32_t group_cols = 0) {
         Build b;
         int rc = ::build(inst.data(), src.data(), (int32_t)inst.size(), single_max_n, gang_columns,
-                         split ? cap : std::max(2, nwg / 2), &b, lc.empty() ? nullptr : lc.data(), nullptr, group_k, group_cols,
+                         split ? gang_max : std::max(2, nwg / 2), &b, lc.empty() ? nullptr : lc.data(), nullptr, group_k, group_cols,
                          group_ok.empty() ? nullptr : group_ok.data(), split);
         if (rc) return rc;
         lc_items = 0;
@@ -374,8 +374,8 @@ struct sssp_batch_plan {
 
     int32_t lc_items = 0;
     int32_t group_items = 0;
-    bool split = false;  // instances of shared matrices are split too (see build) ...
-    int32_t cap = 0;     // ... over gangs of at most this many members
+    bool split = false;    // instances of shared matrices are split too (see build) ...
+    int32_t gang_max = 0;  // ... over gangs of at most this many members
 
     // Median-free timing of the uploaded configuration: best of 2 launches after a
     // warm-up (ms), or a negative value on a launch error (e set).
@@ -640,8 +640,8 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
             if (c < nmax) cands.push_back(Cand{c, c, false});
         // every instance split (those of shared matrices too): where all run at once, and
         // twice and four times as wide
-        p->cap = gang_cap(cus, 0, p->nwg);
-        if (const int32_t c0 = concurrent_columns(inst, count, p->nwg, p->cap))
+        p->gang_max = gang_cap(cus, 0, p->nwg);
+        if (const int32_t c0 = concurrent_columns(inst, count, p->nwg, p->gang_max))
             for (int32_t c : {c0, 2 * c0, 4 * c0})
                 if (c <= 4096 && c < nmax) cands.push_back(Cand{c, c, true});
     }
