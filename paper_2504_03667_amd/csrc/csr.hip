@@ -98,25 +98,43 @@ __device__ __forceinline__ bool keep_edge(int32_t u, int32_t v, int32_t w, int32
     return u >= 0 && u < n && v >= 0 && v < n && u != v && w >= 0 && w != (int32_t)kInf;
 }
 
+// Scratch of an edge list conversion (device memory).
+struct ConvertScratch {
+    unsigned long long* out;  // [0] edges left out, [1] entries of the lists
+    uint32_t* deg;            // per vertex: entries of its list
+    uint32_t* rank;           // per edge (undirected: then again for its other end): its place in the tail's list
+    uint32_t* cursor;         // per vertex: entries placed so far; only where rank is null
+    unsigned long long* sums; // per chunk of vertices: its entries
+};
+
+// Counts the lists' entries.  The count that an edge finds is its place in the
+// tail's list, kept for k_csr_fill: bound by the atomics, which are then done once
+// instead of again over cursors (see sssp_edges_to_csr for the figures).
 __global__ void k_csr_degree(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
                              const int32_t* __restrict__ ew, int64_t m, int32_t n, int32_t directed,
-                             uint32_t* __restrict__ deg, unsigned long long* __restrict__ bad) {
+                             ConvertScratch cs) {
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
         const int32_t u = eu[e], v = ev[e], w = ew[e];
         const bool self = u == v && u >= 0 && u < n && w >= 0 && w != (int32_t)kInf;
         if (!keep_edge(u, v, w, n)) {
-            if (!self) atomicAdd(bad, 1ull);  // a valid self-loop is ignored, not an error
+            if (!self) atomicAdd(&cs.out[0], 1ull);  // a valid self-loop is ignored, not an error
             continue;
         }
-        atomicAdd(&deg[u], 1u);
-        if (!directed) atomicAdd(&deg[v], 1u);
+        const uint32_t ru = atomicAdd(&cs.deg[u], 1u);
+        const uint32_t rv = directed ? 0u : atomicAdd(&cs.deg[v], 1u);
+        if (cs.rank) {
+            cs.rank[e] = ru;
+            if (!directed) cs.rank[m + e] = rv;
+        }
     }
 }
 
-// row_ptr[0] = 0, row_ptr[i + 1] = row_ptr[i] + deg[i], in three passes over
-// chunks of 1024 vertices: each chunk's total, an exclusive scan of the totals
-// (one workgroup), then each chunk's scan plus its offset.
+// row_ptr[0] = 0, row_ptr[i + 1] = row_ptr[i] + deg[i], in passes over chunks of
+// 1024 vertices: each chunk's total, then each chunk's scan plus its offset, the
+// sum of the totals before it.  With more than kScanDirect chunks one workgroup
+// scans the totals in between (each workgroup would read them all otherwise).
 constexpr int kScanChunk = 1024;
+constexpr int kScanDirect = 4096;
 
 // Inclusive scan of one value per thread over a workgroup of kScanChunk
 // threads; *total gets the workgroup's sum.
@@ -148,12 +166,10 @@ __global__ __launch_bounds__(kScanChunk) void k_csr_chunk_sums(const uint32_t* _
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-// Exclusive scan of the chunk totals in place; row_ptr[0] = 0.
-__global__ __launch_bounds__(kScanChunk) void k_csr_scan_sums(unsigned long long* __restrict__ sums, int32_t chunks,
-                                                              int64_t* __restrict__ row_ptr) {
+// Exclusive scan of the chunk totals in place.
+__global__ __launch_bounds__(kScanChunk) void k_csr_scan_sums(unsigned long long* __restrict__ sums, int32_t chunks) {
     __shared__ unsigned long long wsum[kScanChunk / 64];
     unsigned long long carry = 0;
-    if (threadIdx.x == 0) row_ptr[0] = 0;
     for (int32_t base = 0; base < chunks; base += kScanChunk) {
         const int32_t i = base + (int32_t)threadIdx.x;
         const unsigned long long x = i < chunks ? sums[i] : 0ull;
@@ -164,51 +180,133 @@ __global__ __launch_bounds__(kScanChunk) void k_csr_scan_sums(unsigned long long
     }
 }
 
+// direct: sums holds the totals, else their exclusive scan.  *entries = row_ptr[n].
 __global__ __launch_bounds__(kScanChunk) void k_csr_scan_chunks(const uint32_t* __restrict__ deg, int32_t n,
                                                                 const unsigned long long* __restrict__ sums,
-                                                                int64_t* __restrict__ row_ptr) {
+                                                                bool direct, int64_t* __restrict__ row_ptr,
+                                                                unsigned long long* __restrict__ entries) {
     __shared__ unsigned long long wsum[kScanChunk / 64];
+    unsigned long long total = 0, before = 0;
+    if (direct) {
+        unsigned long long x = 0;
+        for (uint32_t k = threadIdx.x; k < blockIdx.x; k += kScanChunk) x += sums[k];
+        (void)wg_inclusive_scan(x, wsum, &before);
+    } else {
+        before = sums[blockIdx.x];
+    }
     const int64_t i = (int64_t)blockIdx.x * kScanChunk + threadIdx.x;
-    unsigned long long total = 0;
     const unsigned long long incl = wg_inclusive_scan(i < n ? deg[i] : 0ull, wsum, &total);
-    if (i < n) row_ptr[i + 1] = (int64_t)(sums[blockIdx.x] + incl);
+    if (i < n) row_ptr[i + 1] = (int64_t)(before + incl);
+    if (i == 0) row_ptr[0] = 0;
+    if (i == n - 1) *entries = before + incl;
 }
 
 __global__ void k_csr_fill(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
                            const int32_t* __restrict__ ew, int64_t m, int32_t n, int32_t directed,
-                           const int64_t* __restrict__ row_ptr, uint32_t* __restrict__ cursor,
-                           int32_t* __restrict__ col, int32_t* __restrict__ w) {
+                           const int64_t* __restrict__ row_ptr, ConvertScratch cs, int32_t* __restrict__ col,
+                           int32_t* __restrict__ w) {
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
         const int32_t u = eu[e], v = ev[e], wt = ew[e];
         if (!keep_edge(u, v, wt, n)) continue;
-        int64_t p = row_ptr[u] + atomicAdd(&cursor[u], 1u);
+        int64_t p = row_ptr[u] + (cs.rank ? cs.rank[e] : atomicAdd(&cs.cursor[u], 1u));
         col[p] = v;
         w[p] = wt;
         if (!directed) {
-            p = row_ptr[v] + atomicAdd(&cursor[v], 1u);
+            p = row_ptr[v] + (cs.rank ? cs.rank[m + e] : atomicAdd(&cs.cursor[v], 1u));
             col[p] = u;
             w[p] = wt;
         }
     }
 }
 
-// Sort each row by (head, weight) so that the lists do not depend on the order
-// the atomics above took (one thread per row: the rows of the sparse graphs
-// this serves are short).
-__global__ void k_csr_sort_rows(const int64_t* __restrict__ row_ptr, int32_t n, int32_t* __restrict__ col,
-                                int32_t* __restrict__ w) {
-    for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) {
-        const int64_t a = row_ptr[u], b = row_ptr[u + 1];
-        for (int64_t i = a + 1; i < b; ++i) {
-            const int32_t cv = col[i], cw = w[i];
-            int64_t j = i - 1;
-            while (j >= a && (col[j] > cv || (col[j] == cv && w[j] > cw))) {
-                col[j + 1] = col[j];
-                w[j + 1] = w[j];
-                --j;
+__device__ __forceinline__ uint64_t entry_key(int32_t v, int32_t w) {  // both >= 0: compares as (head, weight)
+    return (uint64_t)(uint32_t)v << 32 | (uint32_t)w;
+}
+
+// Sorts col[0, len), w[0, len) by (head, weight); all lanes of a wave call it.
+// Bitonic merges whose every exchange puts the smaller entry first, so entries
+// beyond len, thought of as largest, never move and need not exist.
+__device__ void sort_long_row(int32_t* col, int32_t* w, int64_t len) {
+    for (int64_t k = 2; k < 2 * len; k <<= 1) {
+        for (int64_t j = k >> 1; j > 0; j >>= 1) {
+            const bool flip = j == k >> 1;  // the first exchange of a merge mirrors its second half
+            for (int64_t p = wave_lane(); p < len; p += kWave) {
+                const int64_t in = p & (j - 1), lo = 2 * (p - in) + in;
+                const int64_t hi = flip ? lo + 2 * (j - in) - 1 : lo + j;
+                if (hi >= len) continue;
+                const int32_t cl = col[lo], ch = col[hi], wl = w[lo], wh = w[hi];
+                if (entry_key(cl, wl) > entry_key(ch, wh)) {
+                    col[lo] = ch;
+                    col[hi] = cl;
+                    w[lo] = wh;
+                    w[hi] = wl;
+                }
             }
-            col[j + 1] = cv;
-            w[j + 1] = cw;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // the wave's stores before its next loads
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+}
+
+// Sort each row by (head, weight) so that the lists do not depend on the order
+// the atomics above took.  A wave takes eight rows: eight lanes count for each
+// entry of a row of up to 8 how many precede it and store it there, rows of up to
+// 64 are taken the same way by the whole wave one after the other, longer ones are
+// sorted in place.  Bound by the latency of one load and one store a row, where a
+// thread a row moved entries one by one through memory (see sssp_edges_to_csr).
+__global__ __launch_bounds__(256) void k_csr_sort_rows(const int64_t* __restrict__ row_ptr, int32_t n, int32_t* col,
+                                                       int32_t* w) {
+    constexpr int kLanes = 8;
+    const int lane = wave_lane();
+    const int sub = lane % kLanes;
+    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    const int64_t waves = (int64_t)gridDim.x * blockDim.x / kWave;
+    for (int64_t u0 = wave * (kWave / kLanes); u0 < n; u0 += waves * (kWave / kLanes)) {
+        const int64_t u = u0 + lane / kLanes;
+        int64_t a = 0, len = 0;
+        if (u < n) {
+            a = row_ptr[u];
+            len = row_ptr[u + 1] - a;
+        }
+        const bool mine = len <= kLanes && sub < len;
+        int32_t c = 0, x = 0;
+        if (mine) {
+            c = col[a + sub];
+            x = w[a + sub];
+        }
+        uint32_t pos = 0;
+#pragma unroll
+        for (int j = 0; j < kLanes; ++j) {
+            const uint64_t other = entry_key(__shfl(c, j, kLanes), __shfl(x, j, kLanes));
+            const uint64_t key = entry_key(c, x);
+            pos += j < len && (other < key || (other == key && j < sub)) ? 1u : 0u;
+        }
+        if (mine) {
+            col[a + pos] = c;
+            w[a + pos] = x;
+        }
+        for (uint64_t rest = __ballot(sub == 0 && len > kLanes); rest; rest &= rest - 1) {
+            const int64_t v = u0 + (__ffsll((unsigned long long)rest) - 1) / kLanes;
+            const int64_t av = row_ptr[v], lv = row_ptr[v + 1] - av;
+            if (lv > kWave) {
+                sort_long_row(col + av, w + av, lv);
+                continue;
+            }
+            c = x = 0;
+            if (lane < lv) {
+                c = col[av + lane];
+                x = w[av + lane];
+            }
+            const uint64_t key = entry_key(c, x);
+            pos = 0;
+            for (int j = 0; j < (int)lv; ++j) {
+                const uint64_t other = entry_key(__builtin_amdgcn_readlane(c, j), __builtin_amdgcn_readlane(x, j));
+                pos += other < key || (other == key && j < lane) ? 1u : 0u;
+            }
+            if (lane < lv) {
+                col[av + pos] = c;
+                w[av + pos] = x;
+            }
         }
     }
 }
@@ -960,53 +1058,65 @@ int sssp_csr_grid(int32_t n, const sssp_tuning* tuning, void* stream, int32_t* w
     return SSSP_OK;
 }
 
+// Six launches and one copy back.  Against cursor atomics, a thread a row in the
+// sort, seven launches and two copies: n=10000, m=3n, undirected 156 -> 85 us, 40000
+// 165 -> 95 (sort 32 -> 9, fill 14 -> 8), 10^6 860 -> 660 (degrees 241 and fill 224,
+// bound by scattered atomics and stores, sort 70); n=200000, m=16n 2660 -> 681.
 int sssp_edges_to_csr(const int32_t* eu, const int32_t* ev, const int32_t* ew, int64_t m, int32_t n,
                       int32_t directed, int64_t* row_ptr, int32_t* col, int32_t* w, int64_t* m_out,
                       int64_t* bad_edges, void* stream) {
     if (!row_ptr || n < 1 || m < 0 || (m > 0 && (!eu || !ev || !ew || !col || !w)))
         return err(SSSP_EINVAL, "bad arguments (n=%d m=%lld)", n, (long long)m);
     hipStream_t s = (hipStream_t)stream;
-    // scratch: degrees, then cursors (n words each), the bad-edge counter and the
-    // per-chunk totals of the scan
+    // scratch: the two counts and the degrees, which start at zero, the totals of the
+    // scan's chunks, then each edge's places; where that is too much, cursors instead
     const int32_t chunks = (int32_t)(((int64_t)n + kScanChunk - 1) / kScanChunk);
+    const size_t head = sizeof(unsigned long long) * (2 + (size_t)chunks), per_n = sizeof(uint32_t) * (size_t)n;
+    const size_t ranks = sizeof(uint32_t) * (directed ? 1 : 2) * (size_t)m;
     char* buf = nullptr;
-    const size_t bytes = 2 * sizeof(uint32_t) * (size_t)n + sizeof(unsigned long long) * (1 + (size_t)chunks);
-    hipError_t e = hipMallocAsync((void**)&buf, bytes, s);
+    bool ranked = true;
+    hipError_t e = hipMallocAsync((void**)&buf, head + per_n + ranks, s);
+    if (e != hipSuccess && ranks > per_n) {
+        (void)hipGetLastError();
+        ranked = false;
+        e = hipMallocAsync((void**)&buf, head + 2 * per_n, s);
+    }
     if (e != hipSuccess) return err(SSSP_ENOMEM, "hipMallocAsync: %s", hipGetErrorString(e));
-    uint32_t* deg = reinterpret_cast<uint32_t*>(buf);
-    uint32_t* cursor = deg + n;
-    unsigned long long* bad = reinterpret_cast<unsigned long long*>(cursor + n);
-    unsigned long long* sums = bad + 1;
-    e = zero_fill(buf, (bytes + 3) & ~size_t(3), s);
+    ConvertScratch cs{};
+    cs.sums = reinterpret_cast<unsigned long long*>(buf);
+    cs.out = cs.sums + chunks;
+    cs.deg = reinterpret_cast<uint32_t*>(cs.out + 2);
+    (ranked ? cs.rank : cs.cursor) = cs.deg + n;
+    e = zero_fill(cs.out, 2 * sizeof(unsigned long long) + (ranked ? per_n : 2 * per_n), s);
     const unsigned eb = (unsigned)std::min<int64_t>(std::max<int64_t>(1, (m + 255) / 256), 8192);
-    const unsigned nb = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
+    const unsigned nb = (unsigned)std::min<int64_t>(((int64_t)n + 31) / 32, 8192);
     if (e == hipSuccess && m > 0) {
-        hipLaunchKernelGGL(k_csr_degree, dim3(eb), dim3(256), 0, s, eu, ev, ew, m, n, directed, deg, bad);
+        hipLaunchKernelGGL(k_csr_degree, dim3(eb), dim3(256), 0, s, eu, ev, ew, m, n, directed, cs);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_csr_chunk_sums, dim3(chunks), dim3(kScanChunk), 0, s, deg, n, sums);
-        hipLaunchKernelGGL(k_csr_scan_sums, dim3(1), dim3(kScanChunk), 0, s, sums, chunks, row_ptr);
-        hipLaunchKernelGGL(k_csr_scan_chunks, dim3(chunks), dim3(kScanChunk), 0, s, deg, n, sums, row_ptr);
+        const bool direct = chunks <= kScanDirect;
+        hipLaunchKernelGGL(k_csr_chunk_sums, dim3(chunks), dim3(kScanChunk), 0, s, cs.deg, n, cs.sums);
+        if (!direct) hipLaunchKernelGGL(k_csr_scan_sums, dim3(1), dim3(kScanChunk), 0, s, cs.sums, chunks);
+        hipLaunchKernelGGL(k_csr_scan_chunks, dim3(chunks), dim3(kScanChunk), 0, s, cs.deg, n, cs.sums, direct, row_ptr,
+                           cs.out + 1);
         e = hipGetLastError();
     }
     if (e == hipSuccess && m > 0) {
-        hipLaunchKernelGGL(k_csr_fill, dim3(eb), dim3(256), 0, s, eu, ev, ew, m, n, directed, row_ptr, cursor, col, w);
+        hipLaunchKernelGGL(k_csr_fill, dim3(eb), dim3(256), 0, s, eu, ev, ew, m, n, directed, row_ptr, cs, col, w);
         e = hipGetLastError();
     }
     if (e == hipSuccess && m > 0) {
         hipLaunchKernelGGL(k_csr_sort_rows, dim3(nb), dim3(256), 0, s, row_ptr, n, col, w);
         e = hipGetLastError();
     }
-    int64_t total = 0;
-    unsigned long long nbad = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&total, row_ptr + n, sizeof total, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&nbad, bad, sizeof nbad, hipMemcpyDeviceToHost, s);
+    unsigned long long out[2] = {0, 0};
+    if (e == hipSuccess) e = hipMemcpyAsync(out, cs.out, sizeof out, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFreeAsync(buf, s);
     if (e != hipSuccess) return err(SSSP_EDEVICE, "edge list conversion: %s", hipGetErrorString(e));
-    if (m_out) *m_out = total;
-    if (bad_edges) *bad_edges = (int64_t)nbad;
+    if (m_out) *m_out = (int64_t)out[1];
+    if (bad_edges) *bad_edges = (int64_t)out[0];
     return SSSP_OK;
 }
 

@@ -1,0 +1,61 @@
+"""GPU tests of the edge list conversion to adjacency lists at the sizes where its paths
+change: lists sorted by eight lanes, by a wave, in place, and the prefix sums' two
+forms."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+INF = 2 ** 31 - 1
+
+
+@pytest.fixture(scope="module")
+def sp():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2504_03667_amd as m
+    m.lib()
+    return m
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a).astype(np.int32)).cuda()
+
+
+def lists(eu, ev, ew, n, directed):
+    """(row_ptr, col, w): lists sorted by (head, weight), without self-loops."""
+    if not directed:
+        eu, ev, ew = np.concatenate([eu, ev]), np.concatenate([ev, eu]), np.concatenate([ew, ew])
+    keep = eu != ev
+    eu, ev, ew = eu[keep], ev[keep], ew[keep]
+    order = np.lexsort((ew, ev, eu))
+    return np.concatenate([[0], np.cumsum(np.bincount(eu, minlength=n))]), ev[order], ew[order]
+
+
+def check_lists(sp, eu, ev, ew, n, directed):
+    got = sp.csr_from_edges(dev(eu), dev(ev), dev(ew), n, directed)
+    assert got[3] == 0
+    for a, b in zip(got[:3], lists(eu, ev, ew, n, directed)):
+        assert a.numel() == max(1, b.size)  # empty lists: one entry without meaning
+        assert np.array_equal(a.cpu().numpy()[:b.size], b)
+
+
+@pytest.mark.parametrize("directed", [True, False])
+def test_lists_of_every_length(sp, directed):
+    """Lists of 0 to 70 entries side by side, then 128, 129, 1000, 5000; heads repeat."""
+    rng = np.random.default_rng(7)
+    lens = np.concatenate([rng.permutation(71), [128, 129, 1000, 5000, 1, 8, 9, 64, 65, 0, 3]])
+    n = lens.size
+    eu = rng.permutation(np.repeat(np.arange(n), lens))
+    ev = rng.integers(0, n, size=eu.size)
+    check_lists(sp, eu, ev, rng.integers(0, 5, size=eu.size), n, directed)
+
+
+@pytest.mark.parametrize("n", [1, 2, 7, 31, 1023, 1024, 1025, 4096 * 1024, 4096 * 1024 + 1])
+def test_lists_of_many_vertices(sp, n):
+    rng = np.random.default_rng(n)
+    eu, ev = rng.integers(0, n, size=(2, 4000))
+    eu[:9], ev[9:20] = n - 1, n - 1
+    check_lists(sp, eu, ev, rng.integers(0, INF, size=eu.size), n, False)
