@@ -53,29 +53,56 @@ __global__ void k_scatter_edges(const int32_t* __restrict__ eu, const int32_t* _
     }
 }
 
-// Pointer jumping over the pred forest: after the last step hops[v] is the
+// Pointer jumping over the pred forest: after the last pass hops[v] is the
 // number of edges on v's pred chain to the source (0 at the source, -1 when v
-// is unreachable).  a/b hold (ancestor, hops so far) and are double-buffered.
-__global__ void k_hops_init(const int32_t* __restrict__ pred, const int32_t* __restrict__ dist, int32_t n,
-                            int32_t* __restrict__ anc, int32_t* __restrict__ hop) {
+// is unreachable).  A word holds (ancestor, hops so far).
+struct Jump {
+    int32_t anc, hop;
+};
+
+__device__ __forceinline__ Jump jump_start(const int32_t* __restrict__ pred, const int32_t* __restrict__ dist,
+                                           int32_t v) {
+    const int32_t p = pred[v];
+    const bool reach = dist[v] != kInf;
+    return Jump{reach ? p : -1, reach ? (p >= 0 ? 1 : 0) : -1};
+}
+
+// Each pass follows 2^log2_links links of the one before (of pred, in the first).
+// Bound by launches and, in a pass, by the chain of reads: passes of one doubling
+// took 4.7 us each at n=40000, 18 of them, though few chains of shortest path trees
+// go beyond the first 32 links; now 8 us, then 3 passes of 4.
+__global__ void k_hops_first(const int32_t* __restrict__ pred, const int32_t* __restrict__ dist, int32_t n,
+                             int32_t log2_links, Jump* __restrict__ out) {
     for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        const bool reach = dist[v] != kInf;
-        anc[v] = reach ? pred[v] : -1;
-        hop[v] = reach ? (pred[v] >= 0 ? 1 : 0) : -1;
+        Jump x = jump_start(pred, dist, v);
+        for (int32_t k = 1; k < 1 << log2_links && x.anc >= 0 && x.anc < n; ++k) {
+            const Jump y = jump_start(pred, dist, x.anc);
+            x = Jump{y.anc, (int32_t)((uint32_t)x.hop + (uint32_t)y.hop)};
+        }
+        out[v] = x;
     }
 }
 
-__global__ void k_hops_step(const int32_t* __restrict__ anc_in, const int32_t* __restrict__ hop_in, int32_t n,
-                            int32_t* __restrict__ anc_out, int32_t* __restrict__ hop_out) {
+// Passes of four doublings read each word's chain twice as often as two of two
+// would; on large graphs of deep trees (chains longer than 32) that counts for more
+// than launches.
+constexpr int kHopsFirst = 5;
+constexpr int kHopsStep = 4, kHopsStepWide = 2;
+constexpr int32_t kHopsWideN = 131072;
+
+// hops (if given) takes the result instead of out.
+__global__ void k_hops_step(const Jump* __restrict__ in, int32_t n, int32_t log2_links, Jump* __restrict__ out,
+                            int32_t* __restrict__ hops) {
     for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        const int32_t a = anc_in[v];
-        if (a >= 0 && a < n) {
-            anc_out[v] = anc_in[a];
-            hop_out[v] = hop_in[v] + hop_in[a];
-        } else {
-            anc_out[v] = a;
-            hop_out[v] = hop_in[v];
+        Jump x = in[v];
+        for (int32_t k = 1; k < 1 << log2_links && x.anc >= 0 && x.anc < n; ++k) {
+            const Jump y = in[x.anc];
+            x = Jump{y.anc, (int32_t)((uint32_t)x.hop + (uint32_t)y.hop)};
         }
+        if (hops)
+            hops[v] = x.hop;
+        else
+            out[v] = x;
     }
 }
 
@@ -132,30 +159,26 @@ int sssp_edges_to_dense(const int32_t* eu, const int32_t* ev, const int32_t* ew,
 int sssp_hops(const int32_t* pred, const int32_t* dist, int32_t n, int32_t* hops, void* stream) {
     if (!pred || !dist || !hops || n < 1) return err(SSSP_EINVAL, "bad arguments");
     hipStream_t s = (hipStream_t)stream;
-    int32_t* buf = nullptr;
-    hipError_t e = hipMallocAsync((void**)&buf, 3 * sizeof(int32_t) * (size_t)n, s);
+    Jump* buf = nullptr;
+    hipError_t e = hipMallocAsync((void**)&buf, 2 * sizeof(Jump) * (size_t)n, s);
     if (e != hipSuccess) return err(SSSP_ENOMEM, "hipMallocAsync: %s", hipGetErrorString(e));
-    int32_t* a0 = buf;
-    int32_t* a1 = buf + n;
-    int32_t* h1 = buf + 2 * (size_t)n;
     const unsigned blocks = (unsigned)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-    hipLaunchKernelGGL(k_hops_init, dim3(blocks), dim3(256), 0, s, pred, dist, n, a0, hops);
     // ceil(log2 n) + 1 doublings reach the root of every chain
-    int steps = 1;
-    while ((1ll << (steps - 1)) < n) ++steps;
-    int32_t *ai = a0, *hi = hops, *ao = a1, *ho = h1;
-    for (int k = 0; k < steps; ++k) {
-        hipLaunchKernelGGL(k_hops_step, dim3(blocks), dim3(256), 0, s, ai, hi, n, ao, ho);
-        int32_t* t = ai;
-        ai = ao;
-        ao = t;
-        t = hi;
-        hi = ho;
-        ho = t;
+    int left = 1;
+    while ((1ll << (left - 1)) < n) ++left;
+    // the first pass leaves the last one something: that writes hops, and hops may be pred
+    int now = left > kHopsFirst ? kHopsFirst : left - 1;
+    hipLaunchKernelGGL(k_hops_first, dim3(blocks), dim3(256), 0, s, pred, dist, n, now, buf);
+    Jump *in = buf, *out = buf + n;
+    const int each = n < kHopsWideN ? kHopsStep : kHopsStepWide;
+    while ((left -= now) > 0) {
+        now = left < each ? left : each;
+        hipLaunchKernelGGL(k_hops_step, dim3(blocks), dim3(256), 0, s, in, n, now, out, left == now ? hops : nullptr);
+        Jump* t = in;
+        in = out;
+        out = t;
     }
     e = hipGetLastError();
-    if (e == hipSuccess && hi != hops) e = hipMemcpyAsync(hops, hi, sizeof(int32_t) * (size_t)n,
-                                                          hipMemcpyDeviceToDevice, s);
     (void)hipFreeAsync(buf, s);
     if (e != hipSuccess) return err(SSSP_EDEVICE, "hops: %s", hipGetErrorString(e));
     return SSSP_OK;

@@ -1,6 +1,6 @@
-"""GPU tests of the edge list conversion to adjacency lists at the sizes where its paths
-change: lists sorted by eight lanes, by a wave, in place, and the prefix sums' two
-forms."""
+"""GPU tests of edge list conversion and hop counts at the sizes where their paths change:
+adjacency lists sorted by eight lanes, by a wave, in place, and by the prefix sums' two
+forms; pred chains beyond what one pass of the hop count follows."""
 import numpy as np
 import pytest
 
@@ -59,3 +59,29 @@ def test_lists_of_many_vertices(sp, n):
     eu, ev = rng.integers(0, n, size=(2, 4000))
     eu[:9], ev[9:20] = n - 1, n - 1
     check_lists(sp, eu, ev, rng.integers(0, INF, size=eu.size), n, False)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 65, 1000, 131071, 131072, 131073])
+@pytest.mark.parametrize("depth", ["chain", "random"])
+def test_hops(sp, n, depth):
+    """Chains through all vertices in random order, and random trees; the last vertex of
+    three or more is unreachable.  hops may take pred's place."""
+    rng = np.random.default_rng(n)
+    order = rng.permutation(n)
+    reach = n - 1 if n > 2 else n
+    before = np.arange(-1, reach - 1)
+    if depth == "random":
+        before = np.concatenate([[-1], (rng.random(reach - 1) * np.arange(1, reach)).astype(int)])
+    pred, dist, hops = np.full(n, -1), np.full(n, INF), np.full(n, -1)
+    count = np.zeros(reach, int)
+    for i in range(1, reach):
+        count[i] = count[before[i]] + 1
+    pred[order[1:reach]] = order[before[1:]]
+    dist[order[:reach]] = 3 * count
+    hops[order[:reach]] = count
+    p, d = dev(pred), dev(dist)
+    out = torch.full((n,), 99, dtype=torch.int32, device="cuda")
+    sp.sssp_hops(p, d, out)
+    assert np.array_equal(out.cpu().numpy(), hops)
+    sp.sssp_hops(p, d, p)
+    assert np.array_equal(p.cpu().numpy(), hops)
