@@ -27,11 +27,46 @@ int err(int code, const char* fmt, ...) {
     return sssp::set_error(code, buf);
 }
 
-// W[i][j] = 0 on the diagonal, INT32_MAX (no edge) elsewhere.
-__global__ void k_fill_empty(int32_t* __restrict__ W, int64_t ld, int32_t n) {
-    for (int64_t i = blockIdx.y; i < n; i += gridDim.y)
-        for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x)
-            W[i * ld + j] = i == j ? 0 : kInf;
+// W[i][j] = 0 on the diagonal, INT32_MAX (no edge) elsewhere; *bad = 0.  Bound by
+// the writes: a workgroup takes one segment of a row, kFillSeg entries that start on
+// a cache line whatever the row's alignment, as 16-byte stores (entries outside the
+// row are left alone: there may be gaps between rows).  4-byte stores of a thread an entry
+// took 232 us of a call's 291 at n=16000 (4.4 TB/s) and no less than 318 at n=16001;
+// now 245 and 247 us a call, 1257 -> 1203 at n=40000 (5.5 TB/s).  Grids of 1024 to
+// 8192 workgroups that loop took 263 to 285 us and, at n=16001, 315 to 372.
+constexpr int kFillThreads = 256;
+constexpr int kFillSeg = 4096;
+constexpr int kLineEntries = 32;
+constexpr int64_t kStreamBytes = 256ll << 20;  // what the memory-side cache holds
+
+typedef int32_t quad __attribute__((ext_vector_type(4)));
+
+template <bool Stream>
+__global__ __launch_bounds__(kFillThreads) void k_fill_empty(int32_t* __restrict__ W, int64_t ld, int32_t n,
+                                                             int32_t segs, unsigned long long* __restrict__ bad) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *bad = 0;
+    for (int64_t t = blockIdx.x; t < (int64_t)segs * n; t += gridDim.x) {
+        const int64_t i = t / segs;
+        int32_t* row = W + i * ld;
+        const int64_t off = ((uintptr_t)row >> 2) & (kLineEntries - 1);
+        const int64_t j0 = (t - i * segs) * kFillSeg - off, j1 = j0 + kFillSeg < n ? j0 + kFillSeg : n;
+        for (int64_t j = j0 + 4 * (int64_t)threadIdx.x; j < j1; j += 4 * kFillThreads) {
+            quad v;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = j + c == i ? 0 : kInf;
+            if (j >= 0 && j + 4 <= n) {
+                quad* q = reinterpret_cast<quad*>(row + j);
+                if (Stream)
+                    __builtin_nontemporal_store(v, q);
+                else
+                    *q = v;
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (j + c >= 0 && j + c < n) row[j + c] = v[c];
+            }
+        }
+    }
 }
 
 // Scatter the edges with an atomic minimum, so a duplicated edge keeps its
@@ -135,12 +170,15 @@ int sssp_edges_to_dense(const int32_t* eu, const int32_t* ev, const int32_t* ew,
     unsigned long long* d_bad = nullptr;
     hipError_t e = hipMallocAsync((void**)&d_bad, sizeof(unsigned long long), s);
     if (e != hipSuccess) return err(SSSP_ENOMEM, "hipMallocAsync: %s", hipGetErrorString(e));
-    e = hipMemsetAsync(d_bad, 0, sizeof(unsigned long long), s);
-    dim3 fg((unsigned)((n + 255) / 256 < 64 ? (n + 255) / 256 : 64), (unsigned)(n < 65535 ? n : 65535));
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_fill_empty, fg, dim3(256), 0, s, W, ld, n);
-        e = hipGetLastError();
-    }
+    const int32_t segs = (int32_t)(((int64_t)n + kLineEntries - 1 + kFillSeg - 1) / kFillSeg);
+    const int64_t all = (int64_t)n * segs;
+    // a matrix larger than the memory-side cache streams past it (n=16001 247 us
+    // against 271; n=4000, which stays in it, 66 us against 58)
+    const bool stream_past = (int64_t)n * n * (int64_t)sizeof(int32_t) > kStreamBytes;
+    hipLaunchKernelGGL(stream_past ? k_fill_empty<true> : k_fill_empty<false>,
+                       dim3((unsigned)(all < 0x7fffff ? all : 0x7fffff)), dim3(kFillThreads), 0, s, W, ld, n, segs,
+                       d_bad);
+    e = hipGetLastError();
     if (e == hipSuccess && m > 0) {
         const int64_t blocks = (m + 255) / 256 < 8192 ? (m + 255) / 256 : 8192;
         hipLaunchKernelGGL(k_scatter_edges, dim3((unsigned)blocks), dim3(256), 0, s, eu, ev, ew, m, n, directed, W, ld,

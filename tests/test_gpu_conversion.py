@@ -1,6 +1,7 @@
-"""GPU tests of edge list conversion and hop counts at the sizes where their paths change:
+"""GPU tests of edge list conversions and hop counts at the sizes where their paths change:
 adjacency lists sorted by eight lanes, by a wave, in place, and by the prefix sums' two
-forms; pred chains beyond what one pass of the hop count follows."""
+forms; the dense matrix at every alignment of rows, with what lies between rows left
+alone; pred chains beyond what one pass of the hop count follows."""
 import numpy as np
 import pytest
 
@@ -59,6 +60,27 @@ def test_lists_of_many_vertices(sp, n):
     eu, ev = rng.integers(0, n, size=(2, 4000))
     eu[:9], ev[9:20] = n - 1, n - 1
     check_lists(sp, eu, ev, rng.integers(0, INF, size=eu.size), n, False)
+
+
+@pytest.mark.parametrize("n, ld", [(1, 1), (1, 5), (2, 3), (5, 5), (5, 8), (63, 65), (1023, 1023), (1025, 1026),
+                                   (4096, 4096), (4097, 4097), (4099, 4103)])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_dense_rows_at_any_alignment(sp, n, ld, shift):
+    rng = np.random.default_rng(n)
+    eu, ev = rng.integers(0, n, size=(2, 3 * n))
+    ew = rng.integers(0, 100, size=3 * n)
+    buf = torch.full((n * ld + 8,), -7, dtype=torch.int32, device="cuda")
+    W = buf[shift:shift + n * ld]
+    assert sp.sssp_edges_to_dense(dev(eu), dev(ev), dev(ew), n, W, ld, True) == 0
+    ref = np.full((n, n), INF)
+    np.fill_diagonal(ref, 0)
+    off = eu != ev
+    np.minimum.at(ref, (eu[off], ev[off]), ew[off])
+    want = np.full(n * ld + 8, -7)
+    rows = np.full((n, ld), -7)
+    rows[:, :n] = ref
+    want[shift:shift + n * ld] = rows.ravel()
+    assert np.array_equal(buf.cpu().numpy(), want)
 
 
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 65, 1000, 131071, 131072, 131073])
