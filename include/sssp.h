@@ -71,13 +71,13 @@ extern "C" {
 #define SSSP_FLAG_LABEL_CORRECTING 16u
 /* sssp_dense_solve_ex: the label-correcting method of the paper's CUDA design
  * (Section III-C, Algorithms 3 and 4), made deterministic: sweeps relax the rows
- * of the vertices whose dist changed in the previous sweep until none changes,
- * then one pass over the reachable rows sets pred[v] to the u of smallest
- * (dist[u], u) with dist[u] + W[u][v] == dist[v].  Same dist and pred as
- * Algorithm 1: when that pass finds a tight zero-weight edge the launch solves
- * again with the Dijkstra rounds (SSSP_STATUS_ZERO_FALLBACK).  Runs on the
- * whole-GPU grid (SSSP_FLAG_SINGLE: one workgroup); not with SSSP_FLAG_LITERAL.
- * Stats: ROUNDS = sweeps, SETTLED = rows streamed (frontiers plus the pred pass). */
+ * of the vertices whose dist changed in the previous sweep until none changes;
+ * pred[v] is the u of smallest (dist[u], u) with dist[u] + W[u][v] == dist[v].
+ * Same dist and pred as Algorithm 1: when a tight zero-weight edge was met the
+ * launch solves again with the Dijkstra rounds (SSSP_STATUS_ZERO_FALLBACK).  Runs
+ * on the whole-GPU grid (SSSP_FLAG_SINGLE: one workgroup); not with
+ * SSSP_FLAG_LITERAL.  Stats: ROUNDS = sweeps, SETTLED = the sizes of all frontiers
+ * plus the reachable vertices. */
 
 /* statistics of a finished launch (sssp_last_status `stats`, 4 entries) */
 #define SSSP_STAT_ROUNDS 0     /* rounds (one bucket of equal-dist vertices, or one vertex, each) */

@@ -77,7 +77,7 @@ struct Ctl {
 // Stamp of exchange number b during use `epoch` of a gang's record memory.
 // Bit 63 is always set, and nothing else ever stored in record or list memory
 // has it: list entries are vertex indices below 2^31 (two per 64-bit word) or
-// (dist << 32) | vertex with dist below INT32_MAX, and a record's key (which
+// tagged words that keep it clear (tag_word, rec_rest, lc_word), and a record's key (which
 // can be all ones) sits 8 bytes into its 32-byte record, while records always
 // start at 32-byte offsets of the memory they share with earlier uses.  So a
 // word left in the same memory by an earlier query or launch can never pass

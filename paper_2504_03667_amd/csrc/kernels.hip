@@ -109,7 +109,7 @@ __device__ __attribute__((noinline)) SolveStats gang_variant(BatchItem I, int pa
 }
 
 // A label-correcting item (rank `part` of a gang of I.parts, possibly one): the
-// sweeps, then the pred pass; a tight zero-weight edge sends the whole gang to
+// sweeps; a tight zero-weight edge sends the whole gang to
 // the Dijkstra rounds on the same records (numbering continued).
 template <int T, int G, typename E>
 __device__ __attribute__((noinline)) SolveStats lc_variant(BatchItem I, int part, long long timeout, Bar* bw,
@@ -117,8 +117,8 @@ __device__ __attribute__((noinline)) SolveStats lc_variant(BatchItem I, int part
     SolveStats st = {0, 0, 0, 0, 0};
     const GangWords gw = gang_words(arena + I.scratch_off, I.parts, I.S);
     uint32_t b = 0;
-    const int r = solve_lc<T, G, 8, E, false>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred,
-                                              I.S, part, I.parts, timeout, bw, gw.pubs, gw.lists, g_sh<T>,
+    const int r = solve_lc<T, G, 4, E, false>(static_cast<const E*>(I.W), I.ld, I.n, I.src, I.dist, I.pred,
+                                              I.S, part, I.parts, timeout, gw, g_sh<T>,
                                               g_lc<T>, st, b, epoch, nullptr);
     if (r == kLcFallback) {
         ++st.fallbacks;
