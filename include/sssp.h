@@ -87,7 +87,7 @@ extern "C" {
 
 /* Tuning knobs; pass NULL for the library's choice.  A zero field means "choose". */
 typedef struct sssp_tuning {
-    int32_t threads;       /* one-workgroup solve: workgroup size, 256 or 1024 */
+    int32_t threads;       /* one-workgroup solve: workgroup size, 256, 512 or 1024 */
     int32_t workgroups;    /* workgroups of the whole-GPU kernel, or of a batched launch */
     int32_t single_max_n;  /* batched plans: largest n solved by one workgroup (0 = autotune) */
     int32_t gang_columns;  /* batched plans: columns per gang member above that */

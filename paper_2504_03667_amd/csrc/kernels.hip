@@ -413,6 +413,7 @@ hipError_t launch_single(const SolveArgs& a, int threads, hipStream_t s) {
         if (groups <= 512) return launch_single_t<256, 2, 8>(a, s);
         if (groups <= 1024) return launch_single_t<256, 4, 8>(a, s);
     }
+    if (threads <= 512 && groups <= 512) return launch_single_t<512, 1, 8>(a, s);
     if (groups <= 1024) return launch_single_t<1024, 1, 8>(a, s);
     if (groups <= 2048) return launch_single_t<1024, 2, 8>(a, s);
     if (groups <= 4096) return launch_single_t<1024, 4, 8>(a, s);
