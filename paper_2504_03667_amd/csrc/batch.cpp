@@ -502,28 +502,41 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     std::vector<char> lc;
     if (flags & SSSP_FLAG_LABEL_CORRECTING) lc.assign(count, 1);
     // label-correcting instances have their own split; literal steps are an exchange
-    // each, which one workgroup does not need
+    // each, which one workgroup does not need; a captured launch may run beside a
+    // server that does not exist yet, whose kernel would keep such gangs from forming
     int dev = 0;
     (void)hipGetDevice(&dev);
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capturing) != hipSuccess) {
+        (void)hipGetLastError();
+        capturing = hipStreamCaptureStatusActive;
+    }
     const int32_t cap = gang_cap(cus, served_workgroups(dev), nwg);
-    const int32_t cols = flags & (SSSP_FLAG_LABEL_CORRECTING | SSSP_FLAG_LITERAL)
-                             ? 0 : concurrent_columns(inst, count, nwg, cap);
-    rc = build(inst, src.data(), count, cols ? cols : max_batch_single_n(), cols ? cols : 4096,
-               cols ? cap : std::max(2, nwg / 2), &b,
-               lc.empty() ? nullptr : lc.data(), nullptr, 0, 0, nullptr, cols != 0);
-    if (rc) return rc;
-    nwg = std::max(1, std::min<int>(nwg, (int)b.parts.size()));
-    if (nwg < b.max_parts) nwg = b.max_parts;
+    int32_t cols = flags & (SSSP_FLAG_LABEL_CORRECTING | SSSP_FLAG_LITERAL) || capturing != hipStreamCaptureStatusNone
+                       ? 0 : concurrent_columns(inst, count, nwg, cap);
     // stream-ordered scratch: allocated and freed in the stream's order, so the
     // call stays asynchronous (copies from pageable memory are staged at once)
     BatchItem* d_items = nullptr;
     BatchPart* d_parts = nullptr;
     Bar* d_bars = nullptr;
     char* d_arena = nullptr;
-    hipError_t e = hipMallocAsync((void**)&d_items, sizeof(BatchItem) * b.items.size(), s);
+    hipError_t e = hipSuccess;
+    for (;;) {
+        b = Build();
+        rc = build(inst, src.data(), count, cols ? cols : max_batch_single_n(), cols ? cols : 4096,
+                   cols ? cap : std::max(2, nwg / 2), &b,
+                   lc.empty() ? nullptr : lc.data(), nullptr, 0, 0, nullptr, cols != 0);
+        if (rc) return rc;
+        e = b.arena_bytes ? hipMallocAsync((void**)&d_arena, b.arena_bytes, s) : hipSuccess;
+        if (e == hipSuccess || !cols) break;
+        (void)hipGetLastError();  // no room for the gangs' exchange memory: the split that needs less
+        cols = 0;
+    }
+    nwg = std::max(1, std::min<int>(nwg, (int)b.parts.size()));
+    if (nwg < b.max_parts) nwg = b.max_parts;
+    if (e == hipSuccess) e = hipMallocAsync((void**)&d_items, sizeof(BatchItem) * b.items.size(), s);
     if (e == hipSuccess) e = hipMallocAsync((void**)&d_parts, sizeof(BatchPart) * b.parts.size(), s);
     if (e == hipSuccess) e = hipMallocAsync((void**)&d_bars, sizeof(Bar) * b.items.size(), s);
-    if (e == hipSuccess && b.arena_bytes) e = hipMallocAsync((void**)&d_arena, b.arena_bytes, s);
     if (e != hipSuccess) return err(SSSP_ENOMEM, "hipMallocAsync(batch): %s", hipGetErrorString(e));
     e = hipMemcpyAsync(d_items, b.items.data(), sizeof(BatchItem) * b.items.size(), hipMemcpyHostToDevice, s);
     if (e == hipSuccess)

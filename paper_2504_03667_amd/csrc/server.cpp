@@ -295,7 +295,8 @@ struct sssp_server {
     // rounds' exchanges (about 5 us per round for one workgroup, 8 us per member
     // and round for a gang) plus its rows at about 25 GB/s per workgroup; a
     // label-correcting solve is taken as 24 sweeps and 5x the rows (repeated
-    // relaxations and the pred pass).  True when label-correcting is clearly
+    // relaxations, and a pass for pred that the method had when these costs were
+    // fitted; both methods take less now).  True when label-correcting is clearly
     // cheaper, which also keeps saturation throughput from dropping.
     bool lc_cheaper(const Graph& g, const Query& q) const {
         // both methods priced at their default (wide) split: the query may have
