@@ -338,7 +338,7 @@ constexpr int kWeightSample = 256;
 // length, so that a vertex has about as many edges within a range at any density
 // (8 to 18 tried: n=10^6 of 6 a vertex 1197, 1087, 1372 us at 8, 12, 18; of 20 a
 // vertex 2420, 2235, 2982; twice the mean weight at any density 1.1 and 4.25 ms).
-constexpr unsigned kRangeEdges = 12;
+constexpr double kRangeEdges = 12;
 
 __global__ void k_csr_init(int32_t n, int32_t src, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ w,
                            uint64_t* __restrict__ lab, uint64_t* __restrict__ pkey, uint32_t* __restrict__ lists,
@@ -362,9 +362,8 @@ __global__ void k_csr_init(int32_t n, int32_t src, const int64_t* __restrict__ r
         }
         __syncthreads();
         if (threadIdx.x == 0) {
-            const unsigned long long d =
-                count && m >= 4 * (int64_t)n ? kRangeEdges * (unsigned long long)n * sum / ((unsigned long long)m * count) : 0;
-            cc->delta = d == 0 || d >= kInf ? kInf : (uint32_t)d;
+            const double d = count && m >= 4 * (int64_t)n ? kRangeEdges * (double)n * (double)sum / ((double)m * count) : 0;
+            cc->delta = d < 1 || d >= (double)kInf ? kInf : (uint32_t)d;
         }
     }
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -465,9 +464,10 @@ __device__ __forceinline__ bool tight(uint32_t du, uint32_t dv, int32_t wt) {
 // and now: n=1000 133 -> 115 us, 10000 207 -> 174, 40000 368 -> 248, 200000 824 ->
 // 390, 10^6 2670 -> 980 (event to event, scratch allocation included).
 constexpr uint32_t kLargeFrontier = 32768;
+constexpr uint32_t kRangeFew = 256;  // vertices of a range below which the next ones are twice as wide: the sample
+                                     // misjudges a graph whose paths are not made of its typical edges
 constexpr uint32_t kSoloFrontier = 512;  // n=10000: 256 209 us, 512 212, 768 215, 1536 253
 constexpr int64_t kSoloDegree = 16;     // only if the lists are this short on average
-constexpr uint32_t kSoloSweeps = 4096;  // per run, so that the waiting workgroups' time limit is never near
 constexpr uint32_t kAppendCap = 4096;   // entries gathered in LDS
 
 struct SweepLds {
@@ -597,7 +597,7 @@ __device__ bool frontier_sweeps(uint32_t* __restrict__ count, uint32_t* __restri
     const int wgwaves = (int)(blockDim.x / kWave);
     const int64_t wave = (int64_t)blockIdx.x * wgwaves + threadIdx.x / kWave;
     const int64_t waves = (int64_t)nwg * wgwaves;
-    const uint32_t delta = cc->delta;  // written by the launch before this one
+    uint32_t delta = cc->delta;  // written by the launch before this one
     const uint32_t solo = row_ptr[n] <= kSoloDegree * n ? kSoloFrontier : 0u;
     uint32_t thr = delta, tag = 0, ph = 0, scans = 0;
     if (threadIdx.x < 2) sl.fill[threadIdx.x] = 0;
@@ -613,6 +613,8 @@ __device__ bool frontier_sweeps(uint32_t* __restrict__ count, uint32_t* __restri
                         cur[i] = ld_agent(&lists[(size_t)ph * n + i]);
                     __syncthreads();
                     uint32_t k = 0;
+                    bool hand_back = false;
+                    const long long t_solo = wall_clock64();
                     do {
                         ++sweeps;
                         rows += F;
@@ -623,12 +625,19 @@ __device__ bool frontier_sweeps(uint32_t* __restrict__ count, uint32_t* __restri
                                                     tail, value);
                         __syncthreads();
                         F = *fill;
-                        if (threadIdx.x == 0) sl.fill[(k & 1) ^ 1] = 0;
+                        if (threadIdx.x == 0) {
+                            sl.fill[(k & 1) ^ 1] = 0;
+                            // the waiting workgroups' limit must not be reached by a run of slow
+                            // sweeps (vertices of very long lists) that each stay below it
+                            sl.base = wall_clock64() - t_solo > timeout / 4 ? 1u : 0u;
+                        }
                         uint32_t* t = cur;
                         cur = nxt;
                         nxt = t;
                         __syncthreads();
-                    } while (F && F <= solo && ++k < kSoloSweeps);
+                        hand_back = sl.base != 0;
+                        ++k;
+                    } while (F && F <= solo && !hand_back);
                     // the frontier into list 0 (what did not fit LDS is there already)
                     for (uint32_t i = threadIdx.x; i < min(F, half); i += blockDim.x) st_agent(&lists[i], cur[i]);
                     if (threadIdx.x == 0) {
@@ -691,6 +700,7 @@ __device__ bool frontier_sweeps(uint32_t* __restrict__ count, uint32_t* __restri
         if (!csr_barrier(cc, ++b, nwg, timeout, &count[nx], &F)) return false;
         ph = nx;
         ++scans;
+        if (F < kRangeFew) delta = (uint32_t)min(2 * (uint64_t)delta, (uint64_t)kInf);
         if (F) {
             thr = end;
         } else {

@@ -86,3 +86,18 @@ def test_empty_ranges_and_largest_distances(sp, degree):
     ew = np.concatenate([rng.integers(1, 20, size=eu.size - pad - 4), np.full(pad, 20),
                          [bridge, MAX_DIST - bridge, 1, MAX_DIST - bridge + 1]])
     check(sp, eu, ev, ew, n)
+
+
+def test_ranges_much_narrower_than_the_paths_edges(sp):
+    """A long chain of heavy edges beside many light ones, which set the width of the
+    ranges; hubs whose lists are long while the average one is short."""
+    n, chain = RANGE_N, 3000
+    rng = np.random.default_rng(9)
+    eu, ev = rng.integers(chain, n, size=(2, 4 * n))
+    ew = rng.integers(1, 4, size=eu.size)
+    c = np.arange(chain - 1)
+    hub = np.arange(chain, n)
+    eu = np.concatenate([eu, c, np.full(hub.size, 7)])
+    ev = np.concatenate([ev, c + 1, hub])
+    ew = np.concatenate([ew, rng.integers(10 ** 5, 10 ** 6, size=chain - 1), rng.integers(1, 10 ** 6, size=hub.size)])
+    check(sp, eu, ev, ew, n)
