@@ -118,12 +118,14 @@ __global__ void k_hops_first(const int32_t* __restrict__ pred, const int32_t* __
     }
 }
 
-// Passes of four doublings read each word's chain twice as often as two of two
-// would; on large graphs of deep trees (chains longer than 32) that counts for more
-// than launches.
-constexpr int kHopsFirst = 5;
+// Following more links in a pass reads more words for the same doublings: on large
+// graphs that counts for more than launches.  One doubling a pass, two words each,
+// and passes of 5, then 2 and of 1, then 2 doublings: n=10^6 a random tree 203, 195
+// and 146 us, a single chain 523, 787 and 348; n=100000 97, 85 and 66; n=40000 79 and,
+// with 5, then 4, 42 us.
+constexpr int kHopsFirst = 5, kHopsFirstWide = 1;
 constexpr int kHopsStep = 4, kHopsStepWide = 2;
-constexpr int32_t kHopsWideN = 131072;
+constexpr int32_t kHopsWideN = 65536;
 
 // hops (if given) takes the result instead of out.
 __global__ void k_hops_step(const Jump* __restrict__ in, int32_t n, int32_t log2_links, Jump* __restrict__ out,
@@ -205,7 +207,8 @@ int sssp_hops(const int32_t* pred, const int32_t* dist, int32_t n, int32_t* hops
     int left = 1;
     while ((1ll << (left - 1)) < n) ++left;
     // the first pass leaves the last one something: that writes hops, and hops may be pred
-    int now = left > kHopsFirst ? kHopsFirst : left - 1;
+    const int first = n < kHopsWideN ? kHopsFirst : kHopsFirstWide;
+    int now = left > first ? first : left - 1;
     hipLaunchKernelGGL(k_hops_first, dim3(blocks), dim3(256), 0, s, pred, dist, n, now, buf);
     Jump *in = buf, *out = buf + n;
     const int each = n < kHopsWideN ? kHopsStep : kHopsStepWide;

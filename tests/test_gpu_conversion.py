@@ -83,7 +83,7 @@ def test_dense_rows_at_any_alignment(sp, n, ld, shift):
     assert np.array_equal(buf.cpu().numpy(), want)
 
 
-@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 65, 1000, 131071, 131072, 131073])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 65, 1000, 65535, 65536, 65537, 131073])
 @pytest.mark.parametrize("depth", ["chain", "random"])
 def test_hops(sp, n, depth):
     """Chains through all vertices in random order, and random trees; the last vertex of
