@@ -160,8 +160,10 @@ __device__ __forceinline__ void st_agent(X* p, X v) {
 // arrives at an exchange (its stamp or barrier arrival; in a tagged exchange,
 // its list entries and, separately, its record), a workgroup pauses for a
 // pseudo-random 0 to ~25 us chosen by (workgroup, key), so that tests see many
-// arrival orders, late members and entries that arrive after their record.
-// Compiled out of the product library.
+// arrival orders, late members and entries that arrive after their record; and
+// after an exchange its waves but the first pause likewise before they read the
+// result (stress_wave_delay), while the first goes on.  Compiled out of the
+// product library.
 __device__ __forceinline__ void stress_delay(uint32_t key) {
 #ifdef SSSP_STRESS_DELAYS
     uint32_t h = (blockIdx.x + 1u) * 0x9E3779B9u ^ (key * 0x85EBCA6Bu);
@@ -170,6 +172,13 @@ __device__ __forceinline__ void stress_delay(uint32_t key) {
     h ^= h >> 12;
     if ((h & 3u) == 0u)
         for (uint32_t i = 0, k = (h >> 8) & 7u; i < k; ++i) __builtin_amdgcn_s_sleep(127);
+#else
+    (void)key;
+#endif
+}
+__device__ __forceinline__ void stress_wave_delay(uint32_t key) {
+#ifdef SSSP_STRESS_DELAYS
+    if (threadIdx.x >= kWave) stress_delay(key * 16u + threadIdx.x / kWave);
 #else
     (void)key;
 #endif

@@ -325,8 +325,8 @@ __device__ __forceinline__ void lc_read_wave(uint64_t* recs, int S, int nwg, uin
         run += ck;
     }
     if (l == kWave - 1) {
-        sh.res.rows = inc;
-        sh.res.flags = (small ? 2u : 0u) | (late << 2);
+        sh.res[tag & 1u].rows = inc;
+        sh.res[tag & 1u].flags = (small ? 2u : 0u) | (late << 2);
     }
 }
 
@@ -339,10 +339,10 @@ __device__ __forceinline__ uint32_t lc_records(uint64_t* recs, int S, int nwg, u
             else lc_read_wave<T, 4>(recs, S, nwg, tag, timeout, sh, lc);
         }
         __syncthreads();
-        const uint32_t z = scalar(sh.res.flags);
+        const uint32_t z = scalar(sh.res[tag & 1u].flags);
         staged = (z & 2u) != 0;
         ok = (z & 4u) == 0;
-        return scalar(sh.res.rows);
+        return scalar(sh.res[tag & 1u].rows);
     }
     uint32_t c = 0, late = sh.stage_late;
     if ((int)threadIdx.x < nwg) {

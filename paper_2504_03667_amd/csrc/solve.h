@@ -30,10 +30,15 @@ struct SharedSolve {
     uint32_t cnt[T];
     uint64_t rk;  // results for the whole workgroup (lc.h, multi.h)
     uint32_t rz, rm;
+    // read_records results for the whole workgroup, by exchange parity.  A round in
+    // which the slice reads no row has no barrier between the reads of one exchange's
+    // result and wave 0's stores of the next: those go to the other slot, and wave 0
+    // comes back to this one only after the next exchange's barrier, which every
+    // wave passes after its reads.
     struct alignas(16) {
         uint32_t d, vert, rows, flags;
-    } res;  // read_records results for the whole workgroup
-    uint64_t res_need;  // ... and, for narrow slices, the lanes whose group the next round reads
+    } res[2];
+    uint64_t res_need[2];  // ... and, for narrow slices, the lanes whose group the next round reads
     uint32_t claim[2];    // chunk claims of a balanced round, broadcast by thread 0
     uint32_t stage_late;  // a bucket entry did not arrive in time (set once; the solve then ends)
     int32_t item;
@@ -499,7 +504,7 @@ __device__ __forceinline__ uint64_t wait_tag(const uint64_t* p, uint64_t w, uint
 }
 
 // The wave's part of read_records: lane l polls members l + 64 k, k < KM, and the
-// wave leaves the exchange's result in sh.res and the bucket in sh.list (staged)
+// wave leaves the exchange's result in sh.res[tag & 1] and the bucket in sh.list (staged)
 // or its counts and offsets in sh.cnt / sh.pre.
 template <int T, int G, bool NARROW, int KM>
 __device__ __forceinline__ void read_wave(uint64_t* recs, const uint64_t* __restrict__ rl, int S, int nwg,
@@ -618,11 +623,12 @@ __device__ __forceinline__ void read_wave(uint64_t* recs, const uint64_t* __rest
     // the slice's owners are lanes of this wave: their groups the next round reads
     const uint64_t open = NARROW ? wave_mask(group_open(cand[0], d, wmin)) : 0ull;
     if (l == kWave - 1) {  // one 16-byte store here, one load in every thread
-        sh.res.d = d;
-        sh.res.vert = low;
-        sh.res.rows = inc;
-        sh.res.flags = hazard | (small ? 2u : 0u) | (late << 2);
-        if (NARROW) sh.res_need = open;
+        auto& res = sh.res[tag & 1u];
+        res.d = d;
+        res.vert = low;
+        res.rows = inc;
+        res.flags = hazard | (small ? 2u : 0u) | (late << 2);
+        if (NARROW) sh.res_need[tag & 1u] = open;
     }
 }
 
@@ -660,8 +666,9 @@ __device__ __forceinline__ bool read_records(uint64_t* recs, const uint64_t* __r
             else read_wave<T, G, NARROW, 4>(recs, rl, S, nwg, wmin, tag, timeout, sh, stamps, stamp, cand);
         }
         __syncthreads();
+        stress_wave_delay(tag);
         // the same in every thread: scalar registers
-        const auto res = sh.res;
+        const auto res = sh.res[tag & 1u];
         d_out = scalar(res.d);
         u_out = scalar(res.vert);
         M = scalar(res.rows);
@@ -669,7 +676,7 @@ __device__ __forceinline__ bool read_records(uint64_t* recs, const uint64_t* __r
         Z = z & 1u;
         staged = (z & 2u) != 0;
         if (NARROW) {
-            const uint64_t o = sh.res_need;
+            const uint64_t o = sh.res_need[tag & 1u];
             open = ((uint64_t)scalar((uint32_t)(o >> 32)) << 32) | scalar((uint32_t)o);
         }
         return (z & 4u) == 0;

@@ -1,0 +1,25 @@
+"""Host-only check that a workgroup's waves read the result of the exchange they are
+at, whatever their order, compiled from the library's own headers."""
+import os
+import subprocess
+import tempfile
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = "/opt/rocm/bin/hipcc"
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_waves_read_their_own_exchange():
+    src = os.path.join(ROOT, "tests", "native", "result_slots.cpp")
+    with tempfile.TemporaryDirectory() as tmp:
+        exe = os.path.join(tmp, "result_slots")
+        b = subprocess.run([HIPCC, "-x", "hip", "--offload-arch=gfx950", "-O1", "-std=c++17",
+                            "-I", os.path.join(ROOT, "include"),
+                            "-I", os.path.join(ROOT, "paper_2504_03667_amd", "csrc"), src, "-o", exe],
+                           capture_output=True, text=True)
+        assert b.returncode == 0, b.stderr[-3000:]
+        r = subprocess.run([exe], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        assert "result slots ok" in r.stdout
