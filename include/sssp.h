@@ -370,13 +370,15 @@ int sssp_edges_to_csr(const int32_t* eu, const int32_t* ev, const int32_t* ew, i
  * order settles first, recovered by a pass over the vertices those edges touch
  * (one workgroup per distance; SSSP_STATUS_ZERO_FALLBACK, informational).
  * tuning->workgroups (may be NULL) sets the grid (default about n / 256; never
- * above 1024 nor the co-resident count).  Stats: ROUNDS = sweeps, SETTLED = edge
+ * above 1024 nor the co-resident count, less what a server's kernel holds); those of
+ * its workgroups that other work keeps off the GPU for the launch's first 0.2 ms or
+ * longer take no part.  Stats: ROUNDS = sweeps, SETTLED = edge
  * lists relaxed (the sweep count may differ between runs; dist and pred do not).
  * Allocates stream-ordered scratch of about 100 n bytes.  Asynchronous. */
 int sssp_csr_solve(const int64_t* row_ptr, const int32_t* col, const int32_t* w, int32_t n, int32_t src,
                    int32_t* dist, int32_t* pred, const sssp_tuning* tuning, void* stream);
 
-/* The grid sssp_csr_solve would launch for n vertices on the stream's device:
+/* The grid sssp_csr_solve would launch now for n vertices on the stream's device:
  * *workgroups, and (each may be NULL) the co-resident workgroups per compute unit
  * and the compute units that bound it. */
 int sssp_csr_grid(int32_t n, const sssp_tuning* tuning, void* stream, int32_t* workgroups, int32_t* per_cu,

@@ -8,7 +8,8 @@
 // Such graphs have many distinct distances and few edges, so the solve uses the
 // label-correcting method (the paper's CUDA design, Algorithms 3 and 4, made
 // deterministic in its results) over edges:
-//   * a persistent cooperative grid; sweep k relaxes the edge lists of the
+//   * a persistent grid of the workgroups that are on the GPU when the launch
+//     starts (close_team); sweep k relaxes the edge lists of the
 //     vertices whose dist dropped in sweep k-1 (the first frontier is the
 //     source) with an agent-scope atomic minimum on the head's running dist;
 //     the first lowering of a vertex in a sweep appends it to the next
@@ -40,6 +41,7 @@ int set_error(int code, const char* msg);                                     //
 int stream_ctl(hipStream_t stream, Ctl** out, int* cus, long long* clock_khz);  // api.cpp
 bool grid_launch_is_plain();                                                    // api.cpp
 long long grid_barrier_ticks(long long clock_khz);                              // api.cpp
+int served_workgroups(int device);                                              // server.cpp
 
 namespace {
 
@@ -69,6 +71,10 @@ struct CsrCtl {
     uint32_t rest[3];     // smallest dist beyond the threshold, by scan number mod 3
     uint32_t delta;       // distances handled at a time (kInf: all)
     uint32_t pad2[18];
+    uint32_t join;  // workgroups that have arrived; kTeamClosed: no more are taken
+    uint32_t pad3[31];
+    uint64_t team;  // (workgroups of the team << 32) | the first frontier it is handed; 0 before that
+    uint32_t pad4[30];
 };
 
 // Scratch of zero_tie_pred (device memory; n = vertices, H = 2^hbits >= 2n).
@@ -381,6 +387,8 @@ __global__ void k_csr_init(int32_t n, int32_t src, const int64_t* __restrict__ r
         cc->nlev = 0;
         cc->next_level = 0;
         for (int i = 0; i < 3; ++i) cc->rest[i] = kInf;
+        cc->join = 0;
+        cc->team = 0;
         if (n < kRangeMinN) cc->delta = kInf;
     }
 }
@@ -429,6 +437,62 @@ __device__ __forceinline__ bool csr_barrier(CsrCtl* cc, uint32_t b, uint32_t nwg
     const bool ok = __syncthreads_or(late) == 0;
     if (value) *value = handed;
     return ok;
+}
+
+// The workgroups that take part.  A grid barrier waits for all of its workgroups, and
+// other work can keep some from starting for as long as it runs (a resident server
+// holds nearly every compute unit), so the grid's size is what is asked for and the
+// team's is what has come: each workgroup's arrival gives it its rank, and the first,
+// once it has done what it does alone, waits up to `limit` ticks for the rest, then
+// closes the team and hands it the frontier.  Later ones find it closed and leave.
+// close_team is the team's first barrier; false: the first workgroup's word did not
+// come within `timeout`.
+constexpr uint32_t kTeamClosed = 0x80000000u;
+// Waiting longer than a solve takes is no gain: the smallest wait that covers the start
+// of a grid on an idle GPU many times over.
+constexpr int kTeamWaitUs = 200;
+
+__device__ __forceinline__ uint32_t join_team(CsrCtl* cc) {
+    __shared__ uint32_t rank;
+    if (threadIdx.x == 0) {
+        stress_delay(0x7ea3u);
+        rank = __hip_atomic_fetch_add(&cc->join, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    return scalar(rank);
+}
+
+__device__ __forceinline__ bool close_team(CsrCtl* cc, uint32_t rank, uint32_t asked, long long limit,
+                                           long long timeout, uint32_t& size, uint32_t& F) {
+    __shared__ uint64_t handed;
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const long long t0 = wall_clock64();
+        uint64_t team = 0;
+        if (rank == 0) {
+            uint32_t k = ld_agent(&cc->join);
+            while (k < asked && wall_clock64() - t0 < limit) {
+                __builtin_amdgcn_s_sleep(1);
+                k = ld_agent(&cc->join);
+            }
+            k = __hip_atomic_fetch_or(&cc->join, kTeamClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            team = ((uint64_t)k << 32) | F;
+            st_agent(&cc->team, team);
+        } else {
+            unsigned naps = 1;
+            while ((team = ld_agent(&cc->team)) == 0 && wall_clock64() - t0 <= timeout) {
+                for (unsigned i = 0; i < naps; ++i) __builtin_amdgcn_s_sleep(1);
+                if (naps < 8) naps <<= 1;
+            }
+        }
+        handed = team;
+    }
+    __syncthreads();
+    size = scalar((uint32_t)(handed >> 32));
+    F = scalar((uint32_t)handed);
+    return size != 0;
 }
 
 // Does tail u (dist du) reach head v (dist dv) over an edge of weight wt on a
@@ -586,26 +650,28 @@ __device__ __forceinline__ void flush_appends(SweepLds& sl, uint32_t* __restrict
 }
 
 // The barrier that ends a sweep hands over the next frontier's size.  Stops when
-// no vertex is left to relax; false if a barrier wait gave up.
+// no vertex is left to relax; false if a barrier wait gave up.  rank: this
+// workgroup's; nwg gets the number of workgroups (close_team).
 template <class Tail, class Value>
-__device__ bool frontier_sweeps(uint32_t* __restrict__ count, uint32_t* __restrict__ lists,
+__device__ bool frontier_sweeps(uint32_t rank, uint32_t& nwg, long long team_limit,
+                                uint32_t* __restrict__ count, uint32_t* __restrict__ lists,
                                 uint64_t* __restrict__ lab, const int64_t* __restrict__ row_ptr,
                                 const int32_t* __restrict__ col, const int32_t* __restrict__ w, int32_t n, CsrCtl* cc,
                                 uint32_t& b, long long timeout, uint32_t F, unsigned long long& sweeps,
                                 unsigned long long& rows, SweepLds& sl, Tail tail, Value value) {
-    const uint32_t nwg = gridDim.x;
     const int wgwaves = (int)(blockDim.x / kWave);
-    const int64_t wave = (int64_t)blockIdx.x * wgwaves + threadIdx.x / kWave;
-    const int64_t waves = (int64_t)nwg * wgwaves;
+    const int64_t wave = (int64_t)rank * wgwaves + threadIdx.x / kWave;
+    int64_t waves = 0;
     uint32_t delta = cc->delta;  // written by the launch before this one
     const uint32_t solo = row_ptr[n] <= kSoloDegree * n ? kSoloFrontier : 0u;
     uint32_t thr = delta, tag = 0, ph = 0, scans = 0;
+    nwg = 0;
     if (threadIdx.x < 2) sl.fill[threadIdx.x] = 0;
     __syncthreads();
     for (;;) {
         while (F) {
-            if (F <= solo) {
-                if (blockIdx.x == 0) {
+            if (F <= solo || nwg == 0) {
+                if (rank == 0 && F <= solo) {
                     constexpr uint32_t half = kAppendCap / 2;
                     uint32_t* cur = sl.buf;
                     uint32_t* nxt = sl.buf + half;
@@ -648,8 +714,13 @@ __device__ bool frontier_sweeps(uint32_t* __restrict__ count, uint32_t* __restri
                         st_agent(&cc->solo_f, F);
                     }
                 }
-                if (!csr_barrier(cc, ++b, nwg, timeout, &cc->solo_f, &F)) return false;
-                tag = ld_agent(&cc->solo_tag);
+                if (nwg == 0) {
+                    if (!close_team(cc, rank, gridDim.x, team_limit, timeout, nwg, F)) return false;
+                    waves = (int64_t)nwg * wgwaves;
+                } else if (!csr_barrier(cc, ++b, nwg, timeout, &cc->solo_f, &F)) {
+                    return false;
+                }
+                if (solo) tag = ld_agent(&cc->solo_tag);
                 ph = 0;
                 continue;
             }
@@ -657,7 +728,7 @@ __device__ bool frontier_sweeps(uint32_t* __restrict__ count, uint32_t* __restri
             ++sweeps;
             rows += F;
             ++tag;
-            if (blockIdx.x == 0 && threadIdx.x == 0) st_agent(&count[old], 0u);
+            if (rank == 0 && threadIdx.x == 0) st_agent(&count[old], 0u);
             const uint32_t* list = lists + (size_t)ph * n;
             uint32_t* next = lists + (size_t)nx * n;
             auto entry = [&](uint32_t i) { return ld_agent(&list[i]); };
@@ -676,7 +747,7 @@ __device__ bool frontier_sweeps(uint32_t* __restrict__ count, uint32_t* __restri
         const uint32_t nx = ph == 2 ? 0 : ph + 1, old = nx == 2 ? 0 : nx + 1;
         const uint32_t end = (uint32_t)min((uint64_t)thr + delta, (uint64_t)kInf);
         const uint32_t rs = scans % 3;
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (rank == 0 && threadIdx.x == 0) {
             st_agent(&count[old], 0u);
             st_agent(&cc->rest[(scans + 1) % 3], kInf);
         }
@@ -761,14 +832,13 @@ __device__ __forceinline__ uint32_t level_slot(uint32_t d, uint32_t hbits) {
 }
 
 template <int T>
-__device__ bool zero_tie_pred(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-                              const int32_t* __restrict__ w, int32_t n, int32_t src, const uint64_t* __restrict__ lab,
+__device__ bool zero_tie_pred(uint32_t rank, uint32_t nwg, const int64_t* __restrict__ row_ptr,
+                              const int32_t* __restrict__ col, const int32_t* __restrict__ w, int32_t n, int32_t src, const uint64_t* __restrict__ lab,
                               uint64_t* __restrict__ rk, uint64_t* __restrict__ pk, const ZeroTie& zt, CsrCtl* cc,
                               uint32_t& b, long long timeout, int32_t* __restrict__ dist,
                               int32_t* __restrict__ pred, Red<T>& red) {
     __shared__ uint32_t claim;
-    const uint32_t nwg = gridDim.x;
-    const int64_t gtid = (int64_t)blockIdx.x * T + threadIdx.x;
+    const int64_t gtid = (int64_t)rank * T + threadIdx.x;
     const int64_t gsz = (int64_t)nwg * T;
     const uint32_t hmask = (uint32_t)((1ull << zt.hbits) - 1ull);
     auto D = [&](int64_t v) { return label_value(ld_agent(&lab[v])); };
@@ -838,7 +908,7 @@ __device__ bool zero_tie_pred(const int64_t* __restrict__ row_ptr, const int32_t
     if (!csr_barrier(cc, ++b, nwg, timeout)) return false;
     const uint32_t nl = ld_agent(&cc->nlev);
     // where each level's group starts: an exclusive scan of the counts, by workgroup 0
-    if (blockIdx.x == 0) {
+    if (rank == 0) {
         uint32_t run = 0;
         for (uint32_t base = 0; base < nl; base += T) {
             const uint32_t i = base + threadIdx.x;
@@ -949,19 +1019,18 @@ __global__ __launch_bounds__(T) void k_csr_lc(const int64_t* __restrict__ row_pt
                                               int32_t* __restrict__ dist, int32_t* __restrict__ pred,
                                               uint64_t* __restrict__ lab, uint64_t* __restrict__ pkey,
                                               uint64_t* __restrict__ rk, uint32_t* __restrict__ lists,
-                                              CsrCtl* __restrict__ cc, ZeroTie zt, long long timeout,
-                                              Ctl* __restrict__ ctl) {
+                                              CsrCtl* __restrict__ cc, ZeroTie zt, long long team_limit,
+                                              long long timeout, Ctl* __restrict__ ctl) {
     __shared__ Red<T> red;
     __shared__ SweepLds sl;
-    const uint32_t nwg = gridDim.x;
-    const int64_t gtid = (int64_t)blockIdx.x * T + threadIdx.x;
-    const int64_t gsz = (int64_t)nwg * T;
-    uint32_t b = 0;
+    const uint32_t rank = join_team(cc);
+    if (rank & kTeamClosed) return;
+    uint32_t b = 0, nwg = 0;
     unsigned long long sweeps = 0, rows = 0;
     uint32_t neg = 0;
     // distances: label-correcting sweeps from the source (the first frontier)
     bool ok = frontier_sweeps(
-        cc->count, lists, lab, row_ptr, col, w, n, cc, b, timeout, 1u, sweeps, rows, sl,
+        rank, nwg, team_limit, cc->count, lists, lab, row_ptr, col, w, n, cc, b, timeout, 1u, sweeps, rows, sl,
         [&](int32_t u) { return label_value(ld_agent(&lab[u])); },
         [&](uint32_t du, int32_t u, int32_t v, int32_t wt, uint32_t& c) {
             if (!edge_ok(u, v, wt, n)) {
@@ -971,6 +1040,8 @@ __global__ __launch_bounds__(T) void k_csr_lc(const int64_t* __restrict__ row_pt
             c = du + (uint32_t)wt;  // both < 2^31: no wrap
             return c < kInf;        // longer than INT32_MAX - 1: not representable
         });
+    const int64_t gtid = (int64_t)rank * T + threadIdx.x;
+    const int64_t gsz = (int64_t)nwg * T;
     uint32_t zero = 0;
     if (ok) {
         // pred pass: the tight edge of smallest (dist[u], u) into each vertex
@@ -999,7 +1070,7 @@ __global__ __launch_bounds__(T) void k_csr_lc(const int64_t* __restrict__ row_pt
     const uint32_t Z = ok ? ld_agent(&cc->zero) : 0u;
     if (ok && Z) {
         // tight zero-weight edges: the settle order of equal distances decides pred
-        ok = zero_tie_pred<T>(row_ptr, col, w, n, src, lab, rk, pkey, zt, cc, b, timeout, dist, pred, red);
+        ok = zero_tie_pred<T>(rank, nwg, row_ptr, col, w, n, src, lab, rk, pkey, zt, cc, b, timeout, dist, pred, red);
         status |= ok ? kStatusZeroFallback : kStatusTimeout;
     } else if (ok) {
         for (int64_t v = gtid; v < n; v += gsz) {
@@ -1009,12 +1080,12 @@ __global__ __launch_bounds__(T) void k_csr_lc(const int64_t* __restrict__ row_pt
             pred[v] = (v == src || d >= kInf || kk == kNoKey) ? -1 : (int32_t)(uint32_t)kk;
         }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (rank == 0 && threadIdx.x == 0) {
         if (ok && ld_agent(&cc->neg)) status |= kStatusNegWeight;
         ctl->last[kStatRounds] = sweeps;
         ctl->last[kStatSettled] = rows;
         ctl->last[kStatFallbacks] = (status & kStatusZeroFallback) ? 1 : 0;
-        ctl->last[kStatBarriers] = b;
+        ctl->last[kStatBarriers] = b + 1;
         ctl->status = status;
     }
 }
@@ -1033,17 +1104,20 @@ using namespace sssp;
 namespace {
 
 // Workgroups of a CSR solve: about 256 vertices each, at most 1024 and at most the
-// occupancy query times the compute units.  1024 threads, one workgroup per CU:
-// as many waves as 1024 workgroups of 256 threads with a quarter of the barrier's
-// arrivals and of the appends' counter updates (n=10000: 174 us against 196 with
-// 512 vertices each and 241 with 1024).
+// occupancy query times the compute units that no server's kernel holds (it can hold
+// them for as long as queries come; close_team sees to what comes after this count).
+// 1024 threads, one workgroup per CU: as many waves as 1024 workgroups of 256 threads
+// with a quarter of the barrier's arrivals and of the appends' counter updates
+// (n=10000: 174 us against 196 with 512 vertices each and 241 with 1024).
 constexpr int kCsrMaxGrid = 1024;
 
 int csr_grid(int32_t n, const sssp_tuning* tuning, int cus, int* nwg, int* per_cu_out) {
     int per_cu = 0;
     if (csr_occupancy(&per_cu) != 0 || per_cu < 1) return err(SSSP_EDEVICE, "CSR kernel does not fit a CU");
     int g = tuning && tuning->workgroups ? tuning->workgroups : (int)std::max<int64_t>(1, ((int64_t)n + 255) / 256);
-    *nwg = std::max(1, std::min({g, per_cu * cus, kCsrMaxGrid}));
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    *nwg = std::max(1, std::min({g, per_cu * (cus - served_workgroups(dev)), kCsrMaxGrid}));
     if (per_cu_out) *per_cu_out = per_cu;
     return SSSP_OK;
 }
@@ -1174,14 +1248,18 @@ int sssp_csr_solve(const int64_t* row_ptr, const int32_t* col, const int32_t* w,
     e = hipGetLastError();
     if (e == hipSuccess) {
         long long timeout = grid_barrier_ticks(khz);
+        long long limit = std::min(timeout, khz * kTeamWaitUs / 1000);
+#ifdef SSSP_STRESS_DELAYS
+        limit /= 40;  // some arrive too late
+#endif
         if (grid_launch_is_plain()) {
             // ordinary launch of the same grid (co-resident by its size), for profilers
             hipLaunchKernelGGL(k_csr_lc<kCsrThreads>, dim3(nwg), dim3(kCsrThreads), 0, s, row_ptr, col, w, n, src,
-                               dist, pred, lab, pkey, rk, lists, cc, zt, timeout, ctl);
+                               dist, pred, lab, pkey, rk, lists, cc, zt, limit, timeout, ctl);
             e = hipGetLastError();
         } else {
             void* args[] = {(void*)&row_ptr, (void*)&col, (void*)&w, &n, &src, &dist, &pred, &lab, &pkey,
-                            &rk, &lists, &cc, &zt, &timeout, &ctl};
+                            &rk, &lists, &cc, &zt, &limit, &timeout, &ctl};
             e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_csr_lc<kCsrThreads>), dim3(nwg),
                                            dim3(kCsrThreads), args, 0, s);
         }

@@ -32,7 +32,8 @@
 #include "sssp_internal.h"
 
 namespace {
-// Workgroups of the live servers' kernels, per device.
+// Workgroups of the servers' kernels that are on each device (launched and not yet
+// seen to have left).
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_served[kMaxDevices];
 }  // namespace
@@ -237,7 +238,6 @@ struct sssp_server {
     sssp_server_config cfg{};
     hipStream_t stream = nullptr;
     int nwg = 0;
-    bool counted = false;  // its workgroups are in g_served
     long long clock_khz = 100000;
     // pinned host memory shared with the kernel
     ServeControl* ctl = nullptr;
@@ -264,7 +264,7 @@ struct sssp_server {
     int64_t ring_used = 0;            // ring entries of queries in flight
     int64_t launches = 0;
     int64_t completed = 0;
-    bool live = false;       // the kernel is (or may still be) running
+    bool live = false;       // the kernel is (or may still be) running: its workgroups are in g_served
     bool parking = false;    // park requested; waiting for the kernel to leave
     int64_t last_busy = 0;   // last time work was pending or in flight
     bool quit = false;
@@ -402,13 +402,20 @@ struct sssp_server {
     }
 
     bool launch() {
+        const bool was = live;
+        set_live(true);  // counted before it can hold a compute unit
         if (launch_serve(args(), nwg, stream) != hipSuccess) {
+            set_live(was);
             failed = true;
             return false;
         }
         ++launches;
-        live = true;
         return true;
+    }
+
+    void set_live(bool on) {
+        if (on != live && device < kMaxDevices) g_served[device] += on ? nwg : -nwg;
+        live = on;
     }
 
     // The server thread.  Keeps the heartbeat, admits, collects completions.
@@ -425,12 +432,12 @@ struct sssp_server {
             const int64_t t = now_ns();
             if (parking && hipStreamQuery(stream) == hipSuccess) {
                 parking = false;
-                live = false;
+                set_live(false);
                 __atomic_store_n(&ctl->park, 0u, __ATOMIC_RELEASE);
             }
             if (!pending.empty() || !running.empty()) last_busy = t;
             if (live && !parking && !pending.empty() && running.empty() && hipStreamQuery(stream) == hipSuccess)
-                live = false;  // the kernel left (its heartbeat watchdog fired while the server was idle)
+                set_live(false);  // the kernel left (its heartbeat watchdog fired while the server was idle)
             if (!live && !parking && !pending.empty()) launch();
             if (live && !parking) admit();
             if (collect()) {
@@ -481,7 +488,7 @@ int host_alloc(X** p, size_t count, const char* what) {
 }
 
 void release_all(sssp_server* s) {
-    if (s->counted) g_served[s->device] -= s->nwg;
+    s->set_live(false);
     for (auto& g : s->graphs)
         if (g.owned) (void)hipFree(g.owned);
     if (s->stream) (void)hipStreamDestroy(s->stream);
@@ -557,10 +564,6 @@ int sssp_server_create(const sssp_server_config* cfg_in, sssp_server** out) {
     if (e != hipSuccess) return release_all(s), err(SSSP_EDEVICE, "hipStreamCreate: %s", hipGetErrorString(e));
     e = hipDeviceSynchronize();  // scratch initialised before the kernel starts
     if (e != hipSuccess) return release_all(s), err(SSSP_EDEVICE, "hipDeviceSynchronize: %s", hipGetErrorString(e));
-    if (s->device < kMaxDevices) {
-        g_served[s->device] += s->nwg;
-        s->counted = true;
-    }
     if (!s->launch()) return release_all(s), err(SSSP_EDEVICE, "launching the serving kernel failed");
     s->th = std::thread([s] { s->loop(); });
     *out = s;
