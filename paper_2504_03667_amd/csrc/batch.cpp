@@ -63,11 +63,13 @@ constexpr int32_t kSharedSources = 32;
 
 // Members of the largest gang that a launch may use by its own choice.  A gang
 // waits for all of its members, and the launch is an ordinary one beside whatever
-// else runs: with live servers' kernels on `served` of the compute units and up to
-// four launches dispatched at a time (HIP's hardware queues), one of them holds at
-// least a quarter of the rest, so gangs of at most that many members always form.
+// else runs: with up to four launches dispatched at a time (HIP's hardware queues),
+// one of them holds at least a quarter of the compute units, so gangs of at most that
+// many members form.  Beside a server's kernel (`served`), which holds most of the GPU
+// for as long as queries come, there are none: instances that all run at once need the
+// compute units that it holds.
 int32_t gang_cap(int32_t cus, int32_t served, int32_t nwg) {
-    return std::max(0, std::min((cus - served) / 4, nwg / 2));
+    return served > 0 ? 0 : std::max(0, std::min(cus / 4, nwg / 2));
 }
 
 // Columns per member (and largest n solved by one workgroup) that split a set of
@@ -653,7 +655,9 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
             if (c < nmax) cands.push_back(Cand{c, c, false});
         // every instance split (those of shared matrices too): where all run at once, and
         // twice and four times as wide
-        p->gang_max = gang_cap(cus, 0, p->nwg);
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        p->gang_max = gang_cap(cus, served_workgroups(dev), p->nwg);
         if (const int32_t c0 = concurrent_columns(inst, count, p->nwg, p->gang_max))
             for (int32_t c : {c0, 2 * c0, 4 * c0})
                 if (c <= 4096 && c < nmax) cands.push_back(Cand{c, c, true});

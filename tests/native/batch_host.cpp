@@ -1,0 +1,127 @@
+// Host-only checks of the one-shot batched call's choices and of its scratch (built and
+// run by tests/test_batch_host.py): batch.cpp with the runtime calls that it makes on
+// the way and the kernels' launchers replaced by stand-ins that keep books.
+#include <cstdio>
+#include <cstdlib>
+#include <set>
+#include <vector>
+
+#include "batch.cpp"
+
+static int served = 0;          // workgroups of a server's kernel
+static int fail_at = 0;         // the allocation of this number fails (1: the first); 0: none
+static size_t fail_above = ~size_t(0);  // allocations larger than this fail
+static int allocations = 0;
+static std::set<void*> held;    // scratch not yet given back
+static int failures = 0;
+
+struct Launch {
+    std::vector<BatchItem> items;
+    std::vector<BatchPart> parts;
+    int nwg = 0;
+};
+static Launch last;
+static size_t items_bytes = 0;
+
+#define CHECK(c)                                                        \
+    do {                                                                \
+        if (!(c)) {                                                     \
+            std::fprintf(stderr, "FAILED line %d: %s\n", __LINE__, #c); \
+            ++failures;                                                 \
+        }                                                               \
+    } while (0)
+
+extern "C" {
+hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t) {
+    if (++allocations == fail_at || bytes > fail_above) return hipErrorOutOfMemory;
+    *p = std::malloc(bytes);
+    held.insert(*p);
+    return hipSuccess;
+}
+hipError_t hipFreeAsync(void* p, hipStream_t) {
+    CHECK(held.erase(p) == 1);
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t bytes, hipMemcpyKind, hipStream_t) {
+    memcpy(d, s, bytes);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
+    *st = hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+int sssp_dense_solve_ex(const int32_t*, int64_t, int32_t, int32_t, int32_t*, int32_t*, uint32_t, const sssp_tuning*,
+                        void*) { return SSSP_OK; }
+int sssp_last_status(void*, int32_t*, int64_t*) { return SSSP_OK; }
+}
+
+namespace sssp {
+int set_error(int code, const char*) { return code; }
+const char* last_error_text() { return ""; }
+int stream_ctl(hipStream_t, Ctl** c, int* cus, long long* khz) {
+    *c = nullptr;
+    *cus = 256;
+    *khz = 100000;
+    return SSSP_OK;
+}
+int check_instance(const sssp_instance&, int) { return SSSP_OK; }
+int served_workgroups(int) { return served; }
+int batch_occupancy(int* per_cu) { return *per_cu = 1, 0; }
+int max_batch_single_n() { return 16384; }
+int max_batch_slice() { return 16384; }
+size_t ctl_size() { return 64; }
+hipError_t zero_fill(void*, size_t, hipStream_t) { return hipSuccess; }
+hipError_t weight_range(const int32_t*, int64_t, int32_t, int32_t*, hipStream_t) { return hipSuccess; }
+hipError_t compact_copy(const int32_t*, int64_t, int32_t, void*, int64_t, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_batch(const BatchItem* items, const BatchPart* parts, int32_t nparts, Bar*, char*, uint32_t,
+                        long long, Ctl*, int nwg, hipStream_t) {
+    last.parts.assign(parts, parts + nparts);
+    int32_t k = 0;
+    for (const BatchPart& p : last.parts) k = std::max(k, p.item + 1);
+    last.items.assign(items, items + k);
+    last.nwg = nwg;
+    return hipSuccess;
+}
+}  // namespace sssp
+
+static int solve(const std::vector<int32_t>& sizes, const sssp_tuning* t = nullptr) {
+    std::vector<sssp_instance> inst;
+    static int32_t word;
+    for (size_t i = 0; i < sizes.size(); ++i)
+        inst.push_back(sssp_instance{&word + i, sizes[i], sizes[i], 0, &word, &word});
+    last = Launch();
+    allocations = 0;
+    return sssp_dense_solve_batched(inst.data(), (int32_t)inst.size(), 0, t, nullptr);
+}
+
+static int max_parts() {
+    int m = 0;
+    for (const BatchItem& it : last.items) m = std::max(m, it.parts);
+    return m;
+}
+
+static void beside_a_server() {
+    for (int held_by_it : {1, 128, 192, 248, 256}) {
+        served = held_by_it;
+        for (const auto& sizes : {std::vector<int32_t>{70}, {6000, 3000, 500}, {16384, 16384, 2}, {1000, 1000}}) {
+            CHECK(solve(sizes) == SSSP_OK);
+            CHECK(max_parts() == 1 && last.parts.size() == sizes.size());
+        }
+    }
+    served = 0;
+    CHECK(solve({6000, 3000, 500}) == SSSP_OK);
+    CHECK(max_parts() > 1);
+    CHECK(held.empty());
+}
+
+int main(int argc, char** argv) {
+    (void)argc;
+    (void)argv;
+    beside_a_server();
+    if (failures) return 1;
+    std::printf("batch host ok\n");
+    return 0;
+}

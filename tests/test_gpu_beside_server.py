@@ -113,3 +113,36 @@ def test_csr_solve_beside_a_batch_on_half_the_gpu(sp):
             assert sp.sssp_last_status(stream=streams[1])[0] & 3 == 0
             assert np.array_equal(d.cpu().numpy(), dr) and np.array_equal(p.cpu().numpy(), pr), workgroups
             assert plan.status(stream=streams[0])[0] & 3 == 0
+
+
+def batch(rng, sizes):
+    items, refs = [], []
+    for n in sizes:
+        W = random_dense(rng, n, min(1.0, 0.05 + 3.0 / n), 1, 30)
+        s = int(rng.integers(0, n))
+        d, p = (torch.full((n,), -9, dtype=torch.int32, device="cuda") for _ in range(2))
+        items.append((torch.from_numpy(W).cuda(), s, d, p))
+        refs.append(oracle.dijkstra(W, s)[:2])
+    return items, refs
+
+
+def compare(items, refs):
+    for (_, _, d, p), (dr, pr) in zip(items, refs):
+        assert np.array_equal(d.cpu().numpy(), dr) and np.array_equal(p.cpu().numpy(), pr), d.numel()
+        d.fill_(-9)
+        p.fill_(-9)
+
+
+@pytest.mark.parametrize("held", [128, 192])
+def test_one_shot_batch(sp, held):
+    items, refs = batch(np.random.default_rng(7), [70, 300, 1500, 2500, 4000])
+    sp.sssp_dense_solve_batched(items)
+    compare(items, refs)
+    busy = Busy(sp, held)
+    with busy.srv:
+        for _ in range(3):
+            busy.touch()
+            sp.sssp_dense_solve_batched(items)
+            assert sp.sssp_last_status()[0] & 3 == 0
+            busy.stayed()
+            compare(items, refs)
