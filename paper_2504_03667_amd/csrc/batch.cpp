@@ -61,13 +61,11 @@ struct Build {
 // rounds and start first; the shared ones fill the workgroups the gangs leave.
 constexpr int32_t kSharedSources = 32;
 
-// Members of the largest gang that a launch may use by its own choice.  A gang
-// waits for all of its members, and the launch is an ordinary one beside whatever
-// else runs: with up to four launches dispatched at a time (HIP's hardware queues),
-// one of them holds at least a quarter of the compute units, so gangs of at most that
-// many members form.  Beside a server's kernel (`served`), which holds most of the GPU
-// for as long as queries come, there are none: instances that all run at once need the
-// compute units that it holds.
+// Members of the largest gang that a launch may use by its own choice: a quarter of the
+// compute units, which a launch gets also where four (HIP's hardware queues) are
+// dispatched at a time; with fewer the gang is given up (see gang_meet).  Beside a
+// server's kernel (`served`), which holds most of the GPU for as long as queries come,
+// there are none: instances that all run at once need the compute units that it holds.
 int32_t gang_cap(int32_t cus, int32_t served, int32_t nwg) {
     return served > 0 ? 0 : std::max(0, std::min(cus / 4, nwg / 2));
 }
@@ -371,7 +369,7 @@ struct sssp_batch_plan {
 
     hipError_t enqueue(hipStream_t s) {
         return launch_batch(d_items, d_parts, nparts, d_bars, d_arena, flags & SSSP_FLAG_LITERAL,
-                            clock_khz * 10000, d_ctl, nwg, s);
+                            clock_khz * (kGangTimeoutUs / 1000), d_ctl, nwg, s);
     }
 
     int32_t lc_items = 0;
@@ -506,6 +504,7 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     // label-correcting instances have their own split; literal steps are an exchange
     // each, which one workgroup does not need; a captured launch may run beside a
     // server that does not exist yet, whose kernel would keep such gangs from forming
+    // (each would wait for a while, see gang_meet, and then be solved by one workgroup)
     int dev = 0;
     (void)hipGetDevice(&dev);
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
@@ -549,7 +548,7 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     if (e == hipSuccess && b.arena_bytes) e = zero_fill(d_arena, b.arena_bytes, s);
     if (e == hipSuccess)
         e = launch_batch(d_items, d_parts, (int32_t)b.parts.size(), d_bars, d_arena, flags & SSSP_FLAG_LITERAL,
-                         khz * 10000, ctl, nwg, s);
+                         khz * (kGangTimeoutUs / 1000), ctl, nwg, s);
     (void)hipFreeAsync(d_items, s);
     (void)hipFreeAsync(d_parts, s);
     (void)hipFreeAsync(d_bars, s);

@@ -221,8 +221,20 @@ __device__ __forceinline__ SolveStats solve_item(const BatchItem& I, int part, b
 // ---------------------------------------------------------------------------
 // Batched: a grid of workgroups pulls tickets from a counter; each ticket is one
 // part of one item (items are ordered largest first, an item's parts are
-// consecutive tickets, so at most the newest gang is incomplete at a time).
+// consecutive tickets, so at most the newest gang is incomplete at a time).  Whether
+// that gang's other members start depends on what else runs: see gang_meet.
 // ---------------------------------------------------------------------------
+// Ticks that the first part of a gang waits for the others before it solves the item
+// alone: about the time that takes (50 us, and the matrix at 40 GB/s), so that neither
+// choice costs much more than the better one.
+__device__ __forceinline__ long long gang_wait(const BatchItem& I, long long timeout) {
+#ifdef SSSP_STRESS_DELAYS
+    return timeout / kGangTimeoutUs * 10;  // some gangs break
+#else
+    return timeout / kGangTimeoutUs * (50 + (long long)I.n * I.n * I.elem / 40000);
+#endif
+}
+
 template <int T>
 __global__ __launch_bounds__(T) void k_batch(const BatchItem* __restrict__ items, const BatchPart* __restrict__ parts,
                                              int32_t nparts, Bar* __restrict__ bars, char* __restrict__ arena,
@@ -232,16 +244,41 @@ __global__ __launch_bounds__(T) void k_batch(const BatchItem* __restrict__ items
     const bool literal = (flags & kFlagLiteral) != 0;
     const uint32_t epoch = ld_agent(&ctl->epoch);
     for (;;) {
-        if (threadIdx.x == 0)
-            sh.item = (int32_t)__hip_atomic_fetch_add(&ctl->next_item, 1ull, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) {
+            const int32_t t = (int32_t)__hip_atomic_fetch_add(&ctl->next_item, 1ull, __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT);
+            // a gang whose item one workgroup can solve does not wait for members that cannot start
+            bool alone = false;
+            if (t < nparts) {
+                const BatchPart pt = parts[t];
+                const BatchItem& I = items[pt.item];
+                if (I.parts > 1 && I.method == kMethodDijkstra && I.n <= kSingleMax) {
+                    stress_delay(0x6a1u + (uint32_t)t);
+                    alone = !gang_meet(&bars[pt.item].bar, pt.part, (uint32_t)I.parts, gang_wait(I, timeout),
+                                       [] { return (long long)wall_clock64(); },
+                                       [] { __builtin_amdgcn_s_sleep(1); });
+                }
+            }
+            sh.item = alone ? ~t : t;
+        }
         __syncthreads();
-        const int32_t t = sh.item;
+        const int32_t claimed = sh.item;
         __syncthreads();
+        const bool alone = claimed < 0;
+        const int32_t t = alone ? ~claimed : claimed;
         if (t >= nparts) break;
         const BatchPart pt = parts[t];
-        const BatchItem I = items[pt.item];
+        BatchItem I = items[pt.item];
+        const int32_t members = I.parts;
+        if (alone) {
+            if (pt.part != 0) {
+                if (threadIdx.x == 0) gang_leave(&bars[pt.item], (uint32_t)members);
+                continue;
+            }
+            I.parts = 1;
+        }
         const SolveStats st = solve_item<T>(I, pt.part, literal, timeout, bars ? &bars[pt.item] : nullptr, arena, epoch);
+        if (alone && threadIdx.x == 0) gang_leave(&bars[pt.item], (uint32_t)members);
         total.status |= st.status;
         if (pt.part == 0) {  // every gang member computes the same counts; count them once
             total.rounds += st.rounds;

@@ -360,6 +360,33 @@ __device__ __forceinline__ bool gang_leave(Bar* bw, uint32_t members) {
     return true;
 }
 
+// Members of a gang come together (a batched launch, before they solve).  Each counts
+// itself in *word (0 before).  Other work, on other streams, can keep some of a gang's
+// workgroups from starting for as long as it runs, and itself wait for the compute
+// units that the others hold; so the first part, whose ticket comes before the others',
+// gives up after `limit`: it marks the gang broken and solves the item alone, and a
+// member that finds the mark leaves.  True: all `members` are here, each on the GPU.
+// (One thread of each member calls it; a member's own wait ends because part 0, which
+// runs when any of them does, either sees them all or breaks the gang.)
+constexpr uint32_t kGangBroken = 0x80000000u;
+template <class Now, class Pause>
+__host__ __device__ inline bool gang_meet(uint32_t* word, int32_t part, uint32_t members, long long limit, Now now,
+                                          Pause pause) {
+    uint32_t v = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+    const long long t0 = now();
+    while (v < members) {  // a mark makes it larger
+        if (part == 0 && now() - t0 >= limit) {
+            if (__hip_atomic_compare_exchange_strong(word, &v, v | kGangBroken, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT))
+                return false;
+            continue;
+        }
+        pause();
+        v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return (v & kGangBroken) == 0;
+}
+
 // The last workgroup of a launch publishes the launch's statistics and resets
 // the barrier words, the ticket counter and the accumulators for the next launch.
 __device__ __forceinline__ void finish_launch(Ctl* ctl, const SolveStats& st, bool add_stats) {

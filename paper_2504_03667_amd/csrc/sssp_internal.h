@@ -160,6 +160,8 @@ struct BatchPart {
     int32_t part;
 };
 
+// timeout: ticks of kGangTimeoutUs, the wait limit of a gang's exchanges.
+constexpr long long kGangTimeoutUs = 10000000;
 hipError_t launch_batch(const BatchItem* items, const BatchPart* parts, int32_t nparts, Bar* bars, char* arena,
                         uint32_t flags, long long timeout, Ctl* ctl, int nwg, hipStream_t s);
 int batch_occupancy(int* per_cu);

@@ -146,3 +146,45 @@ def test_one_shot_batch(sp, held):
             assert sp.sssp_last_status()[0] & 3 == 0
             busy.stayed()
             compare(items, refs)
+
+
+def test_plan_with_gangs_larger_than_what_is_free(sp):
+    """Made while the GPU is free; a gang that cannot form is given up, and one workgroup
+    solves its item.  Both kinds of matrices, and launches before and after."""
+    items, refs = batch(np.random.default_rng(8), [40, 900, 1500, 2000, 2000])
+    for flags in (0, sp.SSSP_FLAG_COMPACT):
+        with sp.BatchPlan(items, flags, single_max_n=64, gang_columns=16) as plan:
+            assert plan.info()["max_parts"] > 64
+            plan.launch()
+            compare(items, refs)
+            busy = Busy(sp, 192)
+            with busy.srv:
+                for _ in range(3):
+                    busy.touch()
+                    plan.launch()
+                    assert plan.status()[0] & 3 == 0
+                    busy.stayed()
+                    compare(items, refs)
+            plan.launch()
+            assert plan.status()[0] & 3 == 0
+            compare(items, refs)
+
+
+def test_batches_beside_whole_gpu_solves(sp):
+    """On two streams at once: split batches and solves that need all of their workgroups."""
+    rng = np.random.default_rng(9)
+    items, refs = batch(rng, [300, 1500, 2500, 4000, 6000])
+    n = 6000
+    W = random_dense(rng, n, 0.01, 1, 100)
+    dr, pr, _ = oracle.dijkstra(W, 5)
+    Wt = torch.from_numpy(W).cuda()
+    d, p = (torch.full((n,), -9, dtype=torch.int32, device="cuda") for _ in range(2))
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(30):
+        sp.sssp_dense_solve_batched(items, stream=a)
+        sp.sssp_dense_solve_ex(Wt, n, n, 5, d, p, 0, stream=b)
+    assert sp.sssp_last_status(stream=a)[0] & 3 == 0
+    assert sp.sssp_last_status(stream=b)[0] & 3 == 0
+    compare(items, refs)
+    assert np.array_equal(d.cpu().numpy(), dr) and np.array_equal(p.cpu().numpy(), pr)
