@@ -521,6 +521,10 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     BatchPart* d_parts = nullptr;
     Bar* d_bars = nullptr;
     char* d_arena = nullptr;
+    auto give_back = [&] {
+        for (void* p : {(void*)d_items, (void*)d_parts, (void*)d_bars, (void*)d_arena})
+            if (p) (void)hipFreeAsync(p, s);
+    };
     hipError_t e = hipSuccess;
     for (;;) {
         b = Build();
@@ -538,7 +542,10 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     if (e == hipSuccess) e = hipMallocAsync((void**)&d_items, sizeof(BatchItem) * b.items.size(), s);
     if (e == hipSuccess) e = hipMallocAsync((void**)&d_parts, sizeof(BatchPart) * b.parts.size(), s);
     if (e == hipSuccess) e = hipMallocAsync((void**)&d_bars, sizeof(Bar) * b.items.size(), s);
-    if (e != hipSuccess) return err(SSSP_ENOMEM, "hipMallocAsync(batch): %s", hipGetErrorString(e));
+    if (e != hipSuccess) {
+        give_back();
+        return err(SSSP_ENOMEM, "hipMallocAsync(batch): %s", hipGetErrorString(e));
+    }
     e = hipMemcpyAsync(d_items, b.items.data(), sizeof(BatchItem) * b.items.size(), hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(d_parts, b.parts.data(), sizeof(BatchPart) * b.parts.size(), hipMemcpyHostToDevice, s);
@@ -549,10 +556,7 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     if (e == hipSuccess)
         e = launch_batch(d_items, d_parts, (int32_t)b.parts.size(), d_bars, d_arena, flags & SSSP_FLAG_LITERAL,
                          khz * (kGangTimeoutUs / 1000), ctl, nwg, s);
-    (void)hipFreeAsync(d_items, s);
-    (void)hipFreeAsync(d_parts, s);
-    (void)hipFreeAsync(d_bars, s);
-    if (d_arena) (void)hipFreeAsync(d_arena, s);
+    give_back();
     if (e != hipSuccess) return hip_err(e, "batched launch");
     return SSSP_OK;
 }

@@ -21,7 +21,6 @@ struct Launch {
     int nwg = 0;
 };
 static Launch last;
-static size_t items_bytes = 0;
 
 #define CHECK(c)                                                        \
     do {                                                                \
@@ -117,10 +116,30 @@ static void beside_a_server() {
     CHECK(held.empty());
 }
 
-int main(int argc, char** argv) {
-    (void)argc;
-    (void)argv;
+// Every allocation of the call fails in turn: what was taken before is given back.  Where
+// there is no room for the gangs' exchange memory, the call solves without gangs.
+static void short_of_memory() {
+    const std::vector<int32_t> sizes = {6000, 3000, 500};
+    CHECK(solve(sizes) == SSSP_OK && held.empty());
+    const int all = allocations;
+    CHECK(all == 4);
+    for (fail_at = 1; fail_at <= all; ++fail_at) {
+        const int rc = solve(sizes);
+        CHECK(rc == (fail_at == 1 ? SSSP_OK : SSSP_ENOMEM));
+        CHECK(held.empty());
+    }
+    fail_at = 0;
+    fail_above = 4096;
+    CHECK(solve(sizes) == SSSP_OK && max_parts() == 1);
+    CHECK(held.empty());
+    fail_above = 0;
+    CHECK(solve(sizes) == SSSP_ENOMEM && held.empty());
+    fail_above = ~size_t(0);
+}
+
+int main() {
     beside_a_server();
+    short_of_memory();
     if (failures) return 1;
     std::printf("batch host ok\n");
     return 0;
