@@ -101,3 +101,19 @@ def test_ranges_much_narrower_than_the_paths_edges(sp):
     ev = np.concatenate([ev, c + 1, hub])
     ew = np.concatenate([ew, rng.integers(10 ** 5, 10 ** 6, size=chain - 1), rng.integers(1, 10 ** 6, size=hub.size)])
     check(sp, eu, ev, ew, n)
+
+
+@pytest.mark.parametrize("workgroups", [1, 2, 3])
+@pytest.mark.parametrize("spread", [1, 7, 64])
+def test_appends_of_one_workgroup_beyond_the_buffer(sp, spread, workgroups):
+    """Lists of 20 entries on average (no workgroup runs alone): sweeps that append many
+    times what fits the buffer, by waves whose appends end, begin or lie beyond it."""
+    width, fan = 5 * CAP // spread, spread
+    a = 1 + np.arange(width)
+    b = 1 + width + np.arange(width * fan)
+    n = 1 + width + width * fan
+    pad = 20 * n
+    eu = np.concatenate([np.zeros(width, int), np.repeat(a, fan), np.full(pad, n - 1)])
+    ev = np.concatenate([a, b, np.full(pad, 0)])
+    ew = np.concatenate([1 + np.arange(width) % 7, 1 + np.arange(width * fan) % 3, np.full(pad, 9)])
+    check(sp, eu, ev, ew, n, workgroups=workgroups)
