@@ -495,6 +495,18 @@ __device__ __forceinline__ bool close_team(CsrCtl* cc, uint32_t rank, uint32_t a
     return size != 0;
 }
 
+// Number of this wave in the team, neighbours in different workgroups: long lists of
+// vertices whose indices are close, in the passes over all of them, and a frontier handed
+// back for its long lists are then spread over the compute units.  (Other sweeps take
+// neighbours in one workgroup, as they have their heads in common and few workgroups'
+// appends to gather: a torus of 10^6 vertices 6.4 ms against 7.8.)
+__device__ __forceinline__ int64_t team_wave(uint32_t rank, uint32_t nwg) {
+    return (int64_t)(threadIdx.x / kWave) * nwg + rank;
+}
+__device__ __forceinline__ int64_t team_thread(uint32_t rank, uint32_t nwg) {
+    return team_wave(rank, nwg) * kWave + (threadIdx.x & (kWave - 1));
+}
+
 // Does tail u (dist du) reach head v (dist dv) over an edge of weight wt on a
 // shortest path?  Both finite, du + wt == dv (both below 2^31: no wrap).
 __device__ __forceinline__ bool tight(uint32_t du, uint32_t dv, int32_t wt) {
@@ -519,7 +531,9 @@ __device__ __forceinline__ bool tight(uint32_t du, uint32_t dv, int32_t wt) {
 // 8 edges a step: n=10^6 1094 us against 966).  Small ones (half of the sweeps or
 // more) are left to workgroup 0, which keeps them in LDS and needs no grid barrier
 // between them; the others wait at the barrier that ends its run.  Where lists are
-// long on average one workgroup would take longer over them than the barriers take.
+// long on average one workgroup would take longer over them than the barriers take, and
+// a vertex of a long list it leaves to all: it joins the frontier that is handed back
+// (400 lists of 5000 entries reached at once: 2.7 ms, with workgroup 0 alone 12.3).
 // Large graphs take a range of distances at a time: vertices lowered to thr or
 // above are not relaxed yet, and when the frontier is empty a scan of the labels
 // gathers those of the next range (nothing below the old threshold is left to
@@ -532,10 +546,14 @@ constexpr uint32_t kRangeFew = 256;  // vertices of a range below which the next
                                      // misjudges a graph whose paths are not made of its typical edges
 constexpr uint32_t kSoloFrontier = 512;  // n=10000: 256 209 us, 512 212, 768 215, 1536 253
 constexpr int64_t kSoloDegree = 16;     // only if the lists are this short on average
+constexpr int64_t kSoloList = 64;       // ... and of a vertex that workgroup 0 relaxes: longer lists it hands back
+constexpr uint32_t kWide = 0x80000000u;  // mark of a frontier handed back for that (the next sweep is everybody's)
 constexpr uint32_t kAppendCap = 4096;   // entries gathered in LDS
 
 struct SweepLds {
     uint32_t buf[kAppendCap];
+    uint32_t longs[kSoloFrontier];
+    uint32_t nlong[2];
     uint32_t fill[2];
     uint32_t base;
     uint32_t rest;
@@ -576,13 +594,15 @@ __device__ __forceinline__ void append(uint32_t want, const int32_t (&v)[B], uin
 }
 
 // One sweep over frontier entries entry(i), i < F, by the waves wave, wave + waves, ...
+// With `longs`, vertices whose lists are longer than kSoloList are put there (*nlong
+// counts them) and not relaxed.
 template <int G, int B, bool Filter, class Entry, class Tail, class Value>
 __device__ __forceinline__ void sweep_frontier(Entry entry, uint32_t F, int64_t wave, int64_t waves, uint32_t* buf,
                                                uint32_t room, uint32_t* fill, uint32_t* __restrict__ over,
                                                uint32_t* __restrict__ over_count, uint64_t* __restrict__ lab,
                                                const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                                                const int32_t* __restrict__ w, uint32_t tag, uint32_t thr, Tail& tail,
-                                               Value& value) {
+                                               Value& value, uint32_t* longs = nullptr, uint32_t* nlong = nullptr) {
     const int lane = threadIdx.x & (kWave - 1);
     const int sub = lane % G;
     const int64_t per_wave = kWave / G;
@@ -596,6 +616,11 @@ __device__ __forceinline__ void sweep_frontier(Entry entry, uint32_t F, int64_t 
             tv = tail(u);
             e = row_ptr[u] + sub;
             e1 = row_ptr[u + 1];
+            if (longs && e1 - e > kSoloList - sub) {
+                if (sub == 0)
+                    longs[__hip_atomic_fetch_add(nlong, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = (uint32_t)u;
+                e = e1;
+            }
         }
         while (__ballot(e < e1)) {
             int32_t v[B];
@@ -671,11 +696,12 @@ __device__ bool frontier_sweeps(uint32_t rank, uint32_t& nwg, long long team_lim
     const uint32_t solo = row_ptr[n] <= kSoloDegree * n ? kSoloFrontier : 0u;
     uint32_t thr = delta, tag = 0, ph = 0, scans = 0;
     nwg = 0;
-    if (threadIdx.x < 2) sl.fill[threadIdx.x] = 0;
+    if (threadIdx.x < 2) sl.fill[threadIdx.x] = sl.nlong[threadIdx.x] = 0;
     __syncthreads();
+    bool wide = false;
     for (;;) {
         while (F) {
-            if (F <= solo || nwg == 0) {
+            if ((F <= solo && !wide) || nwg == 0) {
                 if (rank == 0 && F <= solo) {
                     constexpr uint32_t half = kAppendCap / 2;
                     uint32_t* cur = sl.buf;
@@ -683,7 +709,7 @@ __device__ bool frontier_sweeps(uint32_t rank, uint32_t& nwg, long long team_lim
                     for (uint32_t i = threadIdx.x; i < F; i += blockDim.x)
                         cur[i] = ld_agent(&lists[(size_t)ph * n + i]);
                     __syncthreads();
-                    uint32_t k = 0;
+                    uint32_t k = 0, L = 0;
                     bool hand_back = false;
                     const long long t_solo = wall_clock64();
                     do {
@@ -693,11 +719,22 @@ __device__ bool frontier_sweeps(uint32_t rank, uint32_t& nwg, long long team_lim
                         uint32_t* fill = &sl.fill[k & 1];
                         sweep_frontier<4, 2, false>([&](uint32_t i) { return cur[i]; }, F, threadIdx.x / kWave, wgwaves,
                                                     nxt, half, fill, lists, nullptr, lab, row_ptr, col, w, tag, thr,
-                                                    tail, value);
+                                                    tail, value, sl.longs, &sl.nlong[k & 1]);
                         __syncthreads();
                         F = *fill;
+                        L = sl.nlong[k & 1];
+                        if (L && (uint64_t)F + L > (uint64_t)n) {
+                            // no room in a list of n for vertices that may be in it twice
+                            __syncthreads();
+                            sweep_frontier<4, 2, false>([&](uint32_t i) { return sl.longs[i]; }, L,
+                                                        threadIdx.x / kWave, wgwaves, nxt, half, fill, lists, nullptr,
+                                                        lab, row_ptr, col, w, tag, thr, tail, value);
+                            __syncthreads();
+                            F = *fill;
+                            L = 0;
+                        }
                         if (threadIdx.x == 0) {
-                            sl.fill[(k & 1) ^ 1] = 0;
+                            sl.fill[(k & 1) ^ 1] = sl.nlong[(k & 1) ^ 1] = 0;
                             // the waiting workgroups' limit must not be reached by a run of slow
                             // sweeps (vertices of very long lists) that each stay below it
                             sl.base = wall_clock64() - t_solo > timeout / 4 ? 1u : 0u;
@@ -706,13 +743,16 @@ __device__ bool frontier_sweeps(uint32_t rank, uint32_t& nwg, long long team_lim
                         cur = nxt;
                         nxt = t;
                         __syncthreads();
-                        hand_back = sl.base != 0;
+                        hand_back = sl.base != 0 || L != 0;
                         ++k;
                     } while (F && F <= solo && !hand_back);
                     // the frontier into list 0 (what did not fit LDS is there already)
                     for (uint32_t i = threadIdx.x; i < min(F, half); i += blockDim.x) st_agent(&lists[i], cur[i]);
+                    for (uint32_t i = threadIdx.x; i < L; i += blockDim.x) st_agent(&lists[F + i], sl.longs[i]);
+                    F = (F + L) | (L ? kWide : 0u);
+                    __syncthreads();
                     if (threadIdx.x == 0) {
-                        sl.fill[0] = sl.fill[1] = 0;
+                        sl.fill[0] = sl.fill[1] = sl.nlong[0] = sl.nlong[1] = 0;
                         st_agent(&count[1], 0u);
                         st_agent(&count[2], 0u);
                         st_agent(&cc->solo_tag, tag);
@@ -726,9 +766,13 @@ __device__ bool frontier_sweeps(uint32_t rank, uint32_t& nwg, long long team_lim
                     return false;
                 }
                 if (solo) tag = ld_agent(&cc->solo_tag);
+                wide = (F & kWide) != 0;
+                F &= ~kWide;
                 ph = 0;
                 continue;
             }
+            const int64_t at = wide ? team_wave(rank, nwg) : wave;
+            wide = false;
             const uint32_t nx = ph == 2 ? 0 : ph + 1, old = nx == 2 ? 0 : nx + 1;
             ++sweeps;
             rows += F;
@@ -741,7 +785,7 @@ __device__ bool frontier_sweeps(uint32_t rank, uint32_t& nwg, long long team_lim
                 sweep_frontier<8, 2, true>(entry, F, wave, waves, sl.buf, kAppendCap, &sl.fill[0], next, &count[nx],
                                            lab, row_ptr, col, w, tag, thr, tail, value);
             else
-                sweep_frontier<16, 1, false>(entry, F, wave, waves, sl.buf, kAppendCap, &sl.fill[0], next, &count[nx],
+                sweep_frontier<16, 1, false>(entry, F, at, waves, sl.buf, kAppendCap, &sl.fill[0], next, &count[nx],
                                             lab, row_ptr, col, w, tag, thr, tail, value);
             flush_appends(sl, next, &count[nx]);
             if (!csr_barrier(cc, ++b, nwg, timeout, &count[nx], &F)) return false;
@@ -843,7 +887,7 @@ __device__ bool zero_tie_pred(uint32_t rank, uint32_t nwg, const int64_t* __rest
                               uint32_t& b, long long timeout, int32_t* __restrict__ dist,
                               int32_t* __restrict__ pred, Red<T>& red) {
     __shared__ uint32_t claim;
-    const int64_t gtid = (int64_t)rank * T + threadIdx.x;
+    const int64_t gtid = team_thread(rank, nwg);
     const int64_t gsz = (int64_t)nwg * T;
     const uint32_t hmask = (uint32_t)((1ull << zt.hbits) - 1ull);
     auto D = [&](int64_t v) { return label_value(ld_agent(&lab[v])); };
@@ -1045,7 +1089,7 @@ __global__ __launch_bounds__(T) void k_csr_lc(const int64_t* __restrict__ row_pt
             c = du + (uint32_t)wt;  // both < 2^31: no wrap
             return c < kInf;        // longer than INT32_MAX - 1: not representable
         });
-    const int64_t gtid = (int64_t)rank * T + threadIdx.x;
+    const int64_t gtid = team_thread(rank, nwg);
     const int64_t gsz = (int64_t)nwg * T;
     uint32_t zero = 0;
     if (ok) {

@@ -117,3 +117,35 @@ def test_appends_of_one_workgroup_beyond_the_buffer(sp, spread, workgroups):
     ev = np.concatenate([a, b, np.full(pad, 0)])
     ew = np.concatenate([1 + np.arange(width) % 7, 1 + np.arange(width * fan) % 3, np.full(pad, 9)])
     check(sp, eu, ev, ew, n, workgroups=workgroups)
+
+
+@pytest.mark.parametrize("length", [63, 64, 65, 66, 300])
+@pytest.mark.parametrize("hubs", [1, 7, SOLO - 1, SOLO])
+def test_long_lists_in_a_short_frontier(sp, hubs, length):
+    """The source reaches `hubs` vertices, each of them `length` others (shared by two
+    hubs), those a common end: lists that workgroup 0 relaxes and lists that it hands back,
+    beside short ones, in a graph whose lists are short on average."""
+    h = 1 + np.arange(hubs)
+    leaves = hubs * length // 2 + length
+    first = 1 + hubs
+    leaf = first + np.arange(leaves)
+    end = first + leaves
+    eu = np.concatenate([np.zeros(hubs, int), np.repeat(h, length), leaf])
+    ev = np.concatenate([h, (first + (np.repeat((h - 1) * length // 2, length) + np.tile(np.arange(length), hubs))),
+                         np.full(leaves, end)])
+    ew = np.concatenate([1 + np.arange(hubs) % 5, 1 + np.arange(hubs * length) % 4, 9 - np.arange(leaves) % 9])
+    mixed = np.arange(0, hubs, 3) + 1  # every third hub has a short list
+    keep = ~(np.isin(eu, mixed) & (ev >= first + 5) & (hubs > 1)) | (eu >= first)
+    check(sp, eu[keep], ev[keep], ew[keep], end + 1)
+    check(sp, eu, ev, ew, end + 1)
+
+
+@pytest.mark.parametrize("n", [300, 505, SOLO, SOLO + 2])
+def test_hubs_where_every_vertex_is_lowered_in_every_sweep(sp, n):
+    """Frontiers of all vertices, long lists among them: together more than a list holds."""
+    v = np.arange(1, n)
+    hubs = np.arange(40, 40 + 5)
+    eu = np.concatenate([np.zeros(n - 1, int), v[1:], np.repeat(hubs, 70)])
+    ev = np.concatenate([v, v[1:] - 1, np.tile(100 + np.arange(70), hubs.size)])
+    ew = np.concatenate([10 ** 6 - 2 * v, np.ones(n - 2, int), np.full(70 * hubs.size, 10 ** 6)])
+    check(sp, eu, ev, ew, n)
