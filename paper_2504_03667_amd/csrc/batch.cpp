@@ -70,23 +70,36 @@ int32_t gang_cap(int32_t cus, int32_t served, int32_t nwg) {
     return served > 0 ? 0 : std::max(0, std::min(cus / 4, nwg / 2));
 }
 
-// Columns per member (and largest n solved by one workgroup) that split a set of
-// instances so that all their workgroups run at once: the narrowest of 64 to 4096
-// whose parts, at most `cap` an instance, fit the nwg workgroups, or 0 when not even
-// 4096 does or gangs are not allowed (then the instances fill the GPU one workgroup
-// each).  A compute unit alone streams rows at 25 to 60 GB/s, so few instances on
-// one workgroup each leave most of the memory's 7 TB/s idle: 24 graphs of up to
-// 6000 vertices 2.6 ms, split 0.57.
-int32_t concurrent_columns(const sssp_instance* inst, int32_t count, int32_t nwg, int32_t cap) {
+// Largest n that a one-shot call solves by one workgroup where it splits the others into
+// slices of c columns: one of more vertices makes a gang of at least three.  A round of a
+// gang takes 3 us, from slices of more than 256 columns on 5; one workgroup's takes 1.8
+// (n=1000) to 3.6 (n=4000) and streams rows at 25 to 60 GB/s.  So smaller graphs and gangs
+// of two lose where the rounds are many, and win little where the rows are dense (16 to 96
+// graphs, all split against all alone, of 950 rounds and of 13: n=1000 1.6 and 0.83,
+// n=2000 c=1024 2.2 and 0.88, n=4000 c=2048 1.9 and 0.81, c=1024 1.6 and 0.48, c=256 0.94
+// and 0.22).
+int32_t alone_max_n(int32_t c) { return std::max(1024, 2 * c); }
+
+// Columns per member that split a set of instances so that all their workgroups run at
+// once: the narrowest of 64 to 4096 whose parts, at most `cap` an instance, fit the nwg
+// workgroups, or 0 when not even 4096 does, gangs are not allowed or nothing is split
+// (then the instances fill the GPU one workgroup each).  A compute unit alone streams rows
+// at 25 to 60 GB/s, so few instances on one workgroup each leave most of the memory's
+// 7 TB/s idle: 24 graphs of up to 6000 vertices 2.6 ms, split 0.53.  `alone`: the largest
+// n that is not split, by c.
+template <class Alone>
+int32_t concurrent_columns(const sssp_instance* inst, int32_t count, int32_t nwg, int32_t cap, Alone alone) {
     if (cap < 2) return 0;
     for (int32_t c = 64; c <= 4096; c *= 2) {
         int64_t parts = 0;
-        bool fits = true;
+        bool fits = true, split = false;
         for (int32_t i = 0; i < count && parts <= nwg; ++i) {
-            parts += std::min<int64_t>(((int64_t)inst[i].n + c - 1) / c, cap);
+            const bool gang = inst[i].n > alone(c);
+            parts += gang ? std::min<int64_t>(((int64_t)inst[i].n + c - 1) / c, cap) : 1;
             fits = fits && (int64_t)inst[i].n <= (int64_t)cap * max_batch_slice();
+            split = split || gang;
         }
-        if (fits && parts <= nwg) return c;
+        if (fits && parts <= nwg) return split ? c : 0;
     }
     return 0;
 }
@@ -514,7 +527,7 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     }
     const int32_t cap = gang_cap(cus, served_workgroups(dev), nwg);
     int32_t cols = flags & (SSSP_FLAG_LABEL_CORRECTING | SSSP_FLAG_LITERAL) || capturing != hipStreamCaptureStatusNone
-                       ? 0 : concurrent_columns(inst, count, nwg, cap);
+                       ? 0 : concurrent_columns(inst, count, nwg, cap, alone_max_n);
     // stream-ordered scratch: allocated and freed in the stream's order, so the
     // call stays asynchronous (copies from pageable memory are staged at once)
     BatchItem* d_items = nullptr;
@@ -528,7 +541,7 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     hipError_t e = hipSuccess;
     for (;;) {
         b = Build();
-        rc = build(inst, src.data(), count, cols ? cols : max_batch_single_n(), cols ? cols : 4096,
+        rc = build(inst, src.data(), count, cols ? alone_max_n(cols) : max_batch_single_n(), cols ? cols : 4096,
                    cols ? cap : std::max(2, nwg / 2), &b,
                    lc.empty() ? nullptr : lc.data(), nullptr, 0, 0, nullptr, cols != 0);
         if (rc) return rc;
@@ -661,7 +674,7 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
         int dev = 0;
         (void)hipGetDevice(&dev);
         p->gang_max = gang_cap(cus, served_workgroups(dev), p->nwg);
-        if (const int32_t c0 = concurrent_columns(inst, count, p->nwg, p->gang_max))
+        if (const int32_t c0 = concurrent_columns(inst, count, p->nwg, p->gang_max, [](int32_t c) { return c; }))
             for (int32_t c : {c0, 2 * c0, 4 * c0})
                 if (c <= 4096 && c < nmax) cands.push_back(Cand{c, c, true});
     }

@@ -740,25 +740,10 @@ __device__ __forceinline__ void clear_merge(uint64_t* mrg, int n64) {
     for (int i = threadIdx.x; i < n64; i += T) mrg[i] = kNoKey;
 }
 
-// Minimum of key and OR of flags over the slice owners (the first L threads,
-// partition 0); valid in the owners.  Threads that are not owners must pass
-// kNoKey / 0.  When the owners fit in wave 0 this is a wave reduction with no
-// workgroup barrier (and only wave 0 takes part); otherwise a block reduction
-// that every thread must enter.
-template <int T>
-__device__ __forceinline__ void owner_min_or(uint64_t& key, uint32_t& flags, int L, Red<T>& red) {
-    if (L <= kWave) {
-        if (threadIdx.x < kWave) {
-            key = wave_min64(key);
-            flags = wave_or32(flags);
-        }
-        return;
-    }
-    block_min_or<T>(key, flags, red);
-}
-
-// Exclusive prefix sum over the owners (same rules as owner_min_or); `total`
-// gets the sum.
+// Exclusive prefix sum over the slice owners (the first L threads, partition 0); valid
+// in the owners, `total` gets the sum.  Threads that are not owners must pass 0.  When
+// the owners fit in wave 0 this is a wave scan with no workgroup barrier (and only wave
+// 0 takes part); otherwise a block scan that every thread must enter.
 template <int T>
 __device__ __forceinline__ uint32_t owner_excl_scan(uint32_t x, uint32_t& total, int L, Red<T>& red) {
     if (L <= kWave) {

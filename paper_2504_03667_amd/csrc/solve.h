@@ -476,29 +476,55 @@ __device__ __forceinline__ void publish(const uint32_t (&cand)[G][4], const Layo
         return;
     }
     if (NARROW) return;
-    uint64_t key = kNoKey;
-    if (lo.r == 0) {
+    // the owners are whole waves: each finds its minimum, two workgroup barriers tell the
+    // slice's and the entries before each wave's (sh.min3[0] is all ones before: thread 0
+    // sets it back before the barrier of the exchange)
+    const bool owners = threadIdx.x < (unsigned)lo.L;
+    if (owners) {
+        uint32_t dmin = 0xffffffffu;
 #pragma unroll
         for (int k = 0; k < G; ++k)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                key = umin64(key, make_key(cand[k][j], (uint32_t)(col0 + local_col(lo, k, j))));
-    }
-    uint32_t none = 0;
-    owner_min_or<T>(key, none, lo.L, sh.red);
-    const uint32_t dmin = (uint32_t)(key >> 32);
-    uint32_t mask = 0;
-    if (lo.r == 0 && dmin < kInf) {
+            for (int j = 0; j < 4; ++j) dmin = min(dmin, cand[k][j]);
+        dmin = wave_min32(dmin);
+        uint32_t low = ~0u;
 #pragma unroll
-        for (int k = 0; k < G; ++k)
+        for (int k = G - 1; k >= 0; --k)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (cand[k][j] == dmin) mask |= 1u << (4 * k + j);
+            for (int j = 3; j >= 0; --j)
+                if (cand[k][j] == dmin) low = (uint32_t)local_col(lo, k, j);
+        low = wave_min32(low);
+        if (wave_lane() == 0)
+            __hip_atomic_fetch_min(&sh.min3[0], make_key(dmin, low), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    uint32_t total = 0;
-    uint32_t rank = owner_excl_scan<T>(__popc(mask), total, lo.L, sh.red);
-    if (entries) {
+    __syncthreads();
+    const uint64_t key = sh.min3[0];
+    const uint32_t dmin = scalar((uint32_t)(key >> 32));
+    uint32_t mask = 0, inc = 0;
+    if (owners) {
+        if (dmin < kInf) {
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (cand[k][j] == dmin) mask |= 1u << (4 * k + j);
+        }
+        inc = wave_prefix32((uint32_t)__popc(mask));
+        if (wave_lane() == kWave - 1) sh.red.b[threadIdx.x / kWave] = inc;
+    }
+    __syncthreads();
+    const int w = threadIdx.x / kWave, waves = lo.L / kWave;
+    uint32_t total = 0, before = 0;
+    if (owners) {
+        for (int i = 0; i < waves; ++i) {
+            const uint32_t c = sh.red.b[i];
+            before += i < w ? c : 0u;
+            total += c;
+        }
+    }
+    if (entries && mask) {
         stress_delay(2u * tag + 1u);
+        uint32_t rank = before + inc - (uint32_t)__popc(mask);
 #pragma unroll
         for (int k = 0; k < G; ++k)
 #pragma unroll
@@ -508,8 +534,9 @@ __device__ __forceinline__ void publish(const uint32_t (&cand)[G][4], const Layo
     }
     if (threadIdx.x == 0) {
         stress_delay(2u * tag);
-        st_agent(&rec[kRecRest], rec_rest(tag, (uint32_t)key, total, fused && dmin == d ? 1u : 0u));
+        st_agent(&rec[kRecRest], rec_rest(tag, (uint32_t)col0 + (uint32_t)key, total, fused && dmin == d ? 1u : 0u));
         st_agent(&rec[kRecDist], tag_word(tag, dmin));
+        sh.min3[0] = kNoKey;
     }
 }
 
@@ -836,6 +863,7 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
     const Pub* stamps1 = gw.pubs + (size_t)(b0 & 1) * nwg;
     if (threadIdx.x == 0) sh.stage_late = 0u;
     if (threadIdx.x < 3) sh.open3[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) sh.min3[0] = kNoKey;
     if (threadIdx.x == 0) sh.listed = 0u;
     if (threadIdx.x < 4 * kSparseGroups) sh.sparse[threadIdx.x] = kNoKey;
     __atomic_signal_fence(__ATOMIC_SEQ_CST);

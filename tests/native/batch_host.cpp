@@ -116,6 +116,26 @@ static void beside_a_server() {
     CHECK(held.empty());
 }
 
+// Small graphs are solved by one workgroup, and so are those of which the others' slices
+// would make a gang of two; all workgroups of a split launch run at once.
+static void sizes_that_are_split() {
+    for (int n : {1, 64, 65, 1000, 1024}) {
+        CHECK(solve({n}) == SSSP_OK && max_parts() == 1);
+        CHECK(solve({n, n, 6000}) == SSSP_OK && max_parts() > 1);
+        for (const BatchItem& it : last.items) CHECK((it.n == n) == (it.parts == 1));
+    }
+    for (int n : {1025, 2049, 4097, 6001, 16384}) CHECK(solve({n}) == SSSP_OK && max_parts() > 1);
+    for (int count = 1; count <= 300; ++count)
+        for (int n : {1025, 1500, 2048, 2049, 4000, 4100, 6000, 9000}) {
+            CHECK(solve(std::vector<int32_t>(count, n)) == SSSP_OK);
+            CHECK(max_parts() == 1 || (max_parts() >= 3 && last.parts.size() <= 256));
+            CHECK(max_parts() == 1 || last.items[0].S * (max_parts() - 1) < n);
+        }
+    CHECK(solve(std::vector<int32_t>(96, 2000)) == SSSP_OK && max_parts() == 1);
+    CHECK(solve(std::vector<int32_t>(48, 2000)) == SSSP_OK && max_parts() > 1);
+    CHECK(held.empty());
+}
+
 // Every allocation of the call fails in turn: what was taken before is given back.  Where
 // there is no room for the gangs' exchange memory, the call solves without gangs.
 static void short_of_memory() {
@@ -139,6 +159,7 @@ static void short_of_memory() {
 
 int main() {
     beside_a_server();
+    sizes_that_are_split();
     short_of_memory();
     if (failures) return 1;
     std::printf("batch host ok\n");

@@ -59,3 +59,27 @@ def test_one_shot_and_plan(sp, sizes, copies):
                 status, stats = plan.status()
                 assert status & 3 == 0
                 check(("plan", flags), stats)
+
+
+@pytest.mark.parametrize("sizes,copies", [([1025], 1), ([1026, 1025], 2), ([2049], 40), ([4100, 300, 1500], 5),
+                                          ([5001], 30), ([6001, 1024], 16), ([9000], 3)])
+def test_one_shot_splits(sp, sizes, copies):
+    """Gangs of the one-shot call: slices of 64 to 2048 columns whose last is partial,
+    beside instances that are not split; few rounds and many; zero weights."""
+    rng = np.random.default_rng(sum(sizes) * copies)
+    items, refs = [], []
+    for n in sizes:
+        for p, hi, zero in ((0.05, 30, 0.0), (5.0 / n, 1000, 0.02)):
+            W = random_dense(rng, n, p, 1, hi, zero_prob=zero)
+            Wt, want = torch.from_numpy(W).cuda(), {}
+            for _ in range(copies):
+                s = int(rng.integers(0, 5))
+                want[s] = want.get(s) or oracle.dijkstra(W, s)
+                items.append((Wt, s, *(torch.full((n,), -9, dtype=torch.int32, device="cuda") for _ in range(2))))
+                refs.append(want[s])
+    sp.sssp_dense_solve_batched(items)
+    status, stats = sp.sssp_last_status()
+    assert status & 3 == 0
+    for (_, s, d, p), (dr, pr, _) in zip(items, refs):
+        assert np.array_equal(d.cpu().numpy(), dr) and np.array_equal(p.cpu().numpy(), pr), (d.numel(), s)
+    assert stats[1] == sum(r for _, _, r in refs)
