@@ -168,7 +168,7 @@ __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld
         const long long t_round = trace ? wall_clock64() : 0;
         const bool step = literal || redo;
         const uint32_t bucket = settle(cs, d, step, step ? owner_bit(lo, (int64_t)u0, n) : 0u);
-        if (!step && sparse_round(ng, M, lo.P)) {
+        if (!step && sparse_round(ng, M, lo.P, ~0u)) {
             list_groups<T, G>(cs.x, d, wmin, lo, sh);
             for (uint32_t i = 0; i < ng; ++i)
                 stream_sparse<T, E, false>(W, ld, 0, n, 4 * (int)sh.group[i], (int)M,
@@ -906,7 +906,7 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
             if (late) sh.stage_late = 1u;
         };
         const uint32_t C = (M + kCap - 1) / kCap;
-        const bool sparse = !step && sparse_round(ng, M, lo.P);
+        const bool sparse = !step && sparse_round(ng, M, lo.P, (uint32_t)S * (uint32_t)sizeof(E));
         if (paired && C >= kPairChunks && (ng == 0 || sparse)) {
             // leave the partner none of this member's rows to claim
             used |= 1u << (b & 1);

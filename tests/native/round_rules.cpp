@@ -1,0 +1,32 @@
+// Host-only checks of rules on a round's shape (built and run by
+// tests/test_round_rules.py; no kernel is launched).
+#include <cstdio>
+
+#include "engine.h"
+
+using namespace sssp;
+
+static int failures = 0;
+#define CHECK(c)                                                        \
+    do {                                                                \
+        if (!(c)) {                                                     \
+            std::fprintf(stderr, "FAILED line %d: %s\n", __LINE__, #c); \
+            ++failures;                                                 \
+        }                                                               \
+    } while (0)
+
+int main() {
+    // rows are read by groups only while the groups' lines are fewer bytes than the rows'
+    // parts, whatever the number of rows and partitions
+    for (uint32_t bytes : {64u, 128u, 256u, 528u, 1024u, 16384u})
+        for (int P : {1, 4, 16, 64})
+            for (uint32_t m : {1u, 64u, 65u, 1000u, 25613u, 65536u})
+                for (uint32_t ng = 0; ng <= 64; ++ng)
+                    CHECK(!sparse_round(ng, m, P, bytes) || (ng * 128u <= bytes && m > 64u && ng <= kSparseGroups));
+    // the stragglers of large dense graphs still are
+    CHECK(sparse_round(1, 20628, 16, 1024) && sparse_round(8, 60421, 16, 1024));
+    CHECK(sparse_round(4, 25613, 16, 528) && !sparse_round(5, 25613, 16, 528));
+    if (failures) return 1;
+    std::printf("round rules ok\n");
+    return 0;
+}
