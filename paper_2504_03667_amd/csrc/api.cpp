@@ -252,7 +252,7 @@ int solve(const int32_t* W, int64_t ld, int32_t n, int32_t src, int32_t* dist, i
     if (single) {
         if (n > max_single_n())
             return fail(SSSP_EUNSUPPORTED, "n=%d exceeds the one-workgroup limit %d", n, max_single_n());
-        int threads = tuning && tuning->threads ? tuning->threads : single_threads(n);
+        int threads = tuning && tuning->threads ? tuning->threads : single_threads(n, (flags & SSSP_FLAG_LITERAL) != 0);
         e = launch_single(a, threads, stream);
         if (e != hipSuccess) return hip_fail(e, "launch(one-workgroup solve)");
     } else {

@@ -97,7 +97,7 @@ extern "C" int sssp_dense_solve_noalloc(const int32_t* W, int64_t ld, int32_t n,
     if (single) {
         if (n > max_single_n()) return set_error(SSSP_EUNSUPPORTED, "n exceeds the one-workgroup limit");
         // the one-workgroup kernel only writes the control block's status and statistics
-        e = launch_single(a, single_threads(n), s);
+        e = launch_single(a, single_threads(n, (flags & SSSP_FLAG_LITERAL) != 0), s);
         if (e != hipSuccess) return set_error(SSSP_EDEVICE, "launch of the one-workgroup solve failed");
     } else {
         int nwg = 0, S = 0;

@@ -36,8 +36,11 @@ hipError_t launch_single(const SolveArgs& a, int threads, hipStream_t s);
 // fewer batches, fewer pass its barriers sooner; kernel times with 256, 512, 1024: n=128
 // 78.8, 79.1, 80.9 us; n=256, p=0.1 71.8, 69.0, 69.6; n=700, p=0.1 76.6, 70.5, 70.3,
 // p=0.5 99.4, 95.7, 98.0; n=1024, p=0.1 96.6, 82.0, 76.7, p=0.5 113.4, 102.7, 98.2, of
-// two rows a round on average (p=0.01) 809, 862, 846.
-inline int single_threads(int32_t n) { return n <= 128 ? 256 : n <= 768 ? 512 : 1024; }
+// two rows a round on average (p=0.01) 809, 862, 846.  Literal steps read a row each and
+// are all barriers (n=768 906, 1018, 1049; n=1024 1222, 1386, 1412).
+inline int single_threads(int32_t n, bool literal) {
+    return n <= 128 || (literal && n <= 1024) ? 256 : !literal && n <= 768 ? 512 : 1024;
+}
 int max_single_n();
 
 // plain: ordinary launch of the same kernel, the grid already bounded by the

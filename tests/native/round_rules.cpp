@@ -3,6 +3,7 @@
 #include <cstdio>
 
 #include "engine.h"
+#include "sssp_internal.h"
 
 using namespace sssp;
 
@@ -26,6 +27,11 @@ int main() {
     // the stragglers of large dense graphs still are
     CHECK(sparse_round(1, 20628, 16, 1024) && sparse_round(8, 60421, 16, 1024));
     CHECK(sparse_round(4, 25613, 16, 528) && !sparse_round(5, 25613, 16, 528));
+    // threads of the one-workgroup solve: literal steps take the fewest that hold the columns
+    for (int n : {1, 128, 129, 300, 768, 769, 1000, 1024}) CHECK(single_threads(n, true) == 256);
+    CHECK(single_threads(128, false) == 256 && single_threads(129, false) == 512);
+    CHECK(single_threads(768, false) == 512 && single_threads(769, false) == 1024);
+    for (int n : {1025, 5000, 16384}) CHECK(single_threads(n, true) == 1024 && single_threads(n, false) == 1024);
     if (failures) return 1;
     std::printf("round rules ok\n");
     return 0;
