@@ -89,7 +89,7 @@ int32_t alone_max_n(int32_t c) { return std::max(1024, 2 * c); }
 // n that is not split, by c.
 template <class Alone>
 int32_t concurrent_columns(const sssp_instance* inst, int32_t count, int32_t nwg, int32_t cap, Alone alone) {
-    if (cap < 2) return 0;
+    if (cap < 3) return 0;  // gangs of two: see alone_max_n
     for (int32_t c = 64; c <= 4096; c *= 2) {
         int64_t parts = 0;
         bool fits = true, split = false;

@@ -131,6 +131,11 @@ static void sizes_that_are_split() {
             CHECK(max_parts() == 1 || (max_parts() >= 3 && last.parts.size() <= 256));
             CHECK(max_parts() == 1 || last.items[0].S * (max_parts() - 1) < n);
         }
+    for (int workgroups = 1; workgroups <= 12; ++workgroups) {
+        sssp_tuning t{};
+        t.workgroups = workgroups;
+        CHECK(solve({6000}, &t) == SSSP_OK && max_parts() != 2 && (max_parts() > 1) == (workgroups >= 6));
+    }
     CHECK(solve(std::vector<int32_t>(96, 2000)) == SSSP_OK && max_parts() == 1);
     CHECK(solve(std::vector<int32_t>(48, 2000)) == SSSP_OK && max_parts() > 1);
     CHECK(held.empty());
