@@ -71,26 +71,32 @@ int32_t gang_cap(int32_t cus, int32_t served, int32_t nwg) {
 }
 
 // Largest n that a one-shot call solves by one workgroup where it splits the others into
-// slices of c columns: one of more vertices makes a gang of at least three.  A round of a
-// gang takes 3 us, from slices of more than 256 columns on 5; one workgroup's takes 1.8
-// (n=1000) to 3.6 (n=4000) and streams rows at 25 to 60 GB/s.  So smaller graphs and gangs
-// of two lose where the rounds are many, and win little where the rows are dense (16 to 96
-// graphs, all split against all alone, of 950 rounds and of 13: n=1000 1.6 and 0.83,
-// n=2000 c=1024 2.2 and 0.88, n=4000 c=2048 1.9 and 0.81, c=1024 1.6 and 0.48, c=256 0.94
-// and 0.22).
-int32_t alone_max_n(int32_t c) { return std::max(1024, 2 * c); }
+// slices of c columns: one of more vertices makes a gang of at least three, or of two from
+// 4097 vertices on.  A round of a gang takes 3 us, from slices of more than 256 columns on
+// 5; one workgroup's takes 1.8 (n=1000) to 3.6 (n=4000) and streams rows at 25 to 60 GB/s.
+// So smaller graphs and gangs of two lose where the rounds are many, and win less where
+// the rows are dense (16 to 100 graphs, all split against all alone, of about 950 rounds
+// and of 4 to 13: n=300 1.5 and 1.4, n=1000 1.6 and 0.83, n=2000 c=1024 2.2 and 0.88,
+// n=4000 c=2048 1.9 and 0.81, c=1024 1.6 and 0.48, c=256 0.94 and 0.22, n=4300 c=4096 1.7
+// and 0.57, n=8000 1.1 and 0.73).
+constexpr int32_t kSmallN = 768;
+int32_t alone_max_n(int32_t c) { return c >= 4096 ? c : std::max(kSmallN, 2 * c); }
+// Widest slice whose gang runs the short rounds (see gang_by_size in kernels.hip).
+constexpr int32_t kNarrowColumns = 256;
 
 // Columns per member that split a set of instances so that all their workgroups run at
 // once: the narrowest of 64 to 4096 whose parts, at most `cap` an instance, fit the nwg
 // workgroups, or 0 when not even 4096 does, gangs are not allowed or nothing is split
 // (then the instances fill the GPU one workgroup each).  A compute unit alone streams rows
 // at 25 to 60 GB/s, so few instances on one workgroup each leave most of the memory's
-// 7 TB/s idle: 24 graphs of up to 6000 vertices 2.6 ms, split 0.53.  `alone`: the largest
-// n that is not split, by c.
+// 7 TB/s idle: 24 graphs of up to 6000 vertices 2.6 ms, split 0.45.  `alone`: the largest
+// n that is not split, by c.  *spare (may be null): workgroups left over.
 template <class Alone>
-int32_t concurrent_columns(const sssp_instance* inst, int32_t count, int32_t nwg, int32_t cap, Alone alone) {
+int32_t concurrent_columns(const sssp_instance* inst, int32_t count, int32_t nwg, int32_t cap, Alone alone,
+                           int32_t* spare = nullptr) {
+    if (spare) *spare = 0;
     if (cap < 3) return 0;  // gangs of two: see alone_max_n
-    for (int32_t c = 64; c <= 4096; c *= 2) {
+    for (int32_t c = 64; c <= 4096; c += c & (c - 1) ? c / 3 : c / 2) {  // 64, 96, 128, 192, ...
         int64_t parts = 0;
         bool fits = true, split = false;
         for (int32_t i = 0; i < count && parts <= nwg; ++i) {
@@ -99,7 +105,10 @@ int32_t concurrent_columns(const sssp_instance* inst, int32_t count, int32_t nwg
             fits = fits && (int64_t)inst[i].n <= (int64_t)cap * max_batch_slice();
             split = split || gang;
         }
-        if (fits && parts <= nwg) return split ? c : 0;
+        if (fits && parts <= nwg) {
+            if (spare && split) *spare = nwg - (int32_t)parts;
+            return split ? c : 0;
+        }
     }
     return 0;
 }
@@ -130,7 +139,10 @@ void group_shape(int32_t n, int32_t want, int32_t cols, int32_t* S, int32_t* par
 // solved by a gang of workgroups.  lc (may be null): per instance, solve it
 // with the label-correcting method (never for shared matrices).
 // split: instances of shared matrices are split like the others (when there are
-// not enough of them to fill the GPU by themselves).
+// not enough of them to fill the GPU by themselves).  spare: workgroups that the largest
+// instances which single_max_n leaves whole may take beyond one each, for slices of
+// kNarrowColumns (where many instances make the others' wide, one of 4000 dense vertices
+// left whole is the launch's last to end).
 // group_k > 1 (with group_ok marking the eligible instances): instances of a
 // shared matrix are solved group_k at a time in lockstep by gangs of group_cols
 // columns per member (kMethodGroup items, queued between the other instances
@@ -138,7 +150,7 @@ void group_shape(int32_t n, int32_t want, int32_t cols, int32_t* S, int32_t* par
 int build(const sssp_instance* inst, const Source* src, int32_t count, int32_t single_max_n,
           int32_t gang_columns, int32_t max_parts, Build* out, const char* lc = nullptr,
           std::vector<int32_t>* order_out = nullptr, int32_t group_k = 0, int32_t group_cols = 0,
-          const char* group_ok = nullptr, bool split = false) {
+          const char* group_ok = nullptr, bool split = false, int32_t spare = 0) {
     std::vector<int32_t> order(count);
     for (int32_t i = 0; i < count; ++i) order[i] = i;
     std::map<std::pair<const void*, int64_t>, int32_t> uses;
@@ -215,11 +227,18 @@ int build(const sssp_instance* inst, const Source* src, int32_t count, int32_t s
         b.src = I.src;
         const bool use_lc = lc && lc[order[k]] && !shared[order[k]];
         b.method = use_lc ? kMethodLabelCorrecting : kMethodDijkstra;
-        if (!use_lc && (I.n <= single_max_n || shared[order[k]])) {
+        int32_t cols = use_lc ? kLcColumns : gang_columns;
+        bool alone = !use_lc && (I.n <= single_max_n || shared[order[k]]);
+        const int32_t narrow = (I.n + kNarrowColumns - 1) / kNarrowColumns;
+        if (alone && I.n > kSmallN && narrow - 1 <= spare && narrow <= max_parts) {
+            alone = false;
+            cols = kNarrowColumns;
+            spare -= narrow - 1;
+        }
+        if (alone) {
             b.parts = 1;
             b.S = I.n;
         } else {
-            const int32_t cols = use_lc ? kLcColumns : gang_columns;
             int64_t p = ((int64_t)I.n + cols - 1) / cols;
             p = std::max<int64_t>(use_lc ? 1 : 2, std::min<int64_t>(p, max_parts));
             int64_t s = ((int64_t)I.n + p - 1) / p;
@@ -526,8 +545,9 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
         capturing = hipStreamCaptureStatusActive;
     }
     const int32_t cap = gang_cap(cus, served_workgroups(dev), nwg);
+    int32_t spare = 0;
     int32_t cols = flags & (SSSP_FLAG_LABEL_CORRECTING | SSSP_FLAG_LITERAL) || capturing != hipStreamCaptureStatusNone
-                       ? 0 : concurrent_columns(inst, count, nwg, cap, alone_max_n);
+                       ? 0 : concurrent_columns(inst, count, nwg, cap, alone_max_n, &spare);
     // stream-ordered scratch: allocated and freed in the stream's order, so the
     // call stays asynchronous (copies from pageable memory are staged at once)
     BatchItem* d_items = nullptr;
@@ -543,7 +563,7 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
         b = Build();
         rc = build(inst, src.data(), count, cols ? alone_max_n(cols) : max_batch_single_n(), cols ? cols : 4096,
                    cols ? cap : std::max(2, nwg / 2), &b,
-                   lc.empty() ? nullptr : lc.data(), nullptr, 0, 0, nullptr, cols != 0);
+                   lc.empty() ? nullptr : lc.data(), nullptr, 0, 0, nullptr, cols != 0, cols ? spare : 0);
         if (rc) return rc;
         e = b.arena_bytes ? hipMallocAsync((void**)&d_arena, b.arena_bytes, s) : hipSuccess;
         if (e == hipSuccess || !cols) break;

@@ -119,16 +119,16 @@ static void beside_a_server() {
 // Small graphs are solved by one workgroup, and so are those of which the others' slices
 // would make a gang of two; all workgroups of a split launch run at once.
 static void sizes_that_are_split() {
-    for (int n : {1, 64, 65, 1000, 1024}) {
+    for (int n : {1, 64, 65, 700, 768}) {
         CHECK(solve({n}) == SSSP_OK && max_parts() == 1);
         CHECK(solve({n, n, 6000}) == SSSP_OK && max_parts() > 1);
         for (const BatchItem& it : last.items) CHECK((it.n == n) == (it.parts == 1));
     }
-    for (int n : {1025, 2049, 4097, 6001, 16384}) CHECK(solve({n}) == SSSP_OK && max_parts() > 1);
+    for (int n : {769, 2049, 4097, 6001, 16384}) CHECK(solve({n}) == SSSP_OK && max_parts() > 1);
     for (int count = 1; count <= 300; ++count)
-        for (int n : {1025, 1500, 2048, 2049, 4000, 4100, 6000, 9000}) {
+        for (int n : {769, 1500, 2048, 2049, 4000, 4100, 6000, 9000}) {
             CHECK(solve(std::vector<int32_t>(count, n)) == SSSP_OK);
-            CHECK(max_parts() == 1 || (max_parts() >= 3 && last.parts.size() <= 256));
+            CHECK(max_parts() == 1 || (max_parts() >= (n > 4096 ? 2 : 3) && last.parts.size() <= 256));
             CHECK(max_parts() == 1 || last.items[0].S * (max_parts() - 1) < n);
         }
     for (int workgroups = 1; workgroups <= 12; ++workgroups) {
@@ -136,6 +136,14 @@ static void sizes_that_are_split() {
         t.workgroups = workgroups;
         CHECK(solve({6000}, &t) == SSSP_OK && max_parts() != 2 && (max_parts() > 1) == (workgroups >= 6));
     }
+    // 64 instances of three members; of the rest, the largest have the workgroups left over
+    std::vector<int32_t> mixed(64, 5500);
+    for (int n : {4000, 3000, 1000, 769, 768, 200}) mixed.push_back(n);
+    CHECK(solve(mixed) == SSSP_OK && last.parts.size() <= 256);
+    for (const BatchItem& it : last.items)
+        CHECK(it.parts == (it.n == 5500 ? 3 : it.n <= 768 ? 1 : (it.n + 255) / 256));
+    mixed.insert(mixed.end(), 4, 4000);
+    CHECK(solve(mixed) == SSSP_OK && last.parts.size() <= 256);
     CHECK(solve(std::vector<int32_t>(96, 2000)) == SSSP_OK && max_parts() == 1);
     CHECK(solve(std::vector<int32_t>(48, 2000)) == SSSP_OK && max_parts() > 1);
     CHECK(held.empty());

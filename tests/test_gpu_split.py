@@ -61,8 +61,8 @@ def test_one_shot_and_plan(sp, sizes, copies):
                 check(("plan", flags), stats)
 
 
-@pytest.mark.parametrize("sizes,copies", [([1025], 1), ([1026, 1025], 2), ([2049], 40), ([4100, 300, 1500], 5),
-                                          ([5001], 30), ([6001, 1024], 16), ([9000], 3)])
+@pytest.mark.parametrize("sizes,copies", [([769], 1), ([1026, 1025], 2), ([2049], 40), ([4100, 300, 1500], 5),
+                                          ([5001], 30), ([6001, 768], 16), ([9000], 3)])
 def test_one_shot_splits(sp, sizes, copies):
     """Gangs of the one-shot call: slices of 64 to 2048 columns whose last is partial,
     beside instances that are not split; few rounds and many; zero weights."""
