@@ -174,7 +174,8 @@ int sssp_last_trace(void* stream, int64_t* t_ns, int32_t* rows, int32_t cap, int
  * pointing at device buffers; instances may share W) in ONE persistent launch
  * in which workgroups pull work from a ticket counter, largest instance first.
  * Few instances are split over gangs of workgroups so that all run at once on the
- * whole GPU; with more, an instance with n <= sssp_batch_max_n() is solved by one
+ * whole GPU (those too small to gain excepted; not while a server's kernel holds most
+ * of it); with more, an instance with n <= sssp_batch_max_n() is solved by one
  * workgroup, a larger one by a gang of workgroups that split its columns.  With
  * SSSP_FLAG_LABEL_CORRECTING every instance whose matrix is not shared by 32
  * or more instances is solved with the label-correcting method (see that

@@ -6,8 +6,8 @@
 //
 // A workgroup owns a contiguous slice of S columns (vertices) of the matrix —
 // the single-GPU form of the paper's 1-D column division (Section III-B): it
-// keeps dist[], pred[] and visited[] of those vertices in registers and writes
-// dist and pred out at the end, so every column has exactly one writer and no
+// keeps dist[], pred[] and visited[] (the top bit of a settled dist, see Cols) of
+// those vertices in registers and writes dist and pred out at the end, so every column has exactly one writer and no
 // atomics are needed on dist or pred.
 //
 // Thread layout inside a workgroup of T threads.  The slice is cut into

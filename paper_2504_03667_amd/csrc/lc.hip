@@ -12,8 +12,8 @@ namespace sssp {
 
 template <int T, int G, int U, bool NT>
 __global__ __launch_bounds__(T) void k_lc(const int32_t* __restrict__ W, int64_t ld, int32_t n, int32_t src,
-                                          int32_t* __restrict__ dist, int32_t* __restrict__ pred, uint32_t flags,
-                                          int32_t S, long long timeout, Ctl* __restrict__ ctl,
+                                          int32_t* __restrict__ dist, int32_t* __restrict__ pred, int32_t S,
+                                          long long timeout, Ctl* __restrict__ ctl,
                                           char* __restrict__ words) {
     SharedSolve<T>& sh = g_sh<T>;
     SolveStats st = {0, 0, 0, 0, 0};
@@ -60,14 +60,13 @@ static hipError_t launch_lc_t(const SolveArgs& a, int nwg, int S, long long time
     int32_t n = a.n, src = a.src;
     int32_t* dist = a.dist;
     int32_t* pred = a.pred;
-    uint32_t flags = a.flags;
     Ctl* ctl = a.ctl;
     if (plain) {
-        hipLaunchKernelGGL((k_lc<T, G, U, NT>), dim3(nwg), dim3(T), 0, s, W, ld, n, src, dist, pred, flags, S, timeout,
+        hipLaunchKernelGGL((k_lc<T, G, U, NT>), dim3(nwg), dim3(T), 0, s, W, ld, n, src, dist, pred, S, timeout,
                            ctl, words);
         return hipGetLastError();
     }
-    void* args[] = {&W, &ld, &n, &src, &dist, &pred, &flags, &S, &timeout, &ctl, &words};
+    void* args[] = {&W, &ld, &n, &src, &dist, &pred, &S, &timeout, &ctl, &words};
     return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_lc<T, G, U, NT>), dim3(nwg), dim3(T), args, 0, s);
 }
 

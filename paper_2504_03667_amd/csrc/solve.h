@@ -28,8 +28,6 @@ struct SharedSolve {
     uint64_t mrg[4 * T];
     uint32_t pre[T];
     uint32_t cnt[T];
-    uint64_t rk;  // results for the whole workgroup (lc.h, multi.h)
-    uint32_t rz, rm;
     // read_records results for the whole workgroup, by exchange parity.  A round in
     // which the slice reads no row has no barrier between the reads of one exchange's
     // result and wave 0's stores of the next: those go to the other slot, and wave 0
@@ -43,7 +41,7 @@ struct SharedSolve {
     uint32_t stage_late;  // a bucket entry did not arrive in time (set once; the solve then ends)
     int32_t item;
     uint32_t flag;
-    uint64_t min3[3];    // solve_single: lowest key of a round, by round number mod 3
+    uint64_t min3[3];    // solve_single: lowest key of a round, by round number mod 3; [0]: publish, wide slices
     uint32_t count3[3];  // ... and its bucket's size
     uint32_t open3[3];   // groups a round can lower, by round number mod 3 (also solve_gang)
     uint32_t listed;     // ... of a sparse round, how many are in group
@@ -135,9 +133,8 @@ __device__ __forceinline__ uint32_t owner_bit(const Layout& lo, int64_t v, int w
 // by that chain, not by bytes, so it has as few workgroup barriers as the data
 // needs: one when the merge is complete, one when the next minimum is known,
 // one when the next bucket is listed (in no particular order: a round's result
-// is a minimum over its rows).  When the owners fit in wave 0 (n <= 256) it finds
-// both by itself and the second barrier falls away.  (Nine barriers and four
-// block reductions before: n=256, p=0.1, 36 rounds, 97 us a call, now 70.)
+// is a minimum over its rows).  (Nine barriers and four block reductions before:
+// n=256, p=0.1, 36 rounds, 97 us a call, now 70.)
 // ---------------------------------------------------------------------------
 template <int T, int G, int U, typename E>
 __device__ __forceinline__ void solve_single(const E* __restrict__ W, int64_t ld, int32_t n, int32_t src,
