@@ -371,9 +371,9 @@ int sssp_edges_to_csr(const int32_t* eu, const int32_t* ev, const int32_t* ew, i
  * order settles first, recovered by a pass over the vertices those edges touch
  * (one workgroup per distance; SSSP_STATUS_ZERO_FALLBACK, informational).
  * tuning->workgroups (may be NULL) sets the grid (default about n / 256; never
- * above 1024 nor the co-resident count, less what a server's kernel holds); those of
- * its workgroups that other work keeps off the GPU for the launch's first 0.2 ms or
- * longer take no part.  Stats: ROUNDS = sweeps, SETTLED = edge
+ * above 1024 nor the co-resident count, less what a server's kernel holds if that is
+ * at most three quarters of the GPU); those of its workgroups that other work keeps
+ * off the GPU for the launch's first 0.2 ms or longer take no part.  Stats: ROUNDS = sweeps, SETTLED = edge
  * lists relaxed (the sweep count may differ between runs; dist and pred do not).
  * Allocates stream-ordered scratch of about 100 n bytes.  Asynchronous. */
 int sssp_csr_solve(const int64_t* row_ptr, const int32_t* col, const int32_t* w, int32_t n, int32_t src,

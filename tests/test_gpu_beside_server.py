@@ -77,6 +77,18 @@ def test_csr_solve(sp, held):
     assert {n: sp.sssp_csr_grid(n)[0] for n, _, _ in cases} == full
 
 
+def test_csr_grid_beside_a_server_on_most_of_the_gpu(sp):
+    """The solve starts when the server leaves, with the whole GPU."""
+    full = sp.sssp_csr_grid(40000)[0]
+    csr, (dr, pr, _) = lists(20000, 6)
+    busy = Busy(sp, 248, idle_park_ms=50)
+    with busy.srv:
+        assert sp.sssp_csr_grid(40000)[0] == full
+        d, p = sp.csr_solve(*csr, 0)
+        assert sp.sssp_last_status()[0] & 3 == 0
+        assert np.array_equal(d.cpu().numpy(), dr) and np.array_equal(p.cpu().numpy(), pr)
+
+
 def test_csr_grid_beside_a_parked_server(sp):
     full = sp.sssp_csr_grid(40000)[0]
     csr, (dr, pr, _) = lists(20000, 3)
