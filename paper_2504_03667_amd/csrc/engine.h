@@ -661,10 +661,12 @@ __device__ __forceinline__ void stream_rows(Cols<G, E>& cs, const Layout& lo, co
 // (measured: 0.7 us a batch); by groups, about 1 + m / 2048 for each of the ng.
 // (n=65536, p=0.5, sources with a few vertices beyond the large last bucket:
 // 2.5 ms without, 1.2 with.)
-// `bytes`: of the slice's part of a row.  Where all members of a gang read at once the
-// memory's rate bounds them, a group's 16 bytes cost a line of 128, and rows are read by
-// groups only while these come to less than the part whole (n=33000, p=0.05, ten of 33
-// groups left: 602 us whole, 938 by groups).
+// `bytes`: of the slice's part of a row, where all workgroups of the GPU read at once and
+// the memory's rate bounds them (else all ones): a group's 16 bytes cost a line of 128,
+// and rows are read by groups only while these come to less than the part whole (n=33000,
+// p=0.05, ten of 33 groups left: 602 us whole, 938 by groups).  A gang among others is
+// bound by its waits (a plan of 62 compact instances, slices of 928 columns: 180 us,
+// under this limit too 241).
 constexpr uint32_t kSparseGroups = 16;
 constexpr uint32_t kLineBytes = 128;
 __host__ __device__ __forceinline__ bool sparse_round(uint32_t ng, uint32_t m, int P, uint32_t bytes) {

@@ -903,7 +903,8 @@ __device__ __forceinline__ bool solve_gang(const E* __restrict__ W, int64_t ld, 
             if (late) sh.stage_late = 1u;
         };
         const uint32_t C = (M + kCap - 1) / kCap;
-        const bool sparse = !step && sparse_round(ng, M, lo.P, (uint32_t)S * (uint32_t)sizeof(E));
+        // the whole-GPU kernels stream from memory at its rate; batched and served gangs do not
+        const bool sparse = !step && sparse_round(ng, M, lo.P, NT ? (uint32_t)S * (uint32_t)sizeof(E) : ~0u);
         if (paired && C >= kPairChunks && (ng == 0 || sparse)) {
             // leave the partner none of this member's rows to claim
             used |= 1u << (b & 1);
