@@ -81,22 +81,36 @@ int32_t gang_cap(int32_t cus, int32_t served, int32_t nwg) {
 // and 0.57, n=8000 1.1 and 0.73).
 constexpr int32_t kSmallN = 768;
 int32_t alone_max_n(int32_t c) { return c >= 4096 ? c : std::max(kSmallN, 2 * c); }
-// Widest slice whose gang runs the short rounds (see gang_by_size in kernels.hip).
-constexpr int32_t kNarrowColumns = 256;
+
+// Columns of the slices into which the largest of the instances left whole (those of up to
+// alone_n vertices) are split with `spare` workgroups: 256, whose rounds are the short
+// ones, 512 or 1024 if that does for all of them.  (Where many instances make the others'
+// slices wide, a dense graph of 4000 vertices left whole is the launch's last to end.)
+bool spare_split(int32_t n, int32_t c, int32_t alone_n) { return n <= alone_n && n > std::max(kSmallN, 2 * c); }
+int32_t spare_columns(const sssp_instance* inst, int32_t count, int32_t alone_n, int32_t spare) {
+    for (int32_t c = 256; c < 1024; c *= 2) {
+        int64_t need = 0;
+        for (int32_t i = 0; i < count; ++i)
+            if (spare_split(inst[i].n, c, alone_n)) need += (inst[i].n + c - 1) / c - 1;
+        if (need <= spare) return c;
+    }
+    return 1024;
+}
 
 // Columns per member that split a set of instances so that all their workgroups run at
 // once: the narrowest of 64 to 4096 whose parts, at most `cap` an instance, fit the nwg
 // workgroups, or 0 when not even 4096 does, gangs are not allowed or nothing is split
 // (then the instances fill the GPU one workgroup each).  A compute unit alone streams rows
 // at 25 to 60 GB/s, so few instances on one workgroup each leave most of the memory's
-// 7 TB/s idle: 24 graphs of up to 6000 vertices 2.6 ms, split 0.45.  `alone`: the largest
-// n that is not split, by c.  *spare (may be null): workgroups left over.
+// 7 TB/s idle: 24 graphs of up to 6000 vertices 2.6 ms, split 0.49.  `alone`: the largest
+// n that is not split, by c.  *spare (may be null): workgroups left over.  fine: 64, 96,
+// 128, 192, ... are tried, not powers of two only.
 template <class Alone>
 int32_t concurrent_columns(const sssp_instance* inst, int32_t count, int32_t nwg, int32_t cap, Alone alone,
-                           int32_t* spare = nullptr) {
+                           bool fine, int32_t* spare = nullptr) {
     if (spare) *spare = 0;
     if (cap < 3) return 0;  // gangs of two: see alone_max_n
-    for (int32_t c = 64; c <= 4096; c += c & (c - 1) ? c / 3 : c / 2) {  // 64, 96, 128, 192, ...
+    for (int32_t c = 64; c <= 4096; c += !fine ? c : c & (c - 1) ? c / 3 : c / 2) {
         int64_t parts = 0;
         bool fits = true, split = false;
         for (int32_t i = 0; i < count && parts <= nwg; ++i) {
@@ -141,8 +155,7 @@ void group_shape(int32_t n, int32_t want, int32_t cols, int32_t* S, int32_t* par
 // split: instances of shared matrices are split like the others (when there are
 // not enough of them to fill the GPU by themselves).  spare: workgroups that the largest
 // instances which single_max_n leaves whole may take beyond one each, for slices of
-// kNarrowColumns (where many instances make the others' wide, one of 4000 dense vertices
-// left whole is the launch's last to end).
+// spare_cols (see spare_columns).
 // group_k > 1 (with group_ok marking the eligible instances): instances of a
 // shared matrix are solved group_k at a time in lockstep by gangs of group_cols
 // columns per member (kMethodGroup items, queued between the other instances
@@ -150,7 +163,7 @@ void group_shape(int32_t n, int32_t want, int32_t cols, int32_t* S, int32_t* par
 int build(const sssp_instance* inst, const Source* src, int32_t count, int32_t single_max_n,
           int32_t gang_columns, int32_t max_parts, Build* out, const char* lc = nullptr,
           std::vector<int32_t>* order_out = nullptr, int32_t group_k = 0, int32_t group_cols = 0,
-          const char* group_ok = nullptr, bool split = false, int32_t spare = 0) {
+          const char* group_ok = nullptr, bool split = false, int32_t spare = 0, int32_t spare_cols = 0) {
     std::vector<int32_t> order(count);
     for (int32_t i = 0; i < count; ++i) order[i] = i;
     std::map<std::pair<const void*, int64_t>, int32_t> uses;
@@ -229,11 +242,13 @@ int build(const sssp_instance* inst, const Source* src, int32_t count, int32_t s
         b.method = use_lc ? kMethodLabelCorrecting : kMethodDijkstra;
         int32_t cols = use_lc ? kLcColumns : gang_columns;
         bool alone = !use_lc && (I.n <= single_max_n || shared[order[k]]);
-        const int32_t narrow = (I.n + kNarrowColumns - 1) / kNarrowColumns;
-        if (alone && I.n > kSmallN && narrow - 1 <= spare && narrow <= max_parts) {
-            alone = false;
-            cols = kNarrowColumns;
-            spare -= narrow - 1;
+        if (alone && spare > 0 && spare_split(I.n, spare_cols, single_max_n)) {
+            const int32_t p = (I.n + spare_cols - 1) / spare_cols;
+            if (p - 1 <= spare && p <= max_parts) {
+                alone = false;
+                cols = spare_cols;
+                spare -= p - 1;
+            }
         }
         if (alone) {
             b.parts = 1;
@@ -547,7 +562,7 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
     const int32_t cap = gang_cap(cus, served_workgroups(dev), nwg);
     int32_t spare = 0;
     int32_t cols = flags & (SSSP_FLAG_LABEL_CORRECTING | SSSP_FLAG_LITERAL) || capturing != hipStreamCaptureStatusNone
-                       ? 0 : concurrent_columns(inst, count, nwg, cap, alone_max_n, &spare);
+                       ? 0 : concurrent_columns(inst, count, nwg, cap, alone_max_n, true, &spare);
     // stream-ordered scratch: allocated and freed in the stream's order, so the
     // call stays asynchronous (copies from pageable memory are staged at once)
     BatchItem* d_items = nullptr;
@@ -563,7 +578,8 @@ int sssp_dense_solve_batched(const sssp_instance* inst, int32_t count, uint32_t 
         b = Build();
         rc = build(inst, src.data(), count, cols ? alone_max_n(cols) : max_batch_single_n(), cols ? cols : 4096,
                    cols ? cap : std::max(2, nwg / 2), &b,
-                   lc.empty() ? nullptr : lc.data(), nullptr, 0, 0, nullptr, cols != 0, cols ? spare : 0);
+                   lc.empty() ? nullptr : lc.data(), nullptr, 0, 0, nullptr, cols != 0, cols ? spare : 0,
+                   cols ? spare_columns(inst, count, alone_max_n(cols), spare) : 0);
         if (rc) return rc;
         e = b.arena_bytes ? hipMallocAsync((void**)&d_arena, b.arena_bytes, s) : hipSuccess;
         if (e == hipSuccess || !cols) break;
@@ -694,7 +710,8 @@ int sssp_batch_plan_create(const sssp_instance* inst, int32_t count, uint32_t fl
         int dev = 0;
         (void)hipGetDevice(&dev);
         p->gang_max = gang_cap(cus, served_workgroups(dev), p->nwg);
-        if (const int32_t c0 = concurrent_columns(inst, count, p->nwg, p->gang_max, [](int32_t c) { return c; }))
+        if (const int32_t c0 =
+                concurrent_columns(inst, count, p->nwg, p->gang_max, [](int32_t c) { return c; }, false))
             for (int32_t c : {c0, 2 * c0, 4 * c0})
                 if (c <= 4096 && c < nmax) cands.push_back(Cand{c, c, true});
     }

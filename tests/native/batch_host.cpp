@@ -142,8 +142,14 @@ static void sizes_that_are_split() {
     CHECK(solve(mixed) == SSSP_OK && last.parts.size() <= 256);
     for (const BatchItem& it : last.items)
         CHECK(it.parts == (it.n == 5500 ? 3 : it.n <= 768 ? 1 : (it.n + 255) / 256));
+    // more of them: wider slices, so that it does for all, then for the largest
     mixed.insert(mixed.end(), 4, 4000);
     CHECK(solve(mixed) == SSSP_OK && last.parts.size() <= 256);
+    for (const BatchItem& it : last.items)
+        CHECK(it.parts == (it.n == 5500 ? 3 : it.n > 1024 ? (it.n + 511) / 512 : 1));
+    mixed.insert(mixed.end(), 14, 4000);
+    CHECK(solve(mixed) == SSSP_OK && last.parts.size() <= 256);
+    for (const BatchItem& it : last.items) CHECK(it.n != 4000 || it.parts == 4 || it.parts == 1);
     CHECK(solve(std::vector<int32_t>(96, 2000)) == SSSP_OK && max_parts() == 1);
     CHECK(solve(std::vector<int32_t>(48, 2000)) == SSSP_OK && max_parts() > 1);
     CHECK(held.empty());
